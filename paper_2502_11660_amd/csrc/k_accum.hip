@@ -19,7 +19,7 @@
 #include <algorithm>
 
 #include "common.hpp"
-#include "curve28.hpp"
+#include "curve29.hpp"
 
 namespace msm {
 namespace {
@@ -51,13 +51,15 @@ __device__ __forceinline__ uint32_t chunk_of(uint32_t e, uint32_t K, uint32_t X)
   return e < longer ? (uint32_t)(e / (K + 4)) : X + (uint32_t)((e - longer) / K);
 }
 
-// One lane per chunk, on the carry-free 28-bit field form (curve28.hpp):
-// points are converted from their 12-word records as they are loaded, the
-// running sum stays in the 28-bit form and is converted back when it is
-// stored.  (Measured against the 12-word form: 2.16 vs 2.30 ms at n = 2^20.
-// Four waves per SIMD, reachable without spills when the addition forms C
-// and D first, measured no faster than three.  Reading keys and indices in
-// groups of four cut the kernel's HBM reads by 31% at the same time.)
+// One lane per chunk, on the signed 29-bit field form (curve29.hpp): points
+// are converted from their 12-word records as they are loaded, the running
+// sum stays in that form and is converted when it is stored (as signed
+// words, fe29.hpp: 28 shifts and ors a coordinate).  Bound by VALU issue at
+// a power-limited clock: 3090 VALU instructions an entry, 2347 of them
+// multiply-adds, issued in 89% of SIMD cycles; n = 2^20 with split digits,
+// sustained: 2.14 ms with the 28-bit core -> 1.90 ms (8.8 G entries/s).
+// (Four waves per SIMD measured no faster than three.  Reading keys and
+// indices in groups of four cut the kernel's HBM reads by 31%.)
 __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
                                                  const int64_t* __restrict__ segoff, uint32_t bb,
                                                  const uint32_t* __restrict__ key,
@@ -78,7 +80,7 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
   uint32_t cur = key[s];
   const bool open_left = (s > 0) && (key[s - 1] == cur);
   bool first_seg = true;
-  xytz28 acc = pt28_identity();
+  xytz29 acc = pt29_identity();
   // Keys and indices are read four at a time with 16-byte loads (chunk
   // lengths are multiples of 4, so a chunk starts on a 16-byte boundary; the arrays carry
   // 32 bytes of padding for a last group that ends past E1).  A lane's
@@ -113,13 +115,13 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
     if (k != cur) {
       uint32_t* dst = (first_seg && open_left) ? head + (size_t)ch * XYTZ_WORDS
                                                : buckets + (size_t)cur * XYTZ_WORDS;
-      st_xytz(dst, pt28_to_words(acc));
-      acc = pt28_identity();
+      st_xytz(dst, pt29_to_words(acc));
+      acc = pt29_identity();
       cur = k;
       first_seg = false;
     }
-    const xyu28 P = pt28_from(ld_xyu(entry_point(pts, segoff, bb, k, ie)));
-    acc = padd28_mixed_signed(acc, P, (ie >> 31) != 0u);
+    const xyu29 P = pt29_from(ld_xyu(entry_point(pts, segoff, bb, k, ie)));
+    acc = padd29_mixed_signed(acc, P, (ie >> 31) != 0u);
   }
   const bool open_right = (e < E1) && (key[e] == cur);
   uint32_t* dst;
@@ -129,7 +131,7 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
     dst = tail + (size_t)ch * XYTZ_WORDS;
   else
     dst = buckets + (size_t)cur * XYTZ_WORDS;
-  st_xytz(dst, pt28_to_words(acc));
+  st_xytz(dst, pt29_to_words(acc));
 }
 
 // chunk ch holds a tail partial: returns true, the bucket and its last chunk
@@ -188,10 +190,10 @@ __global__ void __launch_bounds__(256) k_merge_small(const uint32_t* __restrict_
   // the tail's bucket ends after chunk c
   const uint32_t bk = key[(uint32_t)chunk_start(c + 1, K, X) - 1];
   const uint32_t sp = chunk_of(offsets[bk + 1] - 1, K, X) - c;
-  xytz28 acc = pt28_from(ld_xytz(tail + (size_t)c * XYTZ_WORDS));
+  xytz29 acc = pt29_from(ld_xytz(tail + (size_t)c * XYTZ_WORDS));
   for (uint32_t j = 1; j <= sp; ++j)
-    acc = padd28_full(acc, pt28_from(ld_xytz(head + (size_t)(c + j) * XYTZ_WORDS)));
-  st_xytz(buckets + (size_t)bk * XYTZ_WORDS, pt28_to_words(acc));
+    acc = padd29_full(acc, pt29_from(ld_xytz(head + (size_t)(c + j) * XYTZ_WORDS)));
+  st_xytz(buckets + (size_t)bk * XYTZ_WORDS, pt29_to_words(acc));
 }
 
 // Long split buckets, one block each: the block's threads sum strided heads
@@ -220,33 +222,48 @@ __global__ void __launch_bounds__(LONG_THREADS) k_merge_long(const uint32_t* __r
     const uint32_t span = c1 - ch;
     const uint32_t nact = span < (uint32_t)LONG_THREADS ? span : (uint32_t)LONG_THREADS;
     if (threadIdx.x < nact) {
-      xytz28 acc = pt28_identity();
+      xytz29 acc = pt29_identity();
       for (uint32_t j = ch + 1 + threadIdx.x; j <= c1; j += LONG_THREADS)
-        acc = padd28_full(acc, pt28_from(ld_xytz(head + (size_t)j * XYTZ_WORDS)));
-      st_xytz(part[threadIdx.x], pt28_to_words(acc));
+        acc = padd29_full(acc, pt29_from(ld_xytz(head + (size_t)j * XYTZ_WORDS)));
+      st_xytz(part[threadIdx.x], pt29_to_words(acc));
     }
     __syncthreads();
     // fold partials [0, n) into [0, ceil(n / 2)) until one is left
     for (uint32_t n = nact; n > 1;) {
       const uint32_t half = (n + 1) >> 1;
       if (threadIdx.x + half < n) {
-        const xytz28 a = pt28_from(ld_xytz(part[threadIdx.x]));
-        const xytz28 o = pt28_from(ld_xytz(part[threadIdx.x + half]));
-        st_xytz(part[threadIdx.x], pt28_to_words(padd28_full(a, o)));
+        const xytz29 a = pt29_from(ld_xytz(part[threadIdx.x]));
+        const xytz29 o = pt29_from(ld_xytz(part[threadIdx.x + half]));
+        st_xytz(part[threadIdx.x], pt29_to_words(padd29_full(a, o)));
       }
       __syncthreads();
       n = half;
     }
     if (threadIdx.x == 0) {
-      const xytz28 t = pt28_from(ld_xytz(tail + (size_t)ch * XYTZ_WORDS));
+      const xytz29 t = pt29_from(ld_xytz(tail + (size_t)ch * XYTZ_WORDS));
       st_xytz(buckets + (size_t)b * XYTZ_WORDS,
-              pt28_to_words(padd28_full(t, pt28_from(ld_xytz(part[0])))));
+              pt29_to_words(padd29_full(t, pt29_from(ld_xytz(part[0])))));
     }
     __syncthreads();
   }
 }
 
+// One coordinate per lane: signed records (fe29.hpp) -> coordinates in
+// [0, 2p), the form the caller of msm_bucket_accumulate gets.
+__global__ void __launch_bounds__(256) k_records_unsigned(uint32_t* __restrict__ recs, size_t n) {
+  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (i >= 4 * n) return;
+  uint32_t* rec = recs + i * NL;
+  st_aos(rec, 0, fe_unsigned(ld_aos(rec, 0)));
+}
+
 }  // namespace
+
+int launch_records_unsigned(uint32_t* recs, size_t n, hipStream_t st) {
+  k_records_unsigned<<<(unsigned)((4 * n + 255) / 256), 256, 0, st>>>(recs, n);
+  HIPCHK(hipGetLastError());
+  return MSM_OK;
+}
 
 int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st) {
   const uint32_t* offsets = ws_at<uint32_t>(ws, pl.o_offsets);

@@ -22,7 +22,7 @@
 // job of the batch.
 #include "common.hpp"
 #include "convert.hpp"
-#include "curve28.hpp"
+#include "curve29.hpp"
 #include "quad.hpp"
 #include "wide_unit.hpp"
 
@@ -35,13 +35,18 @@ __device__ __forceinline__ size_t rec_index(uint32_t w, uint32_t nodes, uint32_t
   return ((size_t)w * nodes + n) * slots + s;
 }
 
+// Bucket sums and the lane levels' records are signed (fe29.hpp); the quad
+// and wide units take coordinates in [0, 2p): a lane level followed by one
+// of them stores that form (`uns`), and their own level 0 converts what it
+// loads.
+
 // One level h -> h+1, one addition per lane: addition a < h forms slot a,
 // addition h the total (slot h + 1); the lane of addition 0 also copies
 // slot h (= R.S), so that no lane of a wave idles through another's addition.
 __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__ in, uint32_t h,
                                                     uint32_t nodes_in, uint32_t w_lo,
                                                     uint32_t w_cnt, uint32_t* __restrict__ out,
-                                                    int to_u) {
+                                                    int to_u, int uns) {
   const uint32_t nodes_out = nodes_in >> 1, slots_in = h + 1, slots_out = h + 2;
   const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= (uint64_t)w_cnt * nodes_out * slots_in) return;
@@ -51,19 +56,18 @@ __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__
   const uint32_t* L = in + rec_index(w, nodes_in, 2 * n, slots_in, 0) * XYTZ_WORDS;
   const uint32_t* R = L + (size_t)slots_in * XYTZ_WORDS;
   uint32_t* O = out + rec_index(w, nodes_out, n, slots_out, 0) * XYTZ_WORDS;
-  const fe p2 = fe_const(kP2);
+  // U = k T uses k in the 29-bit form's scale, so U stays consistent with
+  // the point's scale
   if (a == 0) {
-    xytz c = ld_xytz(R + (size_t)h * XYTZ_WORDS);
-    if (to_u) c.T = fe_mul(c.T, fe_const(kK));
-    st_xytz(O + (size_t)h * XYTZ_WORDS, c);
+    xytz29 c = pt29_from(ld_xytz(R + (size_t)h * XYTZ_WORDS));
+    if (to_u) c.T = f29_mul(c.T, f29_const(kK29));
+    st_xytz(O + (size_t)h * XYTZ_WORDS, uns ? pt29_to_unsigned(c) : pt29_to_words(c));
   }
   const uint32_t s = a < h ? a : h + 1;  // output slot
-  // the addition on the carry-free 28-bit form (curve28.hpp); U = k T there
-  // uses k in that form, so U stays consistent with the point's scale
-  xytz28 r = padd28_full(pt28_from(ld_xytz(L + (size_t)a * XYTZ_WORDS)),
-                         pt28_from(ld_xytz(R + (size_t)a * XYTZ_WORDS)));
-  if (to_u) r.T = f28_mul(r.T, f28_const(kK28));
-  st_xytz(O + (size_t)s * XYTZ_WORDS, pt28_to_words(r));
+  xytz29 r = padd29_full(pt29_from(ld_xytz(L + (size_t)a * XYTZ_WORDS)),
+                         pt29_from(ld_xytz(R + (size_t)a * XYTZ_WORDS)));
+  if (to_u) r.T = f29_mul(r.T, f29_const(kK29));
+  st_xytz(O + (size_t)s * XYTZ_WORDS, uns ? pt29_to_unsigned(r) : pt29_to_words(r));
 }
 
 // Same level, four lanes per output record.
@@ -81,12 +85,13 @@ __global__ void __launch_bounds__(256) k_tree_level_quad(const uint32_t* __restr
   const uint32_t* L = in + rec_index(w, nodes_in, 2 * n, slots_in, 0) * XYTZ_WORDS;
   const uint32_t* R = L + (size_t)slots_in * XYTZ_WORDS;
   const fe p2 = fe_const(kP2);
-  fe r;
-  if (s == h) {
-    r = quad_ld(R + (size_t)h * XYTZ_WORDS);
-  } else {
-    const uint32_t src = (s < h) ? s : h;
-    r = quad_add(quad_ld(L + (size_t)src * XYTZ_WORDS), quad_ld(R + (size_t)src * XYTZ_WORDS), p2);
+  const uint32_t src = (s < h) ? s : h;
+  fe r = quad_ld(R + (size_t)src * XYTZ_WORDS);
+  if (h == 0) r = fe_unsigned(r);
+  if (s != h) {
+    fe l = quad_ld(L + (size_t)src * XYTZ_WORDS);
+    if (h == 0) l = fe_unsigned(l);
+    r = quad_add(l, r, p2);
   }
   if (to_u) r = quad_to_u(r);
   quad_st(out + rec_index(w, nodes_out, n, slots_out, s) * XYTZ_WORDS, r);
@@ -121,8 +126,14 @@ __global__ void __launch_bounds__(128) k_tree_level_wide(const uint32_t* __restr
   // L (e < 64, into acc) or R (into opd[0])
   {
     const uint32_t e = threadIdx.x, coord = (e >> 4) & 3u, j = e & 15u;
-    const limb_src v = wu_fetch(e < 64 ? L : R, coord, j);
-    (e < 64 ? s.acc : s.opd[0])[16 * coord + j] = limb_extract(v, j);
+    const uint32_t* rec = e < 64 ? L : R;
+    const limb_src v = wu_fetch(rec, coord, j);
+    uint32_t limb = limb_extract(v, j);
+    // level 0 reads signed coordinates: 2p added to a negative one, whose
+    // top limb then loses the 2^384 of its two's complement
+    if (h == 0 && (int32_t)rec[coord * NL + NL - 1] < 0)
+      limb += 2u * kP24[j] - (j == 15 ? 1u << 24 : 0u);
+    (e < 64 ? s.acc : s.opd[0])[16 * coord + j] = limb;
   }
   unit_sync();
   const wslot q = wslot_here();
@@ -326,10 +337,14 @@ int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStrea
     const uint64_t outs = (uint64_t)S * (nodes >> 1) * (h + 2);
     const int to_u = (h + 1 == bb) ? 1 : 0;
     const uint64_t adds = (uint64_t)S * (nodes >> 1) * (h + 1);
+    // outputs of the next level (the last level feeds the wide unit)
+    const uint64_t next = (uint64_t)S * (nodes >> 2) * (h + 3);
+    const int uns = (to_u || next < pl.tree_quad) ? 1 : 0;
     // the schedule's unit thresholds (defaults: below 65536 outputs a level
     // runs on quads, up to 1024 outputs on wide units, one per output)
     if (outs >= pl.tree_quad)
-      k_tree_level<<<(unsigned)((adds + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S, out, to_u);
+      k_tree_level<<<(unsigned)((adds + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S, out, to_u,
+                                                                   uns);
     else if (outs > pl.tree_wide)
       k_tree_level_quad<<<(unsigned)((4 * outs + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S,
                                                                            out, to_u);

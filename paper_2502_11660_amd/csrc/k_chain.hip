@@ -8,7 +8,7 @@
 //    returning its sum once at the end (the shape of bucket accumulation),
 //    with the mixed addition.
 #include "common.hpp"
-#include "curve28.hpp"
+#include "curve29.hpp"
 #include "quad.hpp"
 #include "wide_unit.hpp"
 
@@ -32,19 +32,19 @@ __global__ void __launch_bounds__(64) k_chain_quad(const uint32_t* __restrict__ 
 }
 
 // One lane: the same chain with the whole addition in one lane (the
-// throughput unit's carry-free 28-bit form).
+// throughput unit's signed 29-bit form).
 __global__ void __launch_bounds__(64) k_chain_lane(const uint32_t* __restrict__ pts,
                                                    uint32_t count, uint32_t* __restrict__ out) {
   if (threadIdx.x != 0) return;
-  xytz28 acc = pt28_identity();
+  xytz29 acc = pt29_identity();
   xytz nxt = ld_xytz(pts);
   for (uint32_t i = 0; i < count; ++i) {
-    const xytz28 cur = pt28_from(nxt);
+    const xytz29 cur = pt29_from(nxt);
     const uint32_t j = (i + 1 < count) ? i + 1 : i;
     nxt = ld_xytz(pts + (size_t)j * XYTZ_WORDS);
-    acc = padd28_full(acc, cur);
+    acc = padd29_full(acc, cur);
   }
-  st_xytz(out, pt28_to_words(acc));
+  st_xytz(out, pt29_to_unsigned(acc));
 }
 
 // The wide unit: waves 0 and 1 run the additions (two phases of four
@@ -107,19 +107,19 @@ __global__ void __launch_bounds__(192) k_chain_wide(const uint32_t* __restrict__
 }
 
 // Accumulator a (one lane) sums the prepared points a, a + A, a + 2A, ...
-// (consecutive lanes read consecutive records), on the carry-free 28-bit
+// (consecutive lanes read consecutive records), on the signed 29-bit
 // form like bucket accumulation.
 __global__ void __launch_bounds__(256) k_acc_stream(const uint32_t* __restrict__ xyu_pts,
                                                     uint32_t n, uint32_t A,
                                                     uint32_t* __restrict__ out) {
   const uint32_t a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= A) return;
-  xytz28 acc = pt28_identity();
+  xytz29 acc = pt29_identity();
   // no prefetch of the next record: it would cost a wave per SIMD, and three
   // resident waves cover the load latency
   for (uint32_t i = a; i < n; i += A)
-    acc = padd28_mixed(acc, pt28_from(ld_xyu(xyu_pts + (size_t)i * XYU_WORDS)));
-  st_xytz(out + (size_t)a * XYTZ_WORDS, pt28_to_words(acc));
+    acc = padd29_mixed(acc, pt29_from(ld_xyu(xyu_pts + (size_t)i * XYU_WORDS)));
+  st_xytz(out + (size_t)a * XYTZ_WORDS, pt29_to_unsigned(acc));
 }
 
 // Few accumulators: one wide unit per accumulator (block a) instead of one

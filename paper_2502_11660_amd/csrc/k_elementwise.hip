@@ -5,7 +5,7 @@
 
 #include "common.hpp"
 #include "convert.hpp"
-#include "curve28.hpp"
+#include "curve29.hpp"
 
 namespace msm {
 namespace {
@@ -52,17 +52,9 @@ __device__ __forceinline__ void st_rows(uint32_t* __restrict__ base, uint32_t co
   }
 }
 
-// canonical form of a product output (< 2p): one conditional subtraction
-__device__ __forceinline__ fe canon_of_product(const fe28& x) {
-  const fe w = f28_to_words(x);
-  uint64_t br;
-  const fe t = fe_sub_mask(w, fe_const(kP), br);
-  return fe_pick(br, w, t);
-}
-
 // out_i = a_i + b_i, SoA limb-major operands; FORM selects the mixed
 // (b prepared: X, Y, U, Z = 1) or the complete (b extended) addition.  On the
-// carry-free 28-bit field form (curve28.hpp); outputs canonical.
+// signed 29-bit field form (curve29.hpp); outputs canonical.
 template <int FORM>
 __global__ void __launch_bounds__(256) k_padd(const uint32_t* __restrict__ a,
                                               const uint32_t* __restrict__ b,
@@ -70,30 +62,30 @@ __global__ void __launch_bounds__(256) k_padd(const uint32_t* __restrict__ a,
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   const uint32_t vo = 4u * i;
-  xytz28 pa;
-  pa.X = f28_from_words(ld_rows(a, count, 0, vo));
-  pa.Y = f28_from_words(ld_rows(a, count, 1, vo));
-  pa.T = f28_from_words(ld_rows(a, count, 2, vo));
-  pa.Z = f28_from_words(ld_rows(a, count, 3, vo));
-  xytz28 r;
+  xytz29 pa;
+  pa.X = f29_from_words(ld_rows(a, count, 0, vo));
+  pa.Y = f29_from_words(ld_rows(a, count, 1, vo));
+  pa.T = f29_from_words(ld_rows(a, count, 2, vo));
+  pa.Z = f29_from_words(ld_rows(a, count, 3, vo));
+  xytz29 r;
   if (FORM == MSM_FORM_XYU) {
-    xyu28 pb;
-    pb.X = f28_from_words(ld_rows(b, count, 0, vo));
-    pb.Y = f28_from_words(ld_rows(b, count, 1, vo));
-    pb.U = f28_from_words(ld_rows(b, count, 2, vo));
-    r = padd28_mixed(pa, pb);
+    xyu29 pb;
+    pb.X = f29_from_words(ld_rows(b, count, 0, vo));
+    pb.Y = f29_from_words(ld_rows(b, count, 1, vo));
+    pb.U = f29_from_words(ld_rows(b, count, 2, vo));
+    r = padd29_mixed_scaled(pa, pb);
   } else {
-    xytz28 pb;
-    pb.X = f28_from_words(ld_rows(b, count, 0, vo));
-    pb.Y = f28_from_words(ld_rows(b, count, 1, vo));
-    pb.T = f28_from_words(ld_rows(b, count, 2, vo));
-    pb.Z = f28_from_words(ld_rows(b, count, 3, vo));
-    r = padd28_full(pa, pb);
+    xytz29 pb;
+    pb.X = f29_from_words(ld_rows(b, count, 0, vo));
+    pb.Y = f29_from_words(ld_rows(b, count, 1, vo));
+    pb.T = f29_from_words(ld_rows(b, count, 2, vo));
+    pb.Z = f29_from_words(ld_rows(b, count, 3, vo));
+    r = padd29_full_scaled(pa, pb);
   }
-  st_rows(out, count, 0, vo, canon_of_product(r.X));
-  st_rows(out, count, 1, vo, canon_of_product(r.Y));
-  st_rows(out, count, 2, vo, canon_of_product(r.T));
-  st_rows(out, count, 3, vo, canon_of_product(r.Z));
+  st_rows(out, count, 0, vo, fe_unsigned(f29_to_words(r.X)));
+  st_rows(out, count, 1, vo, fe_unsigned(f29_to_words(r.Y)));
+  st_rows(out, count, 2, vo, fe_unsigned(f29_to_words(r.T)));
+  st_rows(out, count, 3, vo, fe_unsigned(f29_to_words(r.Z)));
 }
 
 // Weierstrass affine (ordinary form) -> prepared (X, Y, U = k x y), Z = 1

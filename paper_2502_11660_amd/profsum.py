@@ -37,8 +37,8 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ACCUM_SOURCES = ["paper_2502_11660_amd/csrc/k_accum.hip", "paper_2502_11660_amd/csrc/curve.hpp",
-                 "paper_2502_11660_amd/csrc/field.hpp", "paper_2502_11660_amd/csrc/fe28.hpp",
-                 "paper_2502_11660_amd/csrc/curve28.hpp"]
+                 "paper_2502_11660_amd/csrc/field.hpp", "paper_2502_11660_amd/csrc/fe29.hpp",
+                 "paper_2502_11660_amd/csrc/curve29.hpp"]
 
 
 def short_name(name):

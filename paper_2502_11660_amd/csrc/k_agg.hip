@@ -14,16 +14,17 @@
 // its dependent depth is only c additions.  Large levels run one addition per
 // lane; small ones use the four-lane quad unit (quad.hpp) to cut latency.
 //
-// Each window then forms S_w by Horner's rule on one wide unit, and group
+// Each window then forms S_w by Horner's rule on one latency unit, and group
 // aggregation Q = sum_w 2^(w c) S_w is Horner's rule over the windows of a job
 // (c doublings per window), the dependent chain the paper assigns to its
-// low-latency unit: one wide two-wave unit per job (wide_unit.hpp).  The
+// low-latency unit: one three-wave unit per job (wide26.hpp).  The
 // result is mapped back to Weierstrass affine form.  A "window" below is a segment: one window of one
 // job of the batch.
 #include "common.hpp"
 #include "convert.hpp"
 #include "curve29.hpp"
 #include "quad.hpp"
+#include "wide26.hpp"
 #include "wide_unit.hpp"
 
 namespace msm {
@@ -184,78 +185,83 @@ __global__ void __launch_bounds__(128) k_tree_level_wide(const uint32_t* __restr
            words_of_limbs(O + 16 * lane));
 }
 
-// Per window (block w, one wide unit): S_w = sum_t 2^t X_t (+ S for signed
-// digits) by Horner's rule over the bits t, with X_t (slot t < bb of the
-// tree's root) and S (slot bb) in XYUZ form.  Writes S_w as XYTZ (record 2w)
-// and XYUZ (record 2w + 1).  Each lane fetches its limb of the next slot
-// while the current step runs.
-__global__ void __launch_bounds__(128) k_window_combine(const uint32_t* __restrict__ root,
-                                                        uint32_t bb, int add_total,
-                                                        uint32_t* __restrict__ wsum) {
-  __shared__ wunit_lds<2> s;
+// Per window (block w, one latency unit of wide26.hpp): S_w = sum_t 2^t X_t
+// (+ S for signed digits) by Horner's rule over the bits t, with X_t (slot
+// t < bb of the tree's root) and S (slot bb) in XYUZ form.  Writes S_w as XYTZ
+// (record 2w) and XYUZ (record 2w + 1).  Wave 2 loads each slot a step ahead
+// and lays it out as the next addition's operand.
+__global__ void __launch_bounds__(W26_THREADS) k_window_combine(const uint32_t* __restrict__ root,
+                                                                uint32_t bb, int add_total,
+                                                                uint32_t* __restrict__ wsum) {
+  __shared__ __attribute__((aligned(16))) w26_lds s;
   const uint32_t w = blockIdx.x;
-  wunit_init(s);  // accumulator = identity
-  unit_sync();    // (written by wave 0 for both waves)
-  const wslot q = wslot_here();
+  const w26_lane q = w26_lane_here(s);
   const uint32_t* V = root + (size_t)w * (bb + 1) * XYTZ_WORDS;
-  limb_src nxt = wu_fetch(V + (size_t)(bb - 1) * XYTZ_WORDS, q.k, q.j);
   const int steps = (int)bb + (add_total ? 1 : 0);
-  uint32_t par = 0;
-  for (int i = 0; i < steps; ++i) {
-    // step i adds slot bb - 1 - i (i < bb) or the total (slot bb)
-    const uint32_t* opd = s.opd[i & 1];
-    // each lane writes the coordinate limb its own wave reads
-    if (q.act) s.opd[i & 1][16 * q.k + q.j] = limb_extract(nxt, q.j);
-    const int following = i + 1 < (int)bb ? (int)bb - 2 - i : (int)bb;  // clamped
-    nxt = wu_fetch(V + (size_t)following * XYTZ_WORDS, q.k, q.j);
-    wave_lds_sync();
-    if (i >= 1 && i < (int)bb) wu_dbl(s, q, par);
-    wu_add_u(s, opd, q, par);
+  // step i adds slot bb - 1 - i (i < bb) or the total (slot bb); clamped
+  auto slot = [&](int i) { return V + (size_t)(i < (int)bb ? (int)bb - 1 - i : (int)bb) * XYTZ_WORDS; };
+  w26_fetch f;
+  if (q.wave == 2) f = w26_load(slot(0));
+  w26_init(s);
+  w26_sync();
+  if (q.wave == 2) {
+    w26_put_identity(s);
+    w26_put_operand(s, q, f, 0);
+    f = w26_load(slot(1));
   }
-  __syncthreads();  // the accumulator's coordinates come from both waves
-  if (threadIdx.x < 64) {
-    // record 2w: XYTZ; record 2w + 1: XYUZ with U = k T (one more product,
-    // in the first half of wave 0)
-    wu_store_acc(s, wsum + (size_t)(2 * w) * XYTZ_WORDS);
-    const bool h0 = q.k == 0 && q.act;
-    const uint32_t u = wmul2(h0 ? s.acc[32 + q.j] : 0u, h0 ? limb_of_const(kK, q.j) : 0u, s.mul[0]);
-    if (h0) s.prod[0][32 + q.j] = u;
+  w26_sync();
+  for (int i = 0; i < steps; ++i) {
+    if (i >= 1 && i < (int)bb) w26_dbl(q);
+    w26_add(q, i & 1, [&] {
+      w26_put_operand(s, q, f, (i & 1) ^ 1);
+      f = w26_load(slot(i + 2 < steps ? i + 2 : steps - 1));
+    });
+  }
+  if (q.wave == 0) {
+    w26_store(s, wsum + (size_t)(2 * w) * XYTZ_WORDS, W26_T);
+  } else if (q.wave == 1) {
+    const uint32_t u = w26_mul(q, s.at(W26_T), s.at(W26_K) + (wlane() & 31u));
+    if (wlane() < 16) s.at(W26_E)[q.j] = u;
     wave_lds_sync();
-    const uint32_t lane = wlane();
-    if (lane < 4) {
-      const uint32_t* src = lane == 2 ? s.prod[0] + 32 : s.acc + 16 * lane;
-      st_aos(wsum + (size_t)(2 * w + 1) * XYTZ_WORDS, (int)lane, words_of_limbs(src));
-    }
+    w26_store(s, wsum + (size_t)(2 * w + 1) * XYTZ_WORDS, W26_E);
   }
 }
 
-// Group aggregation of job j (block j, one wide unit): Q = sum_w 2^(w c) S_w
-// by Horner's rule over the job's W windows.  Each lane loads its limb of the
-// next window sum while the doublings of the current window run.
-__global__ void __launch_bounds__(128) k_horner_wide(const uint32_t* __restrict__ wsum,
-                                                     uint32_t W, uint32_t c,
-                                                     uint32_t* __restrict__ qstate) {
-  __shared__ wunit_lds<2> s;
+// Group aggregation of job j (block j, one latency unit): Q = sum_w 2^(w c) S_w
+// by Horner's rule over the job's W windows; wave 2 loads the next window's
+// sum during the doublings.
+__global__ void __launch_bounds__(W26_THREADS) k_horner_wide(const uint32_t* __restrict__ wsum,
+                                                             uint32_t W, uint32_t c,
+                                                             uint32_t* __restrict__ qstate) {
+  __shared__ __attribute__((aligned(16))) w26_lds s;
   const uint32_t job = blockIdx.x;
-  wunit_init(s);
-  const wslot q = wslot_here();
+  const w26_lane q = w26_lane_here(s);
   const uint32_t* ws = wsum + (size_t)2 * job * W * XYTZ_WORDS;
-  const limb_src top = wu_fetch(ws + (size_t)(2 * (W - 1)) * XYTZ_WORDS, q.k, q.j);
-  limb_src nxt = {0u, 0u};
-  if (W >= 2) nxt = wu_fetch(ws + (size_t)(2 * W - 3) * XYTZ_WORDS, q.k, q.j);
-  unit_sync();
-  if (q.act) s.acc[16 * q.k + q.j] = limb_extract(top, q.j);  // S_{W-1}, XYTZ
-  unit_sync();
-  uint32_t par = 0;
-  for (int w = (int)W - 2; w >= 0; --w) {
-    // S_w, XYUZ (read after the doublings); then fetch S_{w-1}
-    if (q.act) s.opd[0][16 * q.k + q.j] = limb_extract(nxt, q.j);
-    if (w >= 1) nxt = wu_fetch(ws + (size_t)(2 * w - 1) * XYTZ_WORDS, q.k, q.j);
-    for (uint32_t t = 0; t < c; ++t) wu_dbl(s, q, par);
-    wu_add_u(s, s.opd[0], q, par);
+  // S_w, XYUZ (w clamped: W = 1 has none to add)
+  auto sum = [&](int w) { return ws + (size_t)(2 * (w < 0 ? 0 : w) + 1) * XYTZ_WORDS; };
+  w26_fetch top, f;
+  if (q.wave == 2) {
+    top = w26_load(ws + (size_t)(2 * (W - 1)) * XYTZ_WORDS);  // S_{W-1}, XYTZ
+    f = w26_load(sum((int)W - 2));
   }
-  __syncthreads();  // the accumulator's coordinates come from both waves
-  if (threadIdx.x < 64) wu_store_acc(s, qstate + (size_t)job * XYTZ_WORDS);
+  w26_init(s);
+  w26_sync();
+  if (q.wave == 2) {
+    w26_put_acc(s, q, top);
+    w26_put_operand(s, q, f, 0);
+    f = w26_load(sum((int)W - 3));
+  }
+  w26_sync();
+  int o = 0;
+  for (int w = (int)W - 2; w >= 0; --w) {
+    for (uint32_t t = 0; t < c; ++t) w26_dbl(q);
+    w26_add(q, o, [&] {
+      w26_put_operand(s, q, f, o ^ 1);
+      f = w26_load(sum(w - 2));
+    });
+    o ^= 1;
+  }
+  if (q.wave == 0) w26_store(s, qstate + (size_t)job * XYTZ_WORDS, W26_T);
 }
 
 // Twisted-Edwards extended (Montgomery form) -> Weierstrass affine, ordinary
@@ -353,7 +359,7 @@ int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStrea
     in = out;
     nodes >>= 1;
   }
-  k_window_combine<<<S, 128, 0, st>>>(in, bb, pl.encoding == MSM_DIGITS_UNSIGNED ? 0 : 1, wsum);
+  k_window_combine<<<S, W26_THREADS, 0, st>>>(in, bb, pl.encoding == MSM_DIGITS_UNSIGNED ? 0 : 1, wsum);
   HIPCHK(hipGetLastError());
   return MSM_OK;
 }
@@ -362,7 +368,7 @@ int launch_horner(const Plan& pl, void* ws, hipStream_t st) {
   ProfScope prof(PT_HORNER, st);
   const JobView jv = job_view(pl, ws);
   uint32_t* qstate = ws_at<uint32_t>(ws, pl.o_qstate);
-  k_horner_wide<<<(unsigned)pl.J, 128, 0, st>>>(ws_at<uint32_t>(ws, pl.o_wsum), (uint32_t)pl.W,
+  k_horner_wide<<<(unsigned)pl.J, W26_THREADS, 0, st>>>(ws_at<uint32_t>(ws, pl.o_wsum), (uint32_t)pl.W,
                                                  (uint32_t)pl.c, qstate);
   k_finalize<<<(unsigned)pl.J, 64, 0, st>>>(qstate, jv, ws_at<uint32_t>(ws, pl.o_flags));
   HIPCHK(hipGetLastError());

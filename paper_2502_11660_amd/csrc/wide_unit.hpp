@@ -1,8 +1,9 @@
 // Latency-oriented point arithmetic on wide elements: two waves per point.
 //
-// Bucket and group aggregation end in chains of dependent additions and
-// doublings (Sec. II-C), served by a separate low-latency PADD mapping
-// (Sec. V-A).  Here one point occupies two waves: every formula below has
+// The unit of the dependent chain of msm_padd_chain, of few accumulators of
+// msm_accumulate_stream and of the smallest levels of the aggregation tree
+// (Sec. V-A's separate low-latency PADD mapping; the Horner chains run on
+// wide26.hpp).  Here one point occupies two waves: every formula below has
 // four independent products per phase, and the four 32-lane halves of the two
 // waves each compute one of them with wmul2 (the half's index k = 2 wave +
 // half picks the product).  Coordinates live in LDS between phases as 16
@@ -13,10 +14,8 @@
 //
 // Lazy bounds (products come back below a b / R + 1.001 p, p / R < 0.0066):
 // with every coordinate below 1.2p (inputs below 2p where noted),
-//   addition   E = B - A + 3p < 4.2p   F = D - C + 3p < 5.4p
-//              G = D + C < 3.6p        H = B + A < 2.4p
-//   doubling   E = 2 T Z < 2.4p            G = B - A + 2p < 3.2p
-//              H = 3p - A - B <= 3p        F = G - 2 Z^2 + 3p < 6.2p
+//   E = B - A + 3p < 4.2p   F = D - C + 3p < 5.4p
+//   G = D + C < 3.6p        H = B + A < 2.4p
 // so every product operand stays below 8p and every product below 1.2p;
 // limbs stay below 2^28.
 #pragma once
@@ -33,7 +32,7 @@ struct wunit_lds {
   uint32_t acc[64];      // X, Y, T, Z of the accumulator
   uint32_t prod[2][64];  // phase-1 products, alternating between operations
   uint32_t opd[2][64];  // second operands X, Y, U = kT, Z (two slots)
-  uint32_t c2p[16], c3p[16];
+  uint32_t c3p[16];
 };
 
 // this lane's place in the unit: product k = 2 wave + half, limb j
@@ -68,7 +67,6 @@ __device__ __forceinline__ void wunit_init(wunit_lds<WAVES>& s) {
   wmul2_init(s.mul[t >> 6]);
   if (t < 16) {
     const uint32_t up = t < 15 ? (1u << 26) : 0u, down = t >= 1 ? 4u : 0u;
-    s.c2p[t] = 2u * kP24[t] + up - down;
     s.c3p[t] = 3u * kP24[t] + up - down;
   }
   if (t < 64) {
@@ -77,7 +75,7 @@ __device__ __forceinline__ void wunit_init(wunit_lds<WAVES>& s) {
   }
 }
 
-// phase 2 shared by addition and doubling: (E F, G H, E H, F G) -> acc
+// phase 2: (E F, G H, E H, F G) -> acc
 template <int WAVES>
 __device__ __forceinline__ void wu_products_out(wunit_lds<WAVES>& s, const wslot& q, uint32_t E,
                                                 uint32_t F, uint32_t G, uint32_t H) {
@@ -89,11 +87,10 @@ __device__ __forceinline__ void wu_products_out(wunit_lds<WAVES>& s, const wslot
   if (!q.act) s.acc[16 * q.k + q.j] = v;  // result limb j sits in lane 16 + j
 }
 
-// Both operations below take two phases and meet the other computing wave
-// once, in a unit_sync between the phases (other waves of the block must
-// meet it too).  The first phase of either operation reads only coordinates
-// its own wave wrote (wave 0: X, Y; wave 1: T, Z; the doubling forms
-// 2XY as 2TZ) and writes the product buffer par, which alternates between
+// The addition takes two phases and meets the other computing wave once, in a
+// unit_sync between the phases (other waves of the block must meet it too).
+// Its first phase reads only coordinates its own wave wrote (wave 0: X, Y;
+// wave 1: T, Z) and writes the product buffer par, which alternates between
 // operations: so no sync is needed after the second phase, while the other
 // wave may still be reading the previous buffer.  A cross-wave read of the
 // accumulator after the last operation needs a block barrier.
@@ -122,29 +119,6 @@ __device__ __forceinline__ void wu_add_u(wunit_lds<WAVES>& s, const uint32_t* op
     const uint32_t A = prod[q.j], B = prod[16 + q.j], C = prod[32 + q.j], D = prod[48 + q.j],
                    c = s.c3p[q.j];
     wu_products_out(s, q, (B + c) - A, (D + c) - C, D + C, B + A);
-  }
-  wave_lds_sync();
-}
-
-// 2 acc by the dedicated doubling (a = -1), with E = 2XY taken as 2TZ:
-// A = X^2, B = Y^2, T Z, 2 Z^2 in the first phase.
-template <int WAVES>
-__device__ __forceinline__ void wu_dbl(wunit_lds<WAVES>& s, const wslot& q, uint32_t& par) {
-  uint32_t* prod = s.prod[par];
-  par ^= 1u;
-  {
-    const uint32_t o = s.acc[16 * q.k + q.j];            // X, Y, T, Z
-    const uint32_t r = q.k == 2 ? s.acc[48 + q.j] : o;   // X, Y, Z, Z
-    const uint32_t v0 = wmul2_hi(q.act ? o : 0u, q.act ? r : 0u, s.mul[threadIdx.x >> 6]);
-    const uint32_t v = q.k == 3 ? v0 << 1 : v0;          // 2 Z^2
-    if (!q.act) prod[16 * q.k + q.j] = v;
-  }
-  unit_sync();
-  {
-    const uint32_t A = prod[q.j], B = prod[16 + q.j], TZ = prod[32 + q.j], Z2 = prod[48 + q.j];
-    const uint32_t c2 = s.c2p[q.j], c3 = s.c3p[q.j], AB = A + B;
-    const uint32_t G = (B + c2) - A;
-    wu_products_out(s, q, TZ + TZ, (G + c3) - Z2, G, c3 - AB);
   }
   wave_lds_sync();
 }

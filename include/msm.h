@@ -271,9 +271,10 @@ int msm_run_noalloc(const uint32_t* xyu, const uint32_t* scalars, size_t n, int 
  * msm_job: device pointers owned by the caller (prepared points, scalars,
  * MSM_RESULT_WORDS result words), n >= 1 points, window width c (0 = the
  * choice of msm_run with c = 0), and the schedule (0 = the default for
- * each): chunk, the digit entries one lane sums in bucket accumulation
- * (default: enough entries that one resident round of lanes covers the
- * class; every value is rounded up to a multiple of 4, at least 4);
+ * each): chunk, the digit entries one lane (or, in small classes, four
+ * lanes) sums in bucket accumulation (default: enough entries that one
+ * resident round of lanes covers the class; every value is rounded up to a
+ * multiple of 4, at least 4);
  * tree_quad, aggregation-tree levels
  * with fewer outputs than this run on the four-lane unit (default 65536);
  * tree_wide, levels with at most this many outputs run on the wide two-wave

@@ -53,11 +53,13 @@ def n_bucket(n):
 
 def default_chunk(total_entries, cus=256):
     """The average length of the library's default accumulation chunks for a
-    class with this many digit entries: one chunk per lane of a resident
-    round (256 CUs x 4 SIMDs x 3 waves x 64), at least 16 entries; the
-    library splits that into lengths K and K + 4 (multiples of 4)."""
-    lanes = cus * 4 * 3 * 64
-    return max(16, -(-int(total_entries) // lanes))
+    class with this many digit entries: one chunk per lane of one, two or
+    three waves per SIMD (below 16 and 48 entries a lane of one wave), at
+    least 4 entries; the library splits that into lengths K and K + 4
+    (multiples of 4)."""
+    e, lanes = int(total_entries), cus * 4 * 64
+    waves = 1 if e < 16 * lanes else 2 if e < 48 * lanes else 3
+    return max(4, -(-e // (waves * lanes)))
 
 
 class Autotuner:

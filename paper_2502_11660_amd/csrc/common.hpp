@@ -125,6 +125,34 @@ struct JobView {
 
 constexpr uint32_t SORT_TILE = 8192;  // digits per pass-1 sort tile
 
+// Accumulation chunks (k_accum.hip).  Their length follows from the number of
+// entries, which only the device knows (zero digits have none): one chunk per
+// unit, where `units` units give every SIMD one wave.
+struct AccumGeom {
+  uint32_t units;  // lanes or quads of one wave per SIMD
+  uint32_t fixed;  // a schedule's chunk length (0: from the entries)
+  uint32_t quad;   // a unit is a quad
+};
+// Quads up to 2^18 digit slots: above, lanes of four entries are as fast.
+constexpr size_t ACCUM_QUAD_MAX = (size_t)1 << 18;
+// Units for E entries.  Lanes: one wave a SIMD up to 16 entries a lane (a second
+// wave shares the SIMD's issue slots and doubles the split buckets), two up to
+// 24, three above (the most its registers allow).  n = 65536, split digits
+// (1.3 M entries): lanes of 16 took 242 us, two waves a SIMD of lanes of 10
+// take 147.
+__host__ __device__ inline uint32_t accum_units(const AccumGeom& g, uint32_t E) {
+  const uint64_t u = g.units;
+  return g.quad || E < 16 * u ? g.units : (E < 48 * u ? 2 * g.units : 3 * g.units);
+}
+
+// key of the entries that the one-kernel sort keeps for zero digits
+constexpr uint32_t KEY_NONE = 0xffffffffu;
+// bucket b's place in the offsets array: each segment has its 2^bb buckets'
+// starts and its own end
+__host__ __device__ inline size_t offset_index(uint32_t b, uint32_t bb) {
+  return (size_t)b + (b >> bb);
+}
+
 struct Plan {
   int c = 0, W = 0;
   int encoding = MSM_DIGITS_SIGNED;
@@ -136,9 +164,10 @@ struct Plan {
   size_t M = 0;       // buckets S 2^bb
   size_t NW = 0;      // digits N W
   size_t tiles = 0;   // pass-1 sort tiles over all segments
-  size_t chunks = 0;  // accumulation chunks
-  uint32_t K = 32;    // entries per accumulation chunk (the first Kx chunks: K + 4)
-  uint32_t Kx = 0;    // accumulation chunks of K + 4 entries, before those of K
+  AccumGeom accum{};      // how entries are cut into accumulation chunks
+  size_t chunks = 0;      // accumulation chunks, at most
+  size_t long_items = 0;  // capacity of the long-span list: items and segments
+  size_t long_segs = 0;
   uint64_t tree_quad = 65536;  // tree levels with fewer outputs run on quads
   uint64_t tree_wide = 1024;   // levels with at most this many outputs on wide units
   uint32_t lo_bits = 0, hi_bits = 0;  // split of the bb bucket bits in the sort

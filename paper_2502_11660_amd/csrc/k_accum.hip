@@ -11,26 +11,30 @@
 //   * otherwise the last piece, if its bucket continues into later chunks,
 //     goes to tail[chunk] (the bucket starts in this chunk).
 // A split bucket starting in chunk c0 and ending in chunk c1 is then
-// tail[c0] + head[c0+1] + ... + head[c1]: one lane sums it when the span
-// c1 - c0 is small; longer spans are first folded by a binary tree over the
-// head partials.
+// tail[c0] + head[c0+1] + ... + head[c1]: one quad sums it when the span
+// c1 - c0 is small; longer spans are cut into segments that many blocks fold.
+//
+// A chunk is summed by one lane, or, when there are too few entries to give
+// every SIMD a wave of lanes a few entries each, by one quad (quad29.hpp).
 #include <hip/hip_ext.h>
 
 #include <algorithm>
 
 #include "common.hpp"
 #include "curve29.hpp"
+#include "quad29.hpp"
 
 namespace msm {
 namespace {
 
-constexpr uint32_t SMALL_SPAN = 8;
+constexpr uint32_t SMALL_SPAN = 8;   // chunks beyond the first that one quad sums
+constexpr uint32_t SEG_HEADS = 128;  // heads of a segment of a longer span
 
-// Chunk ch covers entries [ch K, min((ch+1) K, E)), E = offsets[M].  The
-// entry's index word is the point index in its job with the digit's sign in
+// An entry's index word is the point index in its job with the digit's sign in
 // bit 31; segoff[s] is the word offset of segment s's point array from pts
 // (NULL: one job, points at pts).  Addressing from the kernel argument keeps
-// the point loads global (not flat) memory instructions.
+// the point loads global (not flat) memory instructions.  Entries with key
+// KEY_NONE (digit zero, kept in place by the one-kernel sort) add nothing.
 
 __device__ __forceinline__ const uint32_t* entry_point(const uint32_t* __restrict__ pts,
                                                        const int64_t* __restrict__ segoff,
@@ -39,16 +43,33 @@ __device__ __forceinline__ const uint32_t* entry_point(const uint32_t* __restric
   return pts + off + (int64_t)(e & 0x7fffffffu) * XYU_WORDS;
 }
 
-// Chunk ch of the sorted entries: the first X chunks hold K + 4 entries, the
-// rest K (both multiples of 4).
-__device__ __forceinline__ uint64_t chunk_start(uint32_t ch, uint32_t K, uint32_t X) {
-  return (uint64_t)ch * K + 4ull * (ch < X ? ch : X);
-}
+// The chunks of E entries: the first X hold K + 4 entries, the rest K (both
+// multiples of 4, so that keys and indices are read in aligned groups).  One
+// chunk per unit of `units` x the waves per SIMD that E is worth, so that no
+// second, mostly idle round follows; K + 4 first, so that the units' work
+// differs by at most 4 entries.
+struct Chunks {
+  uint32_t K, X;
+  __device__ __forceinline__ uint64_t start(uint32_t ch) const {
+    return (uint64_t)ch * K + 4ull * (ch < X ? ch : X);
+  }
+  __device__ __forceinline__ uint32_t length(uint32_t ch) const { return K + (ch < X ? 4u : 0u); }
+  // the chunk holding entry e
+  __device__ __forceinline__ uint32_t of(uint32_t e) const {
+    const uint32_t longer = X * (K + 4);  // <= the entries
+    return e < longer ? e / (K + 4) : X + (e - longer) / K;
+  }
+};
 
-// the chunk holding entry e
-__device__ __forceinline__ uint32_t chunk_of(uint32_t e, uint32_t K, uint32_t X) {
-  const uint64_t longer = (uint64_t)X * (K + 4);
-  return e < longer ? (uint32_t)(e / (K + 4)) : X + (uint32_t)((e - longer) / K);
+__device__ __forceinline__ Chunks chunks_of(const AccumGeom& g, uint32_t E) {
+  Chunks c = {g.fixed, 0u};
+  if (g.fixed == 0) {
+    const uint32_t units = accum_units(g, E);
+    c.K = max(4u, (E / units) & ~3u);
+    const uint64_t even = (uint64_t)c.K * units;
+    c.X = E > even ? (uint32_t)((E - even + 3) / 4) : 0u;
+  }
+  return c;
 }
 
 // One lane per chunk, on the signed 29-bit field form (curve29.hpp): points
@@ -64,26 +85,25 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
                                                  const int64_t* __restrict__ segoff, uint32_t bb,
                                                  const uint32_t* __restrict__ key,
                                                  const uint32_t* __restrict__ idx,
-                                                 const uint32_t* __restrict__ offsets, uint32_t M,
-                                                 uint32_t K, uint32_t X,
+                                                 const uint32_t* __restrict__ total, AccumGeom g,
                                                  uint32_t* __restrict__ buckets,
                                                  uint32_t* __restrict__ head,
                                                  uint32_t* __restrict__ tail) {
-  const uint32_t E1 = offsets[M];
+  const uint32_t E1 = *total;
+  const Chunks c = chunks_of(g, E1);
   const uint32_t ch = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t s64 = chunk_start(ch, K, X);
+  const uint64_t s64 = c.start(ch);
   if (s64 >= E1) return;
   const uint32_t s = (uint32_t)s64;
-  const uint64_t e64 = s64 + K + (ch < X ? 4u : 0u);
+  const uint64_t e64 = s64 + c.length(ch);
   const uint32_t e = (uint32_t)(e64 < E1 ? e64 : E1);
 
   uint32_t cur = key[s];
   const bool open_left = (s > 0) && (key[s - 1] == cur);
   bool first_seg = true;
   xytz29 acc = pt29_identity();
-  // Keys and indices are read four at a time with 16-byte loads (chunk
-  // lengths are multiples of 4, so a chunk starts on a 16-byte boundary; the arrays carry
-  // 32 bytes of padding for a last group that ends past E1).  A lane's
+  // Keys and indices are read four at a time with 16-byte loads (the arrays
+  // carry 32 bytes of padding for a last group that ends past E1).  A lane's
   // 128-byte line of keys would otherwise be fetched again for every entry:
   // the point gathers of all resident waves evict it between iterations.
   // The next group is loaded two entries ahead, while the current one's
@@ -115,14 +135,17 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
     if (k != cur) {
       uint32_t* dst = (first_seg && open_left) ? head + (size_t)ch * XYTZ_WORDS
                                                : buckets + (size_t)cur * XYTZ_WORDS;
-      st_xytz(dst, pt29_to_words(acc));
+      if (cur != KEY_NONE) st_xytz(dst, pt29_to_words(acc));
       acc = pt29_identity();
       cur = k;
       first_seg = false;
     }
-    const xyu29 P = pt29_from(ld_xyu(entry_point(pts, segoff, bb, k, ie)));
-    acc = padd29_mixed_signed(acc, P, (ie >> 31) != 0u);
+    if (k != KEY_NONE) {
+      const xyu29 P = pt29_from(ld_xyu(entry_point(pts, segoff, bb, k, ie)));
+      acc = padd29_mixed_signed(acc, P, (ie >> 31) != 0u);
+    }
   }
+  if (cur == KEY_NONE) return;
   const bool open_right = (e < E1) && (key[e] == cur);
   uint32_t* dst;
   if (first_seg && open_left)
@@ -134,116 +157,246 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
   st_xytz(dst, pt29_to_words(acc));
 }
 
+// The same with one quad per chunk, for up to ACCUM_QUAD_MAX digit slots: the
+// time is then that of one wave's dependent additions (~2.1 us each here,
+// ~6.7 us on one lane), whose chunks can be as short as four entries.  Each
+// lane loads its own coordinate of a point, one entry ahead.  n = 33, signed
+// digits: 108 us on lanes of 16 entries -> 13 us; n = 4099, split digits
+// (123 K slots): 112 -> 27 us.  At 2^18 slots both take ~30 us (16 entries a
+// quad, 4 a lane), and above the quads' 1.4 times as many instructions cost.
+__global__ void __launch_bounds__(256) k_accum_quad(const uint32_t* __restrict__ pts,
+                                                      const int64_t* __restrict__ segoff,
+                                                      uint32_t bb,
+                                                      const uint32_t* __restrict__ key,
+                                                      const uint32_t* __restrict__ idx,
+                                                      const uint32_t* __restrict__ total,
+                                                      AccumGeom g, uint32_t* __restrict__ buckets,
+                                                      uint32_t* __restrict__ head,
+                                                      uint32_t* __restrict__ tail) {
+  const uint32_t E1 = *total;
+  const Chunks c = chunks_of(g, E1);
+  const uint32_t ch = (blockIdx.x * blockDim.x + threadIdx.x) >> 2;
+  const uint64_t s64 = c.start(ch);
+  if (s64 >= E1) return;  // whole quads
+  const uint32_t s = (uint32_t)s64;
+  const uint64_t e64 = s64 + c.length(ch);
+  const uint32_t e = (uint32_t)(e64 < E1 ? e64 : E1);
+  // the words of this lane's coordinate of entry (k, ie)
+  auto load = [&](uint32_t k, uint32_t ie) {
+    const uint32_t* rec = k == KEY_NONE ? pts : entry_point(pts, segoff, bb, k, ie);
+    return ld_aos(quad_xyu(rec), 0);
+  };
+  uint4 kq = *reinterpret_cast<const uint4*>(key + s);
+  uint4 iq = *reinterpret_cast<const uint4*>(idx + s);
+  uint32_t k = kq.x, ie = iq.x;
+  uint32_t cur = k;
+  const bool open_left = (s > 0) && (key[s - 1] == cur);
+  bool first_seg = true;
+  fe29 acc = quad_identity();
+  fe w = load(k, ie);
+  for (uint32_t i = 0; s + i < e; ++i) {
+    // entry i + 1 (past the chunk's end: loaded from the padded arrays, not
+    // dereferenced)
+    const uint32_t r = i & 3u;
+    uint32_t kn = r == 0 ? kq.y : (r == 1 ? kq.z : kq.w);
+    uint32_t in = r == 0 ? iq.y : (r == 1 ? iq.z : iq.w);
+    if (r == 3) {
+      kq = *reinterpret_cast<const uint4*>(key + s + i + 1);
+      iq = *reinterpret_cast<const uint4*>(idx + s + i + 1);
+      kn = kq.x;
+      in = iq.x;
+    }
+    if (s + i + 1 >= e) kn = KEY_NONE;
+    const fe wn = load(kn, in);
+    if (k != cur) {
+      uint32_t* dst = (first_seg && open_left) ? head + (size_t)ch * XYTZ_WORDS
+                                               : buckets + (size_t)cur * XYTZ_WORDS;
+      if (cur != KEY_NONE) quad_st(dst, acc);
+      acc = quad_identity();
+      cur = k;
+      first_seg = false;
+    }
+    if (k != KEY_NONE) acc = quad_add_mixed(acc, f29_from_words(w), (ie >> 31) != 0u);
+    k = kn;
+    ie = in;
+    w = wn;
+  }
+  if (cur == KEY_NONE) return;
+  const bool open_right = (e < E1) && (key[e] == cur);
+  uint32_t* dst;
+  if (first_seg && open_left)
+    dst = head + (size_t)ch * XYTZ_WORDS;
+  else if (open_right)
+    dst = tail + (size_t)ch * XYTZ_WORDS;
+  else
+    dst = buckets + (size_t)cur * XYTZ_WORDS;
+  quad_st(dst, acc);
+}
+
 // chunk ch holds a tail partial: returns true, the bucket and its last chunk
 __device__ __forceinline__ bool tail_of(const uint32_t* __restrict__ key,
                                         const uint32_t* __restrict__ offsets, uint32_t E1,
-                                        uint32_t K, uint32_t X, uint32_t ch, uint32_t& b,
+                                        uint32_t bb, const Chunks& c, uint32_t ch, uint32_t& b,
                                         uint32_t& c1) {
-  const uint64_t s64 = chunk_start(ch, K, X);
+  const uint64_t s64 = c.start(ch);
   if (s64 >= E1) return false;
   const uint32_t s = (uint32_t)s64;
-  const uint64_t e64 = s64 + K + (ch < X ? 4u : 0u);
+  const uint64_t e64 = s64 + c.length(ch);
   const uint32_t e = (uint32_t)(e64 < E1 ? e64 : E1);
   const uint32_t last = key[e - 1];
-  if (!(e < E1 && key[e] == last)) return false;          // last piece ends here
-  if (s > 0 && key[s - 1] == key[s] && key[s] == last)     // whole chunk is a middle piece
+  if (last == KEY_NONE || !(e < E1 && key[e] == last)) return false;  // last piece ends here
+  if (s > 0 && key[s - 1] == key[s] && key[s] == last)  // whole chunk is a middle piece
     return false;
   b = last;
-  c1 = chunk_of(offsets[b + 1] - 1, K, X);
+  c1 = c.of(offsets[offset_index(b, bb) + 1] - 1);
   return true;
 }
 
-// Split buckets: one lane sums tail + heads when the span is at most
-// SMALL_SPAN chunks; longer spans (skewed inputs) are appended to a work list
-// for k_merge_long.  The block's tasks are packed in LDS first (span 1 at
-// the front, longer spans at the back), so that a wave runs one kind and
-// wholly idle waves leave at once.
-__global__ void __launch_bounds__(256) k_merge_small(const uint32_t* __restrict__ key,
-                                                     const uint32_t* __restrict__ offsets,
-                                                     uint32_t M, uint32_t K, uint32_t X,
-                                                     const uint32_t* __restrict__ head,
-                                                     const uint32_t* __restrict__ tail,
-                                                     uint32_t* __restrict__ buckets,
-                                                     uint32_t* __restrict__ longlist) {
-  __shared__ uint32_t task[256];
-  __shared__ uint32_t cnt[2];
+// The work list of the long spans, in words: [0] items, [1] segments, then
+// each item's chunk, each item's count of finished segments, and (item,
+// segment) pairs.  A long span has more than SMALL_SPAN heads of its own.
+struct LongList {
+  uint32_t* w;
+  uint32_t items;  // capacity
+  __device__ __forceinline__ uint32_t* item(uint32_t i) const { return w + 2 + i; }
+  __device__ __forceinline__ uint32_t* done(uint32_t i) const { return w + 2 + items + i; }
+  __device__ __forceinline__ uint32_t* segment(uint32_t i) const { return w + 2 + 2 * items + 2 * i; }
+};
+
+// Split buckets: one quad sums tail + heads when the span is at most
+// SMALL_SPAN chunks; longer spans (skewed inputs) are listed for k_merge_long.
+// A block looks at 256 chunks and orders its sums by span, longest first, so
+// that the quads of a wave run sums of one length and none idles for a chunk
+// without a tail.  Bound by VALU issue when every chunk boundary splits a
+// bucket, by the latency of the span's additions, ~3 us each, when there
+// are few.  Against one lane a chunk: n = 2^20 (196 K chunks, span 1)
+// 73 -> 58 us, n = 65536 (split digits, spans of 3-4) 92 -> 51 us.
+__global__ void __launch_bounds__(256) k_merge(const uint32_t* __restrict__ key,
+                                               const uint32_t* __restrict__ offsets,
+                                               const uint32_t* __restrict__ total, uint32_t bb,
+                                               AccumGeom g, const uint32_t* __restrict__ head,
+                                               const uint32_t* __restrict__ tail,
+                                               uint32_t* __restrict__ buckets, LongList list) {
+  __shared__ uint32_t cnt[SMALL_SPAN + 1];  // sums of each span, then their places
+  __shared__ uint2 task[256];               // tail's chunk in the block | span << 24, bucket
   const uint32_t tid = threadIdx.x;
-  if (tid < 2) cnt[tid] = 0;
+  if (tid <= SMALL_SPAN) cnt[tid] = 0;
   __syncthreads();
-  const uint32_t E1 = offsets[M];
-  const uint32_t ch = blockIdx.x * blockDim.x + tid;
+  const uint32_t E1 = *total;
+  const Chunks c = chunks_of(g, E1);
+  const uint32_t ch0 = blockIdx.x * blockDim.x;
   uint32_t b = 0, c1 = 0;
-  const bool has = tail_of(key, offsets, E1, K, X, ch, b, c1);
-  const uint32_t span = has ? c1 - ch : 0u;
-  if (has && span > SMALL_SPAN) {
-    const uint32_t slot = atomicAdd(&longlist[0], 1u);
-    longlist[1 + slot] = ch;
-  } else if (has && span == 1) {
-    task[atomicAdd(&cnt[0], 1u)] = ch;
-  } else if (has) {
-    task[255 - atomicAdd(&cnt[1], 1u)] = ch;
+  uint32_t span = tail_of(key, offsets, E1, bb, c, ch0 + tid, b, c1) ? c1 - (ch0 + tid) : 0u;
+  if (span > SMALL_SPAN) {
+    const uint32_t item = atomicAdd(&list.w[0], 1u), segs = (span + SEG_HEADS - 1) / SEG_HEADS;
+    *list.item(item) = ch0 + tid;
+    *list.done(item) = 0u;
+    const uint32_t at = atomicAdd(&list.w[1], segs);
+    for (uint32_t t = 0; t < segs; ++t) {
+      list.segment(at + t)[0] = item;
+      list.segment(at + t)[1] = t;
+    }
+    span = 0;
   }
+  const uint32_t rank = span ? atomicAdd(&cnt[span], 1u) : 0u;
   __syncthreads();
-  const uint32_t n1 = cnt[0], n2 = cnt[1];
-  if (!(tid < n1 || tid >= 256 - n2)) return;
-  const uint32_t c = task[tid];
-  // the tail's bucket ends after chunk c
-  const uint32_t bk = key[(uint32_t)chunk_start(c + 1, K, X) - 1];
-  const uint32_t sp = chunk_of(offsets[bk + 1] - 1, K, X) - c;
-  xytz29 acc = pt29_from(ld_xytz(tail + (size_t)c * XYTZ_WORDS));
-  for (uint32_t j = 1; j <= sp; ++j)
-    acc = padd29_full(acc, pt29_from(ld_xytz(head + (size_t)(c + j) * XYTZ_WORDS)));
-  st_xytz(buckets + (size_t)bk * XYTZ_WORDS, pt29_to_words(acc));
+  uint32_t tasks = 0, at = 0;
+  for (uint32_t t = SMALL_SPAN; t >= 1; --t) {
+    if (t == span) at = tasks;
+    tasks += cnt[t];
+  }
+  if (span) task[at + rank] = make_uint2(tid | (span << 24), b);
+  __syncthreads();
+  for (uint32_t i = tid >> 2; i < tasks; i += 64) {
+    const uint2 t = task[i];
+    const uint32_t ch = ch0 + (t.x & 0xffffffu), n = t.x >> 24;
+    fe29 acc = quad_ld(tail + (size_t)ch * XYTZ_WORDS);
+    fe w = ld_aos(head + (size_t)(ch + 1) * XYTZ_WORDS, (int)quad_lane());
+    for (uint32_t j = 1; j <= n; ++j) {
+      const fe29 h = f29_from_words(w);
+      w = ld_aos(head + (size_t)(ch + (j < n ? j + 1 : j)) * XYTZ_WORDS, (int)quad_lane());
+      acc = quad_add(acc, h);
+    }
+    quad_st(buckets + (size_t)t.y * XYTZ_WORDS, acc);
+  }
 }
 
-// Long split buckets, one block each: the block's threads sum strided heads
-// of the span, then fold their partial sums pairwise through LDS (as many
-// levels as the span needs), and thread 0 adds the tail.  The grid holds a
-// block for every possible list entry (a long span covers more than
-// SMALL_SPAN chunks of its own, so there are at most chunks / SMALL_SPAN, and
-// up to 2048 blocks), so the entries run side by side; blocks past the list's
-// count leave at once.
-constexpr int LONG_THREADS = 128;
-__global__ void __launch_bounds__(LONG_THREADS) k_merge_long(const uint32_t* __restrict__ key,
-                                                             const uint32_t* __restrict__ offsets,
-                                                             uint32_t K, uint32_t X,
-                                                             const uint32_t* __restrict__ head,
-                                                             const uint32_t* __restrict__ tail,
-                                                             uint32_t* __restrict__ buckets,
-                                                             const uint32_t* __restrict__ longlist) {
-  __shared__ uint32_t part[LONG_THREADS][XYTZ_WORDS];
-  const uint32_t count = longlist[0];
-  for (uint32_t item = blockIdx.x; item < count; item += gridDim.x) {
-    const uint32_t ch = longlist[1 + item];
-    // the tail's bucket ends after this chunk
-    const uint32_t e_last = (uint32_t)chunk_start(ch + 1, K, X) - 1;
-    const uint32_t b = key[e_last];
-    const uint32_t c1 = chunk_of(offsets[b + 1] - 1, K, X);
-    const uint32_t span = c1 - ch;
-    const uint32_t nact = span < (uint32_t)LONG_THREADS ? span : (uint32_t)LONG_THREADS;
-    if (threadIdx.x < nact) {
-      xytz29 acc = pt29_identity();
-      for (uint32_t j = ch + 1 + threadIdx.x; j <= c1; j += LONG_THREADS)
-        acc = padd29_full(acc, pt29_from(ld_xytz(head + (size_t)j * XYTZ_WORDS)));
-      st_xytz(part[threadIdx.x], pt29_to_words(acc));
+// Sum of count records at stride `stride` (in records) by the block's quads:
+// each sums every 64th, then they fold pairwise through LDS.  The result is
+// in quad 0.
+constexpr uint32_t LONG_QUADS = 64;
+__device__ __forceinline__ fe29 block_sum(const uint32_t* __restrict__ rec, uint32_t count,
+                                          uint32_t stride, int32_t (*part)[4][NL29]) {
+  const uint32_t quad = threadIdx.x >> 2, q = quad_lane();
+  const uint32_t n = count < LONG_QUADS ? count : LONG_QUADS;
+  fe29 acc = quad_identity();
+  if (quad < n) {
+    acc = quad_ld(rec + (size_t)quad * stride * XYTZ_WORDS);
+    for (uint32_t j = quad + LONG_QUADS; j < count; j += LONG_QUADS)
+      acc = quad_add(acc, quad_ld(rec + (size_t)j * stride * XYTZ_WORDS));
+  }
+  // fold [0, m) into [0, ceil(m / 2))
+  for (uint32_t m = n; m > 1; m = (m + 1) >> 1) {
+    const uint32_t half = (m + 1) >> 1;
+    if (quad >= half && quad < m)
+#pragma unroll
+      for (int i = 0; i < NL29; ++i) part[quad][q][i] = acc.v[i];
+    __syncthreads();
+    if (quad + half < m) {
+      fe29 o;
+#pragma unroll
+      for (int i = 0; i < NL29; ++i) o.v[i] = part[quad + half][q][i];
+      acc = quad_add(acc, o);
     }
     __syncthreads();
-    // fold partials [0, n) into [0, ceil(n / 2)) until one is left
-    for (uint32_t n = nact; n > 1;) {
-      const uint32_t half = (n + 1) >> 1;
-      if (threadIdx.x + half < n) {
-        const xytz29 a = pt29_from(ld_xytz(part[threadIdx.x]));
-        const xytz29 o = pt29_from(ld_xytz(part[threadIdx.x + half]));
-        st_xytz(part[threadIdx.x], pt29_to_words(padd29_full(a, o)));
+  }
+  return acc;
+}
+
+// Long split buckets: one block per segment of SEG_HEADS heads (two
+// additions and a fold of six, whatever the span; one block of lanes a span
+// took 267 us for n = 300 K with half the scalars 0 or 1, this 56).  The block that finishes
+// an item's last segment sums the segments' results, left in the place of
+// their first heads, and adds the tail.
+__global__ void __launch_bounds__(256) k_merge_long(const uint32_t* __restrict__ key,
+                                                    const uint32_t* __restrict__ offsets,
+                                                    const uint32_t* __restrict__ total,
+                                                    uint32_t bb, AccumGeom g,
+                                                    uint32_t* __restrict__ head,
+                                                    const uint32_t* __restrict__ tail,
+                                                    uint32_t* __restrict__ buckets,
+                                                    LongList list) {
+  __shared__ int32_t part[LONG_QUADS][4][NL29];
+  __shared__ uint32_t last;
+  const uint32_t count = list.w[1];
+  if (blockIdx.x >= count) return;
+  const Chunks c = chunks_of(g, *total);
+  for (uint32_t i = blockIdx.x; i < count; i += gridDim.x) {
+    const uint32_t item = list.segment(i)[0], t = list.segment(i)[1];
+    const uint32_t ch = *list.item(item);
+    const uint32_t b = key[(uint32_t)c.start(ch + 1) - 1];  // the tail's bucket ends after chunk ch
+    const uint32_t span = c.of(offsets[offset_index(b, bb) + 1] - 1) - ch;
+    const uint32_t segs = (span + SEG_HEADS - 1) / SEG_HEADS;
+    const uint32_t h0 = t * SEG_HEADS, h1 = min(h0 + SEG_HEADS, span);
+    uint32_t* first = head + (size_t)(ch + 1) * XYTZ_WORDS;
+    fe29 sum = block_sum(first + (size_t)h0 * XYTZ_WORDS, h1 - h0, 1, part);
+    if (segs > 1) {
+      if (threadIdx.x < 4) {
+        quad_st(first + (size_t)h0 * XYTZ_WORDS, sum);
+        __threadfence();
       }
       __syncthreads();
-      n = half;
+      if (threadIdx.x == 0) last = atomicAdd(list.done(item), 1u) + 1 == segs ? 1u : 0u;
+      __syncthreads();
+      const bool mine = last != 0u;
+      __syncthreads();  // read before the next segment's write
+      if (!mine) continue;
+      __threadfence();
+      sum = block_sum(first, segs, SEG_HEADS, part);
     }
-    if (threadIdx.x == 0) {
-      const xytz29 t = pt29_from(ld_xytz(tail + (size_t)ch * XYTZ_WORDS));
-      st_xytz(buckets + (size_t)b * XYTZ_WORDS,
-              pt29_to_words(padd29_full(t, pt29_from(ld_xytz(part[0])))));
-    }
+    if (threadIdx.x < 4)
+      quad_st(buckets + (size_t)b * XYTZ_WORDS,
+              quad_add(quad_ld(tail + (size_t)ch * XYTZ_WORDS), sum));
     __syncthreads();
   }
 }
@@ -267,34 +420,32 @@ int launch_records_unsigned(uint32_t* recs, size_t n, hipStream_t st) {
 
 int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st) {
   const uint32_t* offsets = ws_at<uint32_t>(ws, pl.o_offsets);
+  const uint32_t* total = ws_at<uint32_t>(ws, pl.o_total);
   const uint32_t* key = ws_at<uint32_t>(ws, pl.o_key);
   const uint32_t* idx = ws_at<uint32_t>(ws, pl.o_idx);
   uint32_t* head = ws_at<uint32_t>(ws, pl.o_head);
   uint32_t* tail = ws_at<uint32_t>(ws, pl.o_tail);
-  uint32_t* longlist = ws_at<uint32_t>(ws, pl.o_longlist);
+  // its two counters were cleared by the digit sort
+  const LongList list = {ws_at<uint32_t>(ws, pl.o_longlist), (uint32_t)pl.long_items};
   const int64_t* segoff = pl.J == 1 ? nullptr : ws_at<const int64_t>(ws, pl.o_segoff);
-  const uint32_t K = pl.K, X = pl.Kx, M = (uint32_t)pl.M;
-  const unsigned grid = grid_for(pl.chunks, 256);
-  // longlist[0] was cleared by the digit sort's scatter pass
+  const uint32_t bb = (uint32_t)pl.bb;
+  const AccumGeom g = pl.accum;
+  const unsigned grid = grid_for((g.quad ? 4 : 1) * pl.chunks, 256);
+  const auto kernel = g.quad ? k_accum_quad : k_accum;
   hipEvent_t ea = nullptr, eb = nullptr;
   if (prof_kernel_events(PT_ACCUM, st, &ea, &eb)) {
     // timed by events attached to the dispatch itself
-    hipExtLaunchKernelGGL(k_accum, dim3(grid), dim3(256), 0, st, ea, eb, 0, pl.one.xyu, segoff,
-                          (uint32_t)pl.bb, key, idx, offsets, M, K, X, buckets, head, tail);
+    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, ea, eb, 0, pl.one.xyu, segoff, bb,
+                          key, idx, total, g, buckets, head, tail);
     prof_kernel_record(PT_ACCUM, ea, eb);
   } else {
     ProfScope prof(PT_ACCUM, st);
-    k_accum<<<grid, 256, 0, st>>>(pl.one.xyu, segoff, (uint32_t)pl.bb, key, idx, offsets, M, K,
-                                  X, buckets, head, tail);
+    kernel<<<grid, 256, 0, st>>>(pl.one.xyu, segoff, bb, key, idx, total, g, buckets, head, tail);
   }
   ProfScope prof(PT_MERGE, st);
-  k_merge_small<<<grid, 256, 0, st>>>(key, offsets, M, K, X, head, tail, buckets, longlist);
-  // a block per possible entry (at most chunks / SMALL_SPAN), capped: the
-  // common empty list then costs one short wave per block
-  const unsigned long_grid =
-      (unsigned)std::min<size_t>(2048, std::max<size_t>(1, pl.chunks / SMALL_SPAN));
-  k_merge_long<<<long_grid, LONG_THREADS, 0, st>>>(key, offsets, K, X, head, tail, buckets,
-                                                    longlist);
+  k_merge<<<grid_for(pl.chunks, 256), 256, 0, st>>>(key, offsets, total, bb, g, head, tail, buckets, list);
+  k_merge_long<<<(unsigned)std::min<size_t>(1024, pl.long_segs), 256, 0, st>>>(
+      key, offsets, total, bb, g, head, tail, buckets, list);
   HIPCHK(hipGetLastError());
   return MSM_OK;
 }

@@ -12,7 +12,7 @@
 // Every output of a level is one independent addition, the whole tree costs
 // about 2 * 2^c additions per window (as many as the running-sum method) and
 // its dependent depth is only c additions.  Large levels run one addition per
-// lane; small ones use the four-lane quad unit (quad.hpp) to cut latency.
+// lane; small ones use the four-lane quad unit (quad29.hpp) to cut latency.
 //
 // Each window then forms S_w by Horner's rule on one latency unit, and group
 // aggregation Q = sum_w 2^(w c) S_w is Horner's rule over the windows of a job
@@ -23,7 +23,7 @@
 #include "common.hpp"
 #include "convert.hpp"
 #include "curve29.hpp"
-#include "quad.hpp"
+#include "quad29.hpp"
 #include "wide26.hpp"
 #include "wide_unit.hpp"
 
@@ -36,10 +36,9 @@ __device__ __forceinline__ size_t rec_index(uint32_t w, uint32_t nodes, uint32_t
   return ((size_t)w * nodes + n) * slots + s;
 }
 
-// Bucket sums and the lane levels' records are signed (fe29.hpp); the quad
-// and wide units take coordinates in [0, 2p): a lane level followed by one
-// of them stores that form (`uns`), and their own level 0 converts what it
-// loads.
+// Bucket sums and the lane and quad levels' records are signed (fe29.hpp); the
+// wide unit converts what it loads, and the last level (U = k T in the place
+// of T) stores coordinates in [0, 2p).
 
 // One level h -> h+1, one addition per lane: addition a < h forms slot a,
 // addition h the total (slot h + 1); the lane of addition 0 also copies
@@ -47,7 +46,7 @@ __device__ __forceinline__ size_t rec_index(uint32_t w, uint32_t nodes, uint32_t
 __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__ in, uint32_t h,
                                                     uint32_t nodes_in, uint32_t w_lo,
                                                     uint32_t w_cnt, uint32_t* __restrict__ out,
-                                                    int to_u, int uns) {
+                                                    int to_u) {
   const uint32_t nodes_out = nodes_in >> 1, slots_in = h + 1, slots_out = h + 2;
   const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= (uint64_t)w_cnt * nodes_out * slots_in) return;
@@ -62,13 +61,13 @@ __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__
   if (a == 0) {
     xytz29 c = pt29_from(ld_xytz(R + (size_t)h * XYTZ_WORDS));
     if (to_u) c.T = f29_mul(c.T, f29_const(kK29));
-    st_xytz(O + (size_t)h * XYTZ_WORDS, uns ? pt29_to_unsigned(c) : pt29_to_words(c));
+    st_xytz(O + (size_t)h * XYTZ_WORDS, to_u ? pt29_to_unsigned(c) : pt29_to_words(c));
   }
   const uint32_t s = a < h ? a : h + 1;  // output slot
   xytz29 r = padd29_full(pt29_from(ld_xytz(L + (size_t)a * XYTZ_WORDS)),
                          pt29_from(ld_xytz(R + (size_t)a * XYTZ_WORDS)));
   if (to_u) r.T = f29_mul(r.T, f29_const(kK29));
-  st_xytz(O + (size_t)s * XYTZ_WORDS, uns ? pt29_to_unsigned(r) : pt29_to_words(r));
+  st_xytz(O + (size_t)s * XYTZ_WORDS, to_u ? pt29_to_unsigned(r) : pt29_to_words(r));
 }
 
 // Same level, four lanes per output record.
@@ -85,17 +84,14 @@ __global__ void __launch_bounds__(256) k_tree_level_quad(const uint32_t* __restr
   const uint32_t n = t % nodes_out, w = w_lo + t / nodes_out;
   const uint32_t* L = in + rec_index(w, nodes_in, 2 * n, slots_in, 0) * XYTZ_WORDS;
   const uint32_t* R = L + (size_t)slots_in * XYTZ_WORDS;
-  const fe p2 = fe_const(kP2);
   const uint32_t src = (s < h) ? s : h;
-  fe r = quad_ld(R + (size_t)src * XYTZ_WORDS);
-  if (h == 0) r = fe_unsigned(r);
-  if (s != h) {
-    fe l = quad_ld(L + (size_t)src * XYTZ_WORDS);
-    if (h == 0) l = fe_unsigned(l);
-    r = quad_add(l, r, p2);
-  }
-  if (to_u) r = quad_to_u(r);
-  quad_st(out + rec_index(w, nodes_out, n, slots_out, s) * XYTZ_WORDS, r);
+  fe29 r = quad_ld(R + (size_t)src * XYTZ_WORDS);
+  if (s != h) r = quad_add(quad_ld(L + (size_t)src * XYTZ_WORDS), r);
+  uint32_t* O = out + rec_index(w, nodes_out, n, slots_out, s) * XYTZ_WORDS;
+  if (to_u)
+    quad_st_unsigned(O, quad_to_u(r));
+  else
+    quad_st(O, r);
 }
 
 // Same level, one wide unit (two waves) per output record, for levels with
@@ -130,9 +126,9 @@ __global__ void __launch_bounds__(128) k_tree_level_wide(const uint32_t* __restr
     const uint32_t* rec = e < 64 ? L : R;
     const limb_src v = wu_fetch(rec, coord, j);
     uint32_t limb = limb_extract(v, j);
-    // level 0 reads signed coordinates: 2p added to a negative one, whose
-    // top limb then loses the 2^384 of its two's complement
-    if (h == 0 && (int32_t)rec[coord * NL + NL - 1] < 0)
+    // 2p added to a negative coordinate, whose top limb then loses the
+    // 2^384 of its two's complement
+    if ((int32_t)rec[coord * NL + NL - 1] < 0)
       limb += 2u * kP24[j] - (j == 15 ? 1u << 24 : 0u);
     (e < 64 ? s.acc : s.opd[0])[16 * coord + j] = limb;
   }
@@ -343,14 +339,10 @@ int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStrea
     const uint64_t outs = (uint64_t)S * (nodes >> 1) * (h + 2);
     const int to_u = (h + 1 == bb) ? 1 : 0;
     const uint64_t adds = (uint64_t)S * (nodes >> 1) * (h + 1);
-    // outputs of the next level (the last level feeds the wide unit)
-    const uint64_t next = (uint64_t)S * (nodes >> 2) * (h + 3);
-    const int uns = (to_u || next < pl.tree_quad) ? 1 : 0;
     // the schedule's unit thresholds (defaults: below 65536 outputs a level
     // runs on quads, up to 1024 outputs on wide units, one per output)
     if (outs >= pl.tree_quad)
-      k_tree_level<<<(unsigned)((adds + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S, out, to_u,
-                                                                   uns);
+      k_tree_level<<<(unsigned)((adds + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S, out, to_u);
     else if (outs > pl.tree_wide)
       k_tree_level_quad<<<(unsigned)((4 * outs + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S,
                                                                            out, to_u);

@@ -9,7 +9,7 @@
 //    with the mixed addition.
 #include "common.hpp"
 #include "curve29.hpp"
-#include "quad.hpp"
+#include "quad29.hpp"
 #include "wide_unit.hpp"
 
 namespace msm {
@@ -19,16 +19,15 @@ namespace {
 __global__ void __launch_bounds__(64) k_chain_quad(const uint32_t* __restrict__ pts,
                                                    uint32_t count, uint32_t* __restrict__ out) {
   if (threadIdx.x >= 4) return;
-  const fe p2 = fe_const(kP2);
-  fe acc = quad_identity();
-  fe nxt = quad_ld(pts);
+  fe29 acc = quad_identity();
+  fe nxt = ld_aos(pts, (int)quad_lane());
   for (uint32_t i = 0; i < count; ++i) {
-    const fe cur = nxt;
+    const fe29 cur = f29_from_words(nxt);
     const uint32_t j = (i + 1 < count) ? i + 1 : i;
-    nxt = quad_ld(pts + (size_t)j * XYTZ_WORDS);
-    acc = quad_add(acc, cur, p2);
+    nxt = ld_aos(pts + (size_t)j * XYTZ_WORDS, (int)quad_lane());
+    acc = quad_add(acc, cur);
   }
-  quad_st(out, acc);
+  quad_st_unsigned(out, acc);
 }
 
 // One lane: the same chain with the whole addition in one lane (the

@@ -6,7 +6,8 @@
 // s, bucket m of bb bits) and its index word is the point's index in its job
 // with the digit's sign in bit 31.  Over all M = segments * 2^bb buckets the
 // sort produces
-//   offsets[0..M]  CSR offsets of each bucket's entries (offsets[M] = total),
+//   offsets[]      the start of each bucket's entries, and per segment their end
+//                  (offset_index); the entry count goes to *total
 //   key[], idx[]   the entries in bucket order,
 // and writes the identity into every empty bucket.
 //
@@ -252,11 +253,12 @@ __global__ void __launch_bounds__(SORT_THREADS) k_part_scatter(SortGeom g, uint3
                                                                typename TmpEnt<PK>::T* __restrict__ tmp,
                                                                uint32_t* __restrict__ clear0,
                                                                uint32_t* __restrict__ clear1) {
-  // two list counters of later passes start at zero (the large-partition
-  // list of pass 2 and the long-merge list of the accumulation)
+  // list counters of later passes start at zero (the large-partition list of
+  // pass 2 and the long-merge list of the accumulation)
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *clear0 = 0u;
-    *clear1 = 0u;
+    clear0[0] = 0u;
+    clear1[0] = 0u;
+    clear1[1] = 0u;
   }
   // dynamic LDS, sized by the launch for H = 2^hi_bits partitions: the tile
   // stage, then per partition its global start and its local count / start
@@ -375,7 +377,7 @@ __device__ __forceinline__ void part_sort_rows(const SortGeom& g, uint32_t p, ui
   const uint32_t bucket0 = part_bucket0(g, p);
   if (threadIdx.x < L) {
     const uint32_t lo = threadIdx.x;
-    offsets[bucket0 + lo] = start + cur[lo];
+    offsets[offset_index(bucket0, g.bb) + lo] = start + cur[lo];
     if (hist[lo] == 0 && buckets)
       st_xytz(buckets + (size_t)(bucket0 + lo) * XYTZ_WORDS, pt_identity());
   }
@@ -418,7 +420,9 @@ __global__ void __launch_bounds__(SORT_THREADS) k_part_sort(
   const uint32_t total = *total_p;
   uint32_t start, size;
   part_range(g, scanned, total, ncounts, p, start, size);
-  if (p == 0 && threadIdx.x == 0) offsets[g.S << g.bb] = total;
+  // a segment's last partition ends it
+  if (((p + 1) & ((1u << g.hi_bits) - 1)) == 0 && threadIdx.x == 0)
+    offsets[(size_t)((p >> g.hi_bits) + 1) * ((1u << g.bb) + 1) - 1] = start + size;
   if (size > PART_CAP) {
     if (threadIdx.x == 0) big[1 + atomicAdd(&big[0], 1u)] = p;
     return;
@@ -534,7 +538,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_big_scan(SortGeom g,
     lds_exclusive_scan256(bstart, L);
     const uint32_t bucket0 = part_bucket0(g, p);
     if (lo < L) {
-      offsets[bucket0 + lo] = start + bstart[lo];
+      offsets[offset_index(bucket0, g.bb) + lo] = start + bstart[lo];
       if (run == 0 && buckets)
         st_xytz(buckets + (size_t)(bucket0 + lo) * XYTZ_WORDS, pt_identity());
       for (uint32_t it = 0; it < nit; ++it) cnt[(size_t)(it0 + it) * 256 + lo] += bstart[lo];

@@ -195,28 +195,17 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
     pl.one.n = (uint32_t)(mult * ns[0]);
     pl.one.tps = (uint32_t)((mult * ns[0] + pl.tile_digits - 1) / pl.tile_digits);
   }
-  // accumulation chunks: one per lane k_accum keeps resident in one round
-  // (CUs x 4 SIMDs x 3 waves x 64 lanes; its register use allows 3 waves per
-  // SIMD), so that every lane runs exactly once and no second, mostly idle
-  // round follows; at least 16 entries per chunk.  Chunk lengths are
-  // multiples of 4 (every chunk starts on a 16-byte boundary): Kx chunks of
-  // K + 4 entries, then chunks of K, with K the multiple of 4 below the
-  // average, so that the lanes' work differs by at most 4 entries instead of
-  // all lanes taking the average rounded up to a multiple of 4 and some lanes
-  // none.  A schedule's chunk gives every chunk the same length.
-  const size_t lanes = (size_t)device_cus() * 4 * 3 * 64;
-  if (sched.chunk) {
-    pl.K = ((uint32_t)std::max(4, sched.chunk) + 3u) & ~3u;
-    pl.Kx = 0;
-  } else {
-    const size_t k0 = std::max<size_t>(16, (pl.NW / lanes) & ~(size_t)3);
-    pl.K = (uint32_t)k0;
-    pl.Kx = pl.NW > k0 * lanes ? (uint32_t)((pl.NW - k0 * lanes + 3) / 4) : 0u;
-  }
-  {
-    const size_t longer = (size_t)pl.Kx * (pl.K + 4);
-    pl.chunks = pl.Kx + (pl.NW > longer ? (pl.NW - longer + pl.K - 1) / pl.K : 0);
-  }
+  // accumulation chunks (AccumGeom): at most one per unit, each of at least
+  // four entries, or all of a schedule's length
+  const size_t simds = (size_t)device_cus() * 4;
+  if (sched.chunk) pl.accum.fixed = ((uint32_t)std::max(4, sched.chunk) + 3u) & ~3u;
+  pl.accum.quad = pl.NW <= ACCUM_QUAD_MAX ? 1u : 0u;
+  pl.accum.units = (uint32_t)(simds * (pl.accum.quad ? 16 : 64));
+  pl.chunks = pl.accum.fixed
+                  ? (pl.NW + pl.accum.fixed - 1) / pl.accum.fixed
+                  : std::min<size_t>(accum_units(pl.accum, (uint32_t)pl.NW), (pl.NW + 3) / 4);
+  pl.long_items = pl.chunks / 8 + 1;
+  pl.long_segs = pl.long_items + pl.chunks / 128;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -226,16 +215,14 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
   const size_t rec = XYTZ_WORDS * 4;
   pl.o_flags = take((size_t)J * 4);
   pl.o_total = take(4);
-  pl.o_offsets = take((pl.M + 1) * 4);
+  pl.o_offsets = take((pl.M + pl.S) * 4);
   pl.o_counts = take(pl.ncounts * 4);
   pl.o_blocksums = take(4096 * 4);
   pl.o_digits = take(pl.NW * 4);
   pl.o_tmp = take(pl.NW * 8);
   pl.o_key = take(pl.NW * 4 + 32);  // + 16-byte groups read past the end
   pl.o_idx = take(pl.NW * 4 + 32);
-  pl.o_head = take(pl.chunks * rec);
-  pl.o_tail = take(pl.chunks * rec);
-  pl.o_longlist = take((pl.chunks + 1) * 4);
+  pl.o_longlist = take((2 + 2 * pl.long_items + 2 * pl.long_segs) * 4);
   // large sort partitions: each holds more than SORT_PART_CAP entries, so
   // there are at most NW / SORT_PART_CAP of them, and NW / SORT_BIG_ITEM +
   // that many items
@@ -245,9 +232,12 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
   pl.o_bigcnt = take((pl.NW / SORT_BIG_ITEM + nbig_max + 1) * 256 * 4);
   pl.o_bigitem = take((pl.NW / SORT_BIG_ITEM + nbig_max + 1) * 4);
   // buckets, then the tree levels ping-pong between lvl0 (level 0's M
-  // records) and the bucket array, which level 0 has consumed
+  // records) and the bucket array, which level 0 has consumed; before level 0,
+  // lvl0 holds the accumulation's heads and tails
   pl.o_buckets = take(pl.M * rec);
-  pl.o_lvl0 = take(pl.M * rec);
+  pl.o_lvl0 = take(std::max(pl.M, 2 * pl.chunks) * rec);
+  pl.o_head = pl.o_lvl0;
+  pl.o_tail = pl.o_head + pl.chunks * rec;
   pl.o_lvl1 = pl.o_buckets;
   pl.o_wsum = take(2 * pl.S * rec);
   pl.o_qstate = take((size_t)J * rec);

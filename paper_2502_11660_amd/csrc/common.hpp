@@ -145,6 +145,11 @@ __host__ __device__ inline uint32_t accum_units(const AccumGeom& g, uint32_t E) 
   return g.quad || E < 16 * u ? g.units : (E < 48 * u ? 2 * g.units : 3 * g.units);
 }
 
+// The one-kernel sort takes jobs of at most SMALL_SORT_MAX point records (16 for
+// each of a block's 1024 threads) and buckets that fit its LDS counts.
+constexpr size_t SMALL_SORT_MAX = 16384;
+constexpr int SMALL_SORT_BITS = 13;
+
 // key of the entries that the one-kernel sort keeps for zero digits
 constexpr uint32_t KEY_NONE = 0xffffffffu;
 // bucket b's place in the offsets array: each segment has its 2^bb buckets'
@@ -170,6 +175,7 @@ struct Plan {
   size_t long_segs = 0;
   uint64_t tree_quad = 65536;  // tree levels with fewer outputs run on quads
   uint64_t tree_wide = 1024;   // levels with at most this many outputs on wide units
+  bool small_sort = false;            // the one-kernel sort
   uint32_t lo_bits = 0, hi_bits = 0;  // split of the bb bucket bits in the sort
   uint32_t tpb = 1;                   // pass-1 tiles per block (one histogram per group)
   uint32_t tile_digits = SORT_TILE;   // digits per group, SORT_TILE tpb

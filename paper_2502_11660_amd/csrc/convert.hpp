@@ -446,18 +446,27 @@ struct scalar256 {
   uint32_t w[SCALAR_WORDS];
 };
 
-// Load scalar i; bits >= 253 are reported through *flags and ignored.
-__device__ __forceinline__ scalar256 ld_scalar(const uint32_t* __restrict__ s, uint32_t i,
-                                               uint32_t* __restrict__ flags) {
+// Load scalar i; bits >= 253 set `over` and are ignored.
+__device__ __forceinline__ scalar256 ld_scalar_flag(const uint32_t* __restrict__ s, uint32_t i,
+                                                    uint32_t& over) {
   const uint4* q = reinterpret_cast<const uint4*>(s + (size_t)i * SCALAR_WORDS);
   uint4 a = q[0], b = q[1];
   scalar256 r;
   r.w[0] = a.x; r.w[1] = a.y; r.w[2] = a.z; r.w[3] = a.w;
   r.w[4] = b.x; r.w[5] = b.y; r.w[6] = b.z; r.w[7] = b.w;
   if (r.w[7] >> (SCALAR_BITS - 224)) {
-    if (flags) atomicOr(flags, MSM_FLAG_RANGE);
+    over = 1u;
     r.w[7] &= (1u << (SCALAR_BITS - 224)) - 1u;
   }
+  return r;
+}
+
+// The same, reported through *flags.
+__device__ __forceinline__ scalar256 ld_scalar(const uint32_t* __restrict__ s, uint32_t i,
+                                               uint32_t* __restrict__ flags) {
+  uint32_t over = 0;
+  const scalar256 r = ld_scalar_flag(s, i, over);
+  if (over && flags) atomicOr(flags, MSM_FLAG_RANGE);
   return r;
 }
 

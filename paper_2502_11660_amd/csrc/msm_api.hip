@@ -190,6 +190,7 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
   if (pl.N >= ((size_t)1 << 31) || pl.NW >= ((size_t)1 << 31) || pl.M >= ((size_t)1 << 31))
     return false;
   sort_geometry(pl, ns, J, mult);
+  pl.small_sort = pl.max_n <= SMALL_SORT_MAX && pl.bb <= SMALL_SORT_BITS;
   if (pl.lo_bits > 8 || pl.nb > 4096 || pl.tiles >= ((size_t)1 << 31)) return false;
   if (J == 1) {
     pl.one.n = (uint32_t)(mult * ns[0]);

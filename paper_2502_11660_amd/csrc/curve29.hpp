@@ -115,7 +115,7 @@ __device__ __forceinline__ xytz29 padd29_mixed(const xytz29& a, const xyu29& b) 
 __device__ __forceinline__ xytz29 padd29_full(const xytz29& a, const xytz29& b) {
   const fe29 A = f29_mul(f29_sub(a.Y, a.X), f29_sub(b.Y, b.X));
   const fe29 B = f29_mul(f29_add(a.Y, a.X), f29_add(b.Y, b.X));
-  const fe29 C = f29_mul(a.T, f29_mul(b.T, f29_const(kK29)));
+  const fe29 C = f29_mul(a.T, f29_mul_const(b.T, kK29));
   const fe29 D = f29_mul(a.Z, f29_add(b.Z, b.Z));
   return padd29_tail(A, B, C, D);
 }
@@ -134,7 +134,7 @@ __device__ __forceinline__ xytz29 padd29_mixed_scaled(const xytz29& a, const xyu
 __device__ __forceinline__ xytz29 padd29_full_scaled(const xytz29& a, const xytz29& b) {
   const fe29 A = f29_mul385(f29_sub(a.Y, a.X), f29_sub(b.Y, b.X));
   const fe29 B = f29_mul385(f29_add(a.Y, a.X), f29_add(b.Y, b.X));
-  const fe29 C = f29_mul385(a.T, f29_mul(b.T, f29_const(kK29)));
+  const fe29 C = f29_mul385(a.T, f29_mul_const(b.T, kK29));
   const fe29 D = f29_mul385(a.Z, f29_add(b.Z, b.Z));
   return padd29_tail(A, B, C, D);
 }

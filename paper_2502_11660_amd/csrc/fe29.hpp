@@ -111,8 +111,8 @@ __device__ __forceinline__ fe f29_to_words(const fe29& x) {
 }
 
 // column K of a b - m p without the digits m_j p_0: the products a_i b_{K-i}
-// and m_j (-p)_{K-j} with indices in [0, 13) and j < DIGITS
-template <int K, int DIGITS>
+// and m_j (-p)_{K-j} with indices in [0, 13) and j < DIGITS; b in SGPRs when SB
+template <int K, int DIGITS, bool SB = false>
 __device__ __forceinline__ void f29_column(const fe29& a, const fe29& b, const int32_t* m,
                                            int64_t& acc) {
   constexpr int I0 = K < NL29 ? 0 : K - (NL29 - 1);
@@ -124,7 +124,7 @@ __device__ __forceinline__ void f29_column(const fe29& a, const fe29& b, const i
       x[i - I0] = a.v[i];
       y[i - I0] = b.v[K - i];
     }
-    mad64_run<I1 - I0 + 1, true, false>(acc, x, y);
+    mad64_run<I1 - I0 + 1, true, SB>(acc, x, y);
   }
   constexpr int J1 = K - 1 < DIGITS - 1 ? K - 1 : DIGITS - 1;
   if constexpr (I0 <= J1) {
@@ -139,40 +139,45 @@ __device__ __forceinline__ void f29_column(const fe29& a, const fe29& b, const i
 }
 
 // columns [K, DIGITS): reduction digits
-template <int K, int DIGITS>
+template <int K, int DIGITS, bool SB = false>
 __device__ __forceinline__ void f29_low(const fe29& a, const fe29& b, int32_t* m, int64_t& acc) {
   if constexpr (K < DIGITS) {
-    f29_column<K, DIGITS>(a, b, m, acc);
+    f29_column<K, DIGITS, SB>(a, b, m, acc);
     m[K] = (int32_t)acc & M29;
     acc >>= 29;
-    f29_low<K + 1, DIGITS>(a, b, m, acc);
+    f29_low<K + 1, DIGITS, SB>(a, b, m, acc);
   }
 }
 
 // columns [K, DIGITS + 12): result limbs
-template <int K, int DIGITS>
+template <int K, int DIGITS, bool SB = false>
 __device__ __forceinline__ void f29_high(const fe29& a, const fe29& b, const int32_t* m,
                                          int64_t& acc, fe29& r) {
   if constexpr (K < DIGITS + NL29 - 1) {
-    f29_column<K, DIGITS>(a, b, m, acc);
+    f29_column<K, DIGITS, SB>(a, b, m, acc);
     r.v[K - DIGITS] = (int32_t)acc & M29;
     acc >>= 29;
-    f29_high<K + 1, DIGITS>(a, b, m, acc, r);
+    f29_high<K + 1, DIGITS, SB>(a, b, m, acc, r);
   }
 }
 
 // a b 2^-(29 DIGITS) mod p, product scanning with the reduction interleaved
 // per column.  Operands n or d; result n, in (-(1 + 2^-20) p, 2^-20 p) with
 // fourteen digits, in (-|a b| / 2^377 - p, |a b| / 2^377] with thirteen.
-template <int DIGITS = 14>
+template <int DIGITS = 14, bool SB = false>
 __device__ __forceinline__ fe29 f29_mul(const fe29& a, const fe29& b) {
   int32_t m[DIGITS];
   fe29 r;
   int64_t acc = 0;
-  f29_low<0, DIGITS>(a, b, m, acc);
-  f29_high<DIGITS, DIGITS>(a, b, m, acc, r);
+  f29_low<0, DIGITS, SB>(a, b, m, acc);
+  f29_high<DIGITS, DIGITS, SB>(a, b, m, acc, r);
   r.v[NL29 - 1] = (int32_t)acc;
   return r;
+}
+
+// a times a constant (in SGPRs)
+__device__ __forceinline__ fe29 f29_mul_const(const fe29& a, const int32_t (&c)[NL29]) {
+  return f29_mul<14, true>(a, f29_const(c));
 }
 
 // columns [K, 26) of the 385-bit reduction: limbs straddle two columns
@@ -273,6 +278,29 @@ __device__ __forceinline__ fe29 f29_shl8(const fe29& z) {
   fe29 r;
   int64_t acc = 0;
   f29_shl8_limbs<0>(z, q, acc, r);
+  r.v[NL29 - 1] = (int32_t)acc;
+  return r;
+}
+
+// z 2^-S mod p (S <= 29): 2^(29-S) z with one reduction digit.  z class n with
+// |z| < 2p; result n, in (-(1 + 2^-20) p, 2^-20 p) for S > 20.
+template <int S, int K>
+__device__ __forceinline__ void f29_shift_limbs(const fe29& z, int32_t m, int64_t& acc, fe29& r) {
+  if constexpr (K < NL29) {
+    int32_t x[1] = {z.v[K]}, y[1] = {1 << (29 - S)}, u[1] = {m}, w[1] = {kNP29[K]};
+    mad64_run<1, true, true>(acc, x, y);
+    mad64_run<1, true, true>(acc, u, w);
+    r.v[K - 1] = (int32_t)acc & M29;
+    acc >>= 29;
+    f29_shift_limbs<S, K + 1>(z, m, acc, r);
+  }
+}
+template <int S>
+__device__ __forceinline__ fe29 f29_shift_right(const fe29& z) {
+  const int32_t m = (int32_t)((uint32_t)z.v[0] << (29 - S)) & M29;
+  fe29 r;
+  int64_t acc = z.v[0] >> S;  // (2^(29-S) z_0 - m) / 2^29
+  f29_shift_limbs<S, 1>(z, m, acc, r);
   r.v[NL29 - 1] = (int32_t)acc;
   return r;
 }

@@ -60,13 +60,13 @@ __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__
   // the point's scale
   if (a == 0) {
     xytz29 c = pt29_from(ld_xytz(R + (size_t)h * XYTZ_WORDS));
-    if (to_u) c.T = f29_mul(c.T, f29_const(kK29));
+    if (to_u) c.T = f29_mul_const(c.T, kK29);
     st_xytz(O + (size_t)h * XYTZ_WORDS, to_u ? pt29_to_unsigned(c) : pt29_to_words(c));
   }
   const uint32_t s = a < h ? a : h + 1;  // output slot
   xytz29 r = padd29_full(pt29_from(ld_xytz(L + (size_t)a * XYTZ_WORDS)),
                          pt29_from(ld_xytz(R + (size_t)a * XYTZ_WORDS)));
-  if (to_u) r.T = f29_mul(r.T, f29_const(kK29));
+  if (to_u) r.T = f29_mul_const(r.T, kK29);
   st_xytz(O + (size_t)s * XYTZ_WORDS, to_u ? pt29_to_unsigned(r) : pt29_to_words(r));
 }
 

@@ -91,82 +91,96 @@ __global__ void __launch_bounds__(256) k_padd(const uint32_t* __restrict__ a,
 // Weierstrass affine (ordinary form) -> prepared (X, Y, U = k x y), Z = 1
 // (Sec. II-D: inputs enter as (X, Y, U, Z = 1)):
 //   w = x + 1,  x_e = (beta/alpha) w / y,  y_e = (w - alpha) / (w + alpha)
-// so each point needs the inverse of its denominator y (w + alpha).  The
-// inverses come from one inversion per wave (Montgomery's trick, on two
-// levels).  Each lane walks its points forward multiplying their
-// denominators into a running product (each point's record slot keeps the
-// product before it); the wave then forms prefix and suffix products of the
-// 64 lane products (six shuffle-and-multiply steps each), inverts the wave's
-// total once with all lanes cooperating (fe_inv_lanes), and gives each lane
-// the inverse of its own product as total^-1 x prefix x suffix.  Walking
-// back, the inverse of point j's denominator is (inverse of the product up to
-// j) times (product before j), and multiplying by denominator j steps the
-// inverse back.  With the image phi(P) = (omega x, y) the two denominators
-// y (w + alpha) and y (omega x + 1 + alpha) of a point are multiplied first,
-// so one entry serves both.  A zero denominator (an exceptional point,
-// flagged; it cannot lie in the prime-order subgroup) enters the product as
-// 1 so that it does not spoil the batch; its own record is then
-// unspecified.
-
-// Preparation runs once per point set, off the MSM's path; its products are
-// the out-of-line multiply (fe_mul_cold), which keeps the kernel's register
-// footprint small enough for several waves per SIMD.
+// so each point needs the inverses of y and w + alpha, and its image phi(P) =
+// (omega x, y) that of omega x + 1 + alpha.  They come from one inversion per
+// wave (Montgomery's trick, on three levels).  Each lane walks its points
+// forward multiplying their denominators d = y (w + alpha) (omega x + 1 + alpha)
+// into a running product (each point's record slot keeps the product before
+// it); the wave then forms prefix and suffix products of the 64 lane products
+// (six shuffle-and-multiply steps each), inverts the wave's total once with
+// all lanes cooperating (fe_inv_lanes), and gives each lane the inverse of its
+// own product as total^-1 x prefix x suffix.  Walking back, the inverse of
+// point j's d is (inverse of the product up to j) times (product before j),
+// multiplying by d steps the inverse back, and d's factors split the inverse.
+// A zero denominator (an exceptional point, flagged; it cannot lie in the
+// prime-order subgroup) enters the product as 1 so that it does not spoil the
+// batch; its own record is then unspecified.
+//
+// On the signed 29-bit form (fe29.hpp), whose products reduce by 2^406: an
+// input x as it is stands for x 2^-406 there, every denominator with it, and
+// the constants below bring the outputs into R = 2^384 form, so that nothing is
+// converted on the way in.  Bound by VALU issue: 26 products a point with its
+// image, 16 without (34 and 21 on the out-of-line 12-word multiply before):
+// n = 2^20 with images 764 -> 457 us, without 489 -> 302; few points take the
+// wave inversion's latency, 92 -> 68 and 73 -> 60 us.
+// 1 in the 2^406 form, and 2^812, which takes a value into it
+constexpr int32_t kPrepOne[NL29] = {0x19eaf730, 0x171ffffe, 0xd714cf8, 0x44e31d8, 0x1eb6e262,
+    0xbfad163, 0xd46e9c, 0x10b6ddbf, 0x13b9cbdd,
+    0x75782af, 0x3bd1d8a, 0x1557cab6, 0x15742a14};
+constexpr int32_t kPrepIn[NL29] = {0x1c14cc5c, 0x7b8df46, 0x4c74875, 0xd6832fa,
+    0x5f4afc1, 0x11ea1ee5, 0x9265a5f, 0x9fa84f9, 0x12f6f558,
+    0x18644b2b, 0x1caa9452, 0x11db07d, 0xef492d1};
+// omega 2^406: x -> omega x
+constexpr int32_t kPrepOmega[NL29] = {0x1c8a7893, 0xb7d08f2, 0x6b88506, 0x162aa2ed, 0x1c5fdf80,
+    0x11b95a22, 0x3b86dd7, 0x1191f770, 0x10701220,
+    0x1501c11f, 0x1cee88bb, 0x118d05ec, 0x6f2fa26};
+// 1 + alpha and 1 - alpha
+constexpr int32_t kPrepPlus[NL29] = {0x109adc02, 0x2c1256, 0x71e9f27, 0x17651e1c, 0x64272e6,
+    0x5b2fe0b, 0x1690bf8b, 0x663068c, 0xe86ef0d,
+    0x10ae65fc, 0x16505bb3, 0xc5a693c, 0x32d7560};
+constexpr int32_t kPrepMinus[NL29] = {0xf652401, 0x819eda9, 0x18e160fa, 0x1f556a43,
+    0xe3d8e89, 0xb64def9, 0x17abbc42, 0x17fd1815, 0xc9333cc,
+    0x12b6a44d, 0x1b3e65bc, 0x32fb898, 0x17b62f01};
+// 2^1218: a plain inverse of a value of the 2^406 form -> its inverse there
+constexpr int32_t kPrepInv[NL29] = {0x116ee469, 0x193358dc, 0x5d36c9a, 0x8690878, 0x7b9a713,
+    0x31c169b, 0x1de45103, 0x94b9b1e, 0x140c4b90,
+    0xe3a757c, 0x1315b3f7, 0x393cb0b, 0xfeb6639};
+// (beta / alpha) 2^384 and k 2^428: the outputs' R = 2^384 form
+constexpr int32_t kPrepX[NL29] = {0xad605e4, 0x1be055c7, 0x1d4b1ebe, 0x1727a3c4, 0x1e536363,
+    0x141a8a25, 0x1df4891, 0x1ba853e4, 0x3eb8bf6,
+    0x1011a6a1, 0xea7bf68, 0x1418e548, 0x13c7943b};
+constexpr int32_t kPrepU[NL29] = {0xc36d10f, 0x57c900d, 0x1bd871b8, 0x1d41bd7,
+    0xc494f80, 0xbb719fe, 0x3a2ee3b, 0x15c2767f, 0x1aff76a6,
+    0xea89726, 0x107baa55, 0x1c32e522, 0x8af1458};
 
 // lane-to-lane moves of a field element (lanes without a source keep x)
-__device__ __forceinline__ fe fe_shfl_up(const fe& x, int d) {
-  fe r;
+__device__ __forceinline__ fe29 f29_shfl_up(const fe29& x, int d) {
+  fe29 r;
 #pragma unroll
-  for (int i = 0; i < NL; ++i) r.v[i] = (uint32_t)__shfl_up((int)x.v[i], d, 64);
+  for (int i = 0; i < NL29; ++i) r.v[i] = __shfl_up(x.v[i], d, 64);
   return r;
 }
 
-__device__ __forceinline__ fe fe_shfl_down(const fe& x, int d) {
-  fe r;
+__device__ __forceinline__ fe29 f29_shfl_down(const fe29& x, int d) {
+  fe29 r;
 #pragma unroll
-  for (int i = 0; i < NL; ++i) r.v[i] = (uint32_t)__shfl_down((int)x.v[i], d, 64);
+  for (int i = 0; i < NL29; ++i) r.v[i] = __shfl_down(x.v[i], d, 64);
   return r;
 }
 
-// Every lane's v^-1 (Montgomery form, canonical) for non-zero v < 2p, with
-// one inversion for the wave.  All 64 lanes of the wave must take part.
-__device__ __forceinline__ fe wave_batch_inverse(const fe& v) {
+// canonical words of a product
+__device__ __forceinline__ fe f29_canon(const fe29& x) { return fe_unsigned(f29_to_words(x)); }
+
+// Every lane's v^-1 (2^406 form) for a non-zero product v, with one inversion
+// for the wave.  All 64 lanes of the wave must take part.
+__device__ __forceinline__ fe29 wave_batch_inverse(const fe29& v) {
   const int lane = (int)__lane_id();
-  fe P = v, Q = v;  // inclusive prefix and suffix products over the lanes
-#pragma unroll
+  fe29 A = v, B = v;  // inclusive prefix and suffix products over the lanes
+#pragma unroll 1
   for (int d = 1; d < 64; d <<= 1) {
-    const fe pu = fe_mul_cold(P, fe_shfl_up(P, d));
-    const fe qd = fe_mul_cold(Q, fe_shfl_down(Q, d));
-    P = fe_select(lane >= d, pu, P);
-    Q = fe_select(lane + d < 64, qd, Q);
+    const fe29 au = f29_mul(A, f29_shfl_up(A, d));
+    const fe29 bd = f29_mul(B, f29_shfl_down(B, d));
+    A = f29_select(lane >= d, au, A);
+    B = f29_select(lane + d < 64, bd, B);
   }
-  const fe E = fe_select(lane == 0, fe_const(kOne), fe_shfl_up(P, 1));    // lanes below
-  const fe S = fe_select(lane == 63, fe_const(kOne), fe_shfl_down(Q, 1)); // lanes above
-  fe total;
+  fe29 total;
 #pragma unroll
-  for (int i = 0; i < NL; ++i) total.v[i] = (uint32_t)__builtin_amdgcn_readlane((int)P.v[i], 63);
-  const fe inv_total = fe_mul_cold(fe_inv_lanes(fe_canon(total)), fe_const(kR3));
-  return fe_mul_cold(fe_mul_cold(inv_total, E), S);
-}
-
-// the denominator y (x + 1 + alpha)
-__device__ __forceinline__ fe prep_den(const fe& x, const fe& y) {
-  return fe_mul_cold(y, fe_add(fe_add(x, fe_const(kOne)), fe_const(kAlpha)));
-}
-
-// the record (x_e, y_e, k x_e y_e), canonical, given the inverse of the
-// denominator
-__device__ __forceinline__ void prep_record(const fe& x, const fe& y, const fe& inv,
-                                            uint32_t* rec) {
-  const fe p2 = fe_const(kP2);
-  const fe w = fe_add(x, fe_const(kOne));                 // < 4p
-  const fe wpa = fe_add(w, fe_const(kAlpha));             // < 6p
-  const fe wma = fe_sub_plus(w, fe_const(kAlpha), p2);    // < 6p
-  const fe xe = fe_mul_cold(fe_mul_cold(fe_mul_cold(w, wpa), inv), fe_const(kBetaOverAlpha));
-  const fe ye = fe_mul_cold(fe_mul_cold(wma, y), inv);
-  const fe u = fe_mul_cold(fe_mul_cold(xe, ye), fe_const(kK));
-  st_aos(rec, 0, fe_canon(xe));
-  st_aos(rec, 1, fe_canon(ye));
-  st_aos(rec, 2, fe_canon(u));
+  for (int i = 0; i < NL29; ++i) total.v[i] = __builtin_amdgcn_readlane(A.v[i], 63);
+  const fe29 E = f29_select(lane == 0, f29_const(kPrepOne), f29_shfl_up(A, 1));     // lanes below
+  const fe29 S = f29_select(lane == 63, f29_const(kPrepOne), f29_shfl_down(B, 1));  // lanes above
+  const fe29 es = f29_mul(E, S);
+  const fe inv = fe_inv_lanes(f29_canon(total));
+  return f29_mul(f29_mul_const(f29_from_words(inv), kPrepInv), es);
 }
 
 __device__ __forceinline__ void prepare_identity(uint32_t* rec) {
@@ -175,22 +189,36 @@ __device__ __forceinline__ void prepare_identity(uint32_t* rec) {
   st_aos(rec, 2, fe_zero());
 }
 
-// the point's factor of the batch product (1 for a zero denominator)
-__device__ __forceinline__ fe batch_factor(const fe& den_a, const fe& den_b, bool endo,
-                                           uint32_t& flags) {
-  fe d = endo ? fe_mul_cold(den_a, den_b) : den_a;
-  if (fe_is_zero_canon(fe_canon(d))) {
-    flags |= MSM_FLAG_EXCEPT;
-    d = fe_const(kOne);
+// the image's x, the product of the w + alpha (of the point and its image),
+// and the factor d of the batch (1 for a zero denominator)
+struct prep_den {
+  fe29 xb, P, d;
+};
+template <bool ENDO>
+__device__ __forceinline__ prep_den prep_denominators(const fe29& x, const fe29& y,
+                                                      uint32_t& flags) {
+  prep_den r;
+  const fe29 wa = f29_add(x, f29_const(kPrepPlus));
+  if (ENDO) {
+    r.xb = f29_mul_const(x, kPrepOmega);
+    r.P = f29_mul(wa, f29_add(r.xb, f29_const(kPrepPlus)));
+  } else {
+    r.xb = x;
+    r.P = wa;
   }
-  return d;
+  r.d = f29_mul(r.P, y);
+  if (fe_is_zero_canon(f29_canon(r.d))) {
+    flags |= MSM_FLAG_EXCEPT;
+    r.d = f29_const(kPrepOne);
+  }
+  return r;
 }
 
 // Thread t prepares points i = t + j T, j = 0 .. m-1 (i < n), T = threads;
 // threads t >= T take part in the wave-wide inversion only.
 // ENDO: records 2i and 2i + 1 hold point i and its image (omega x, y).
 template <bool ENDO>
-__global__ void __launch_bounds__(256) k_prepare(const uint32_t* __restrict__ xy,
+__global__ void __launch_bounds__(256, ENDO ? 2 : 4) k_prepare(const uint32_t* __restrict__ xy,
                                                  const uint32_t* __restrict__ inf,
                                                  uint32_t* __restrict__ out, uint32_t n,
                                                  uint32_t T, uint32_t m,
@@ -198,24 +226,29 @@ __global__ void __launch_bounds__(256) k_prepare(const uint32_t* __restrict__ xy
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t mine = t < T ? m : 0u;
   uint32_t flags = 0;
-  fe c = fe_const(kOne);  // product of the factors so far
-  uint32_t last = 0;      // points of this thread
+  fe29 c = f29_const(kPrepOne);  // product of the factors so far
+  uint32_t last = 0;             // points of this thread
+#pragma unroll 1
   for (uint32_t j = 0; j < mine; ++j) {
     const uint64_t i = (uint64_t)t + (uint64_t)j * T;
     if (i >= n) break;
     last = j + 1;
     if (inf && inf[i]) continue;
-    const fe x = fe_mul_cold(ld_soa(xy, n, 0, (size_t)i), fe_const(kR2));
-    const fe y = fe_mul_cold(ld_soa(xy, n, 1, (size_t)i), fe_const(kR2));
-    const fe lhs = fe_canon(fe_mul_cold(y, y));
-    const fe rhs = fe_canon(fe_add(fe_mul_cold(fe_mul_cold(x, x), x), fe_const(kOne)));
+    const fe29 x = f29_from_words(ld_soa(xy, n, 0, (size_t)i));
+    const fe29 y = f29_from_words(ld_soa(xy, n, 1, (size_t)i));
+    // y^2 - 1 = x^3
+    fe29 ym = y, yp = y;
+    ym.v[0] -= 1;
+    yp.v[0] += 1;
+    const fe lhs = f29_canon(f29_mul(ym, yp));
+    const fe rhs = f29_canon(f29_mul(f29_mul(x, x), f29_mul_const(x, kPrepIn)));
     if (!fe_eq_canon(lhs, rhs)) flags |= MSM_FLAG_OFFCURVE;
-    const fe den_a = prep_den(x, y);
-    const fe den_b = ENDO ? prep_den(fe_mul_cold(x, fe_const(kOmega)), y) : den_a;
-    st_aos(out + (size_t)(ENDO ? 2 * i : i) * XYU_WORDS, 0, fe_canon(c));  // product before i
-    c = fe_mul_cold(c, batch_factor(den_a, den_b, ENDO, flags));
+    const prep_den e = prep_denominators<ENDO>(x, y, flags);
+    st_aos(out + (size_t)(ENDO ? 2 * i : i) * XYU_WORDS, 0, f29_to_words(c));  // product before i
+    c = f29_mul(c, e.d);
   }
-  fe tinv = wave_batch_inverse(c);  // inverse of this thread's product
+  fe29 tinv = wave_batch_inverse(c);  // inverse of this thread's product
+#pragma unroll 1
   for (uint32_t jj = last; jj-- > 0;) {
     const uint64_t i = (uint64_t)t + (uint64_t)jj * T;
     uint32_t* rec = out + (size_t)(ENDO ? 2 * i : i) * XYU_WORDS;
@@ -224,20 +257,29 @@ __global__ void __launch_bounds__(256) k_prepare(const uint32_t* __restrict__ xy
       if (ENDO) prepare_identity(rec + XYU_WORDS);
       continue;
     }
-    const fe x = fe_mul_cold(ld_soa(xy, n, 0, (size_t)i), fe_const(kR2));
-    const fe y = fe_mul_cold(ld_soa(xy, n, 1, (size_t)i), fe_const(kR2));
-    const fe den_a = prep_den(x, y);
-    const fe xb = ENDO ? fe_mul_cold(x, fe_const(kOmega)) : x;
-    const fe den_b = ENDO ? prep_den(xb, y) : den_a;
+    const fe29 x = f29_from_words(ld_soa(xy, n, 0, (size_t)i));
+    const fe29 y = f29_from_words(ld_soa(xy, n, 1, (size_t)i));
     uint32_t dummy = 0;
-    const fe d = batch_factor(den_a, den_b, ENDO, dummy);
-    const fe inv_d = fe_mul_cold(tinv, ld_aos(rec, 0));  // 1 / d
-    tinv = fe_mul_cold(tinv, d);                          // 1 / (product before this point)
-    if (ENDO) {
-      prep_record(x, y, fe_mul_cold(inv_d, den_b), rec);
-      prep_record(xb, y, fe_mul_cold(inv_d, den_a), rec + XYU_WORDS);
-    } else {
-      prep_record(x, y, inv_d, rec);
+    const prep_den e = prep_denominators<ENDO>(x, y, dummy);
+    const fe29 inv_d = f29_mul(tinv, f29_from_words(ld_aos(rec, 0)));  // 1 / d
+    tinv = f29_mul(tinv, e.d);  // 1 / (product before this point)
+    const fe29 xs = f29_mul_const(f29_mul(inv_d, e.P), kPrepX);  // (beta / alpha) / y
+    // 1 / P in the outputs' form (2^406 to 2^384)
+    const fe29 inv_p = f29_shift_right<22>(f29_mul(inv_d, y));
+#pragma unroll 1
+    for (uint32_t im = 0; im < (ENDO ? 2u : 1u); ++im) {
+      const fe29 px = ENDO ? f29_select(im != 0, e.xb, x) : x;
+      const fe29 other = f29_add(f29_select(im != 0, x, e.xb), f29_const(kPrepPlus));
+      fe29 w = px;
+      w.v[0] += 1;
+      const fe29 xe = f29_mul(w, xs);
+      const fe29 inv_w = ENDO ? f29_mul(inv_p, other) : inv_p;
+      const fe29 ye = f29_mul(f29_add(px, f29_const(kPrepMinus)), inv_w);
+      const fe29 u = f29_mul(f29_mul_const(xe, kPrepU), ye);
+      st_aos(rec, 0, f29_canon(xe));
+      st_aos(rec, 1, f29_canon(ye));
+      st_aos(rec, 2, f29_canon(u));
+      rec += XYU_WORDS;
     }
   }
   if (flags) atomicOr(status, flags);
@@ -300,9 +342,11 @@ int launch_padd(const uint32_t* a, const uint32_t* b, uint32_t* out, uint32_t co
 
 int launch_prepare(const uint32_t* xy, const uint32_t* inf, uint32_t* xyu, uint32_t n,
                    uint32_t* status, bool endo, hipStream_t st) {
-  // points per thread: enough threads for four waves per SIMD
-  // (256 CUs x 4 SIMDs x 64 lanes x 4), the rest of the points batched
-  const uint32_t m = std::max<uint32_t>(1u, std::min<uint32_t>(64u, n / 262144u));
+  // points per thread: two waves per SIMD, the most the registers of the form
+  // with images allow (256 CUs x 4 SIMDs x 64 lanes x 2), the rest of the
+  // points batched; n = 2^20 with images at three waves and spills 504 us, at one
+  // 514, against 457
+  const uint32_t m = std::max<uint32_t>(1u, std::min<uint32_t>(64u, n / 131072u));
   const uint32_t T = (uint32_t)(((uint64_t)n + m - 1) / m);
   if (endo)
     k_prepare<true><<<grid_for(T, 256), 256, 0, st>>>(xy, inf, xyu, n, T, m, status);

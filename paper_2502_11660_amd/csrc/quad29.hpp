@@ -110,7 +110,7 @@ __device__ __forceinline__ fe29 quad_add_mixed(const fe29& a, const fe29& b, boo
 
 // T -> U = k T in lane 2
 __device__ __forceinline__ fe29 quad_to_u(const fe29& v) {
-  return f29_select(quad_lane() == 2, f29_mul(v, f29_const(kK29)), v);
+  return f29_select(quad_lane() == 2, f29_mul_const(v, kK29), v);
 }
 
 // a + b, both XYTZ

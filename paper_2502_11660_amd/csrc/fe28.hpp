@@ -74,7 +74,7 @@ __device__ __forceinline__ void f28_column(const fe28& a, const fe28& b, const u
     x[i - I0] = a.v[i];
     y[i - I0] = b.v[K - i];
   }
-  mad64_run<I1 - I0 + 1, false, false>(acc, x, y);
+  mad64_block<false, I1 - I0 + 1, 0>(acc, x, y, x, y);
   if constexpr (J1 >= I0) {
     uint32_t u[NL28], q[NL28];
 #pragma unroll
@@ -82,7 +82,7 @@ __device__ __forceinline__ void f28_column(const fe28& a, const fe28& b, const u
       u[j - I0] = m[j];
       q[j - I0] = kP28[K - j];
     }
-    mad64_run<J1 - I0 + 1, false, true>(acc, u, q);
+    mad64_block<false, 0, J1 - I0 + 1>(acc, u, q, u, q);
   }
 }
 

@@ -117,24 +117,24 @@ __device__ __forceinline__ void f29_column(const fe29& a, const fe29& b, const i
                                            int64_t& acc) {
   constexpr int I0 = K < NL29 ? 0 : K - (NL29 - 1);
   constexpr int I1 = K < NL29 ? K : NL29 - 1;
-  if constexpr (I0 <= I1) {
-    int32_t x[NL29], y[NL29];
-#pragma unroll
-    for (int i = I0; i <= I1; ++i) {
-      x[i - I0] = a.v[i];
-      y[i - I0] = b.v[K - i];
-    }
-    mad64_run<I1 - I0 + 1, true, SB>(acc, x, y);
-  }
   constexpr int J1 = K - 1 < DIGITS - 1 ? K - 1 : DIGITS - 1;
-  if constexpr (I0 <= J1) {
-    int32_t u[NL29], q[NL29];
+  constexpr int NA = I1 >= I0 ? I1 - I0 + 1 : 0, NM = J1 >= I0 ? J1 - I0 + 1 : 0;
+  int32_t x[NL29], y[NL29], u[NL29], q[NL29];
 #pragma unroll
-    for (int j = I0; j <= J1; ++j) {
-      u[j - I0] = m[j];
-      q[j - I0] = kNP29[K - j];
-    }
-    mad64_run<J1 - I0 + 1, true, true>(acc, u, q);
+  for (int i = 0; i < NA; ++i) {
+    x[i] = a.v[I0 + i];
+    y[i] = b.v[K - I0 - i];
+  }
+#pragma unroll
+  for (int j = 0; j < NM; ++j) {
+    u[j] = m[I0 + j];
+    q[j] = kNP29[K - I0 - j];
+  }
+  if constexpr (SB) {
+    if constexpr (NA > 0) mad64_block<true, 0, NA>(acc, x, y, x, y);
+    if constexpr (NM > 0) mad64_block<true, 0, NM>(acc, u, q, u, q);
+  } else {
+    mad64_block<true, NA, NM>(acc, x, y, u, q);
   }
 }
 
@@ -263,9 +263,8 @@ __device__ __forceinline__ fe29 f29_add_p(const fe29& a, const fe29& b) {
 template <int K>
 __device__ __forceinline__ void f29_shl8_limbs(const fe29& z, int32_t q, int64_t& acc, fe29& r) {
   if constexpr (K < NL29) {
-    int32_t x[1] = {z.v[K]}, y[1] = {256}, u[1] = {q}, w[1] = {kNP29[K]};
-    mad64_run<1, true, true>(acc, x, y);
-    mad64_run<1, true, true>(acc, u, w);
+    const int32_t x[2] = {z.v[K], q}, y[2] = {256, kNP29[K]};
+    mad64_block<true, 0, 2>(acc, x, y, x, y);
     if constexpr (K + 1 < NL29) {
       r.v[K] = (int32_t)acc & M29;
       acc >>= 29;
@@ -287,9 +286,8 @@ __device__ __forceinline__ fe29 f29_shl8(const fe29& z) {
 template <int S, int K>
 __device__ __forceinline__ void f29_shift_limbs(const fe29& z, int32_t m, int64_t& acc, fe29& r) {
   if constexpr (K < NL29) {
-    int32_t x[1] = {z.v[K]}, y[1] = {1 << (29 - S)}, u[1] = {m}, w[1] = {kNP29[K]};
-    mad64_run<1, true, true>(acc, x, y);
-    mad64_run<1, true, true>(acc, u, w);
+    const int32_t x[2] = {z.v[K], m}, y[2] = {1 << (29 - S), kNP29[K]};
+    mad64_block<true, 0, 2>(acc, x, y, x, y);
     r.v[K - 1] = (int32_t)acc & M29;
     acc >>= 29;
     f29_shift_limbs<S, K + 1>(z, m, acc, r);

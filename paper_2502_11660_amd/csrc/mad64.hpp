@@ -1,14 +1,14 @@
-// Grouped 32x32->64 multiply-adds without carry words (device code): the
+// Column sums of 32x32->64 multiply-adds without carry words (device code): the
 // building block of the one-lane field cores (fe29.hpp, fe28.hpp).
 //
-// N products are added into one 64-bit column accumulator by one asm block
-// (written as asm so that the column's products are added in order onto the
-// incoming carry: as plain C the compiler sums each column from zero and adds
-// the carry afterwards, one extra 64-bit add per column; grouped because the
-// compiler puts a wait state after every asm block).  OP is v_mad_u64_u32 or
-// v_mad_i64_i32, CB the second factor's constraint ("v" for a VGPR, "s" for an
-// SGPR such as a limb of p).  The carry-out goes to a scratch SGPR pair (cc)
-// that nothing reads; it is early-clobber ("=&s") because the block's first
+// All of a column's products are added into one 64-bit accumulator by one asm
+// block (written as asm so that they are added in order onto the incoming
+// carry: as plain C the compiler sums each column from zero and adds the carry
+// afterwards, one extra 64-bit add per column; one block, because the compiler
+// puts a wait state after every one, an instruction slot to a lone wave).  The
+// products of a block are of two VGPRs first, then of a VGPR and an SGPR
+// (such as a limb of p).  The carry-out goes to a scratch SGPR pair that
+// nothing reads; it is early-clobber ("=&s") because the block's first
 // multiply-add writes it before the later ones read their factors, so it must
 // not share a register with an SGPR factor.
 #pragma once
@@ -16,127 +16,104 @@
 #include <stdint.h>
 
 namespace msm {
-#define MSM_MAD64_1(OP, CB, acc, cc, a0, b0) \
-  asm(OP" %0, %1, %2, %3, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0))
 
-#define MSM_MAD64_2(OP, CB, acc, cc, a0, b0, a1, b1) \
-  asm(OP" %0, %1, %2, %3, %0\n\t" \
-      OP" %0, %1, %4, %5, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0), "v"(a1), CB(b1))
+// the first n lines of a block: line i multiplies operands 2 + 2 i and 3 + 2 i
+#define MSM_MADL_1(OP) OP " %0, %1, %2, %3, %0"
+#define MSM_MADL_2(OP) MSM_MADL_1(OP) "\n\t" OP " %0, %1, %4, %5, %0"
+#define MSM_MADL_3(OP) MSM_MADL_2(OP) "\n\t" OP " %0, %1, %6, %7, %0"
+#define MSM_MADL_4(OP) MSM_MADL_3(OP) "\n\t" OP " %0, %1, %8, %9, %0"
+#define MSM_MADL_5(OP) MSM_MADL_4(OP) "\n\t" OP " %0, %1, %10, %11, %0"
+#define MSM_MADL_6(OP) MSM_MADL_5(OP) "\n\t" OP " %0, %1, %12, %13, %0"
+#define MSM_MADL_7(OP) MSM_MADL_6(OP) "\n\t" OP " %0, %1, %14, %15, %0"
+#define MSM_MADL_8(OP) MSM_MADL_7(OP) "\n\t" OP " %0, %1, %16, %17, %0"
+#define MSM_MADL_9(OP) MSM_MADL_8(OP) "\n\t" OP " %0, %1, %18, %19, %0"
+#define MSM_MADL_10(OP) MSM_MADL_9(OP) "\n\t" OP " %0, %1, %20, %21, %0"
+#define MSM_MADL_11(OP) MSM_MADL_10(OP) "\n\t" OP " %0, %1, %22, %23, %0"
+#define MSM_MADL_12(OP) MSM_MADL_11(OP) "\n\t" OP " %0, %1, %24, %25, %0"
+#define MSM_MADL_13(OP) MSM_MADL_12(OP) "\n\t" OP " %0, %1, %26, %27, %0"
+#define MSM_MADL_14(OP) MSM_MADL_13(OP) "\n\t" OP " %0, %1, %28, %29, %0"
+#define MSM_MADL_15(OP) MSM_MADL_14(OP) "\n\t" OP " %0, %1, %30, %31, %0"
+#define MSM_MADL_16(OP) MSM_MADL_15(OP) "\n\t" OP " %0, %1, %32, %33, %0"
+#define MSM_MADL_17(OP) MSM_MADL_16(OP) "\n\t" OP " %0, %1, %34, %35, %0"
+#define MSM_MADL_18(OP) MSM_MADL_17(OP) "\n\t" OP " %0, %1, %36, %37, %0"
+#define MSM_MADL_19(OP) MSM_MADL_18(OP) "\n\t" OP " %0, %1, %38, %39, %0"
+#define MSM_MADL_20(OP) MSM_MADL_19(OP) "\n\t" OP " %0, %1, %40, %41, %0"
+#define MSM_MADL_21(OP) MSM_MADL_20(OP) "\n\t" OP " %0, %1, %42, %43, %0"
+#define MSM_MADL_22(OP) MSM_MADL_21(OP) "\n\t" OP " %0, %1, %44, %45, %0"
+#define MSM_MADL_23(OP) MSM_MADL_22(OP) "\n\t" OP " %0, %1, %46, %47, %0"
+#define MSM_MADL_24(OP) MSM_MADL_23(OP) "\n\t" OP " %0, %1, %48, %49, %0"
+#define MSM_MADL_25(OP) MSM_MADL_24(OP) "\n\t" OP " %0, %1, %50, %51, %0"
 
-#define MSM_MAD64_3(OP, CB, acc, cc, a0, b0, a1, b1, a2, b2) \
-  asm(OP" %0, %1, %2, %3, %0\n\t" \
-      OP" %0, %1, %4, %5, %0\n\t" \
-      OP" %0, %1, %6, %7, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0), "v"(a1), CB(b1), "v"(a2), CB(b2))
+// the first n operand pairs: two VGPRs (x, y), a VGPR and an SGPR (u, q)
+#define MSM_MADV_1 "v"(x[0]), "v"(y[0])
+#define MSM_MADV_2 MSM_MADV_1, "v"(x[1]), "v"(y[1])
+#define MSM_MADV_3 MSM_MADV_2, "v"(x[2]), "v"(y[2])
+#define MSM_MADV_4 MSM_MADV_3, "v"(x[3]), "v"(y[3])
+#define MSM_MADV_5 MSM_MADV_4, "v"(x[4]), "v"(y[4])
+#define MSM_MADV_6 MSM_MADV_5, "v"(x[5]), "v"(y[5])
+#define MSM_MADV_7 MSM_MADV_6, "v"(x[6]), "v"(y[6])
+#define MSM_MADV_8 MSM_MADV_7, "v"(x[7]), "v"(y[7])
+#define MSM_MADV_9 MSM_MADV_8, "v"(x[8]), "v"(y[8])
+#define MSM_MADV_10 MSM_MADV_9, "v"(x[9]), "v"(y[9])
+#define MSM_MADV_11 MSM_MADV_10, "v"(x[10]), "v"(y[10])
+#define MSM_MADV_12 MSM_MADV_11, "v"(x[11]), "v"(y[11])
+#define MSM_MADV_13 MSM_MADV_12, "v"(x[12]), "v"(y[12])
+#define MSM_MADV_14 MSM_MADV_13, "v"(x[13]), "v"(y[13])
+#define MSM_MADS_1 "v"(u[0]), "s"(q[0])
+#define MSM_MADS_2 MSM_MADS_1, "v"(u[1]), "s"(q[1])
+#define MSM_MADS_3 MSM_MADS_2, "v"(u[2]), "s"(q[2])
+#define MSM_MADS_4 MSM_MADS_3, "v"(u[3]), "s"(q[3])
+#define MSM_MADS_5 MSM_MADS_4, "v"(u[4]), "s"(q[4])
+#define MSM_MADS_6 MSM_MADS_5, "v"(u[5]), "s"(q[5])
+#define MSM_MADS_7 MSM_MADS_6, "v"(u[6]), "s"(q[6])
+#define MSM_MADS_8 MSM_MADS_7, "v"(u[7]), "s"(q[7])
+#define MSM_MADS_9 MSM_MADS_8, "v"(u[8]), "s"(q[8])
+#define MSM_MADS_10 MSM_MADS_9, "v"(u[9]), "s"(q[9])
+#define MSM_MADS_11 MSM_MADS_10, "v"(u[10]), "s"(q[10])
+#define MSM_MADS_12 MSM_MADS_11, "v"(u[11]), "s"(q[11])
+#define MSM_MADS_13 MSM_MADS_12, "v"(u[12]), "s"(q[12])
+#define MSM_MADS_14 MSM_MADS_13, "v"(u[13]), "s"(q[13])
 
-#define MSM_MAD64_4(OP, CB, acc, cc, a0, b0, a1, b1, a2, b2, a3, b3) \
-  asm(OP" %0, %1, %2, %3, %0\n\t" \
-      OP" %0, %1, %4, %5, %0\n\t" \
-      OP" %0, %1, %6, %7, %0\n\t" \
-      OP" %0, %1, %8, %9, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0), "v"(a1), CB(b1), "v"(a2), CB(b2), "v"(a3), CB(b3))
-
-#define MSM_MAD64_5(OP, CB, acc, cc, a0, b0, a1, b1, a2, b2, a3, b3, a4, b4) \
-  asm(OP" %0, %1, %2, %3, %0\n\t" \
-      OP" %0, %1, %4, %5, %0\n\t" \
-      OP" %0, %1, %6, %7, %0\n\t" \
-      OP" %0, %1, %8, %9, %0\n\t" \
-      OP" %0, %1, %10, %11, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0), "v"(a1), CB(b1), "v"(a2), CB(b2), "v"(a3), CB(b3), "v"(a4), CB(b4))
-
-#define MSM_MAD64_6(OP, CB, acc, cc, a0, b0, a1, b1, a2, b2, a3, b3, a4, b4, a5, b5) \
-  asm(OP" %0, %1, %2, %3, %0\n\t" \
-      OP" %0, %1, %4, %5, %0\n\t" \
-      OP" %0, %1, %6, %7, %0\n\t" \
-      OP" %0, %1, %8, %9, %0\n\t" \
-      OP" %0, %1, %10, %11, %0\n\t" \
-      OP" %0, %1, %12, %13, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0), "v"(a1), CB(b1), "v"(a2), CB(b2), "v"(a3), CB(b3), "v"(a4), CB(b4), "v"(a5), CB(b5))
-
-#define MSM_MAD64_7(OP, CB, acc, cc, a0, b0, a1, b1, a2, b2, a3, b3, a4, b4, a5, b5, a6, b6) \
-  asm(OP" %0, %1, %2, %3, %0\n\t" \
-      OP" %0, %1, %4, %5, %0\n\t" \
-      OP" %0, %1, %6, %7, %0\n\t" \
-      OP" %0, %1, %8, %9, %0\n\t" \
-      OP" %0, %1, %10, %11, %0\n\t" \
-      OP" %0, %1, %12, %13, %0\n\t" \
-      OP" %0, %1, %14, %15, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0), "v"(a1), CB(b1), "v"(a2), CB(b2), "v"(a3), CB(b3), "v"(a4), CB(b4), "v"(a5), CB(b5), "v"(a6), CB(b6))
-
-#define MSM_MAD64_8(OP, CB, acc, cc, a0, b0, a1, b1, a2, b2, a3, b3, a4, b4, a5, b5, a6, b6, a7, b7) \
-  asm(OP" %0, %1, %2, %3, %0\n\t" \
-      OP" %0, %1, %4, %5, %0\n\t" \
-      OP" %0, %1, %6, %7, %0\n\t" \
-      OP" %0, %1, %8, %9, %0\n\t" \
-      OP" %0, %1, %10, %11, %0\n\t" \
-      OP" %0, %1, %12, %13, %0\n\t" \
-      OP" %0, %1, %14, %15, %0\n\t" \
-      OP" %0, %1, %16, %17, %0" \
-      : "+v"(acc), "=&s"(cc) \
-      : "v"(a0), CB(b0), "v"(a1), CB(b1), "v"(a2), CB(b2), "v"(a3), CB(b3), "v"(a4), CB(b4), "v"(a5), CB(b5), "v"(a6), CB(b6), "v"(a7), CB(b7))
-
-
-template <int N, bool SIGNED, bool SGPR_Y, typename A, typename W>
-__device__ __forceinline__ void mad64_group(A& acc, const W* x, const W* y) {
-  uint64_t cc;
-#define MSM_G1 x[0], y[0]
-#define MSM_G2 MSM_G1, x[1], y[1]
-#define MSM_G3 MSM_G2, x[2], y[2]
-#define MSM_G4 MSM_G3, x[3], y[3]
-#define MSM_G5 MSM_G4, x[4], y[4]
-#define MSM_G6 MSM_G5, x[5], y[5]
-#define MSM_G7 MSM_G6, x[6], y[6]
-#define MSM_G8 MSM_G7, x[7], y[7]
-#define MSM_CALL(f, ...) f(__VA_ARGS__)
-#define MSM_GROUP(n)                                                        \
-  if constexpr (N == n) {                                                   \
-    if constexpr (SIGNED && SGPR_Y)                                         \
-      MSM_CALL(MSM_MAD64_##n, "v_mad_i64_i32", "s", acc, cc, MSM_G##n);     \
-    else if constexpr (SIGNED)                                              \
-      MSM_CALL(MSM_MAD64_##n, "v_mad_i64_i32", "v", acc, cc, MSM_G##n);     \
-    else if constexpr (SGPR_Y)                                              \
-      MSM_CALL(MSM_MAD64_##n, "v_mad_u64_u32", "s", acc, cc, MSM_G##n);     \
-    else                                                                    \
-      MSM_CALL(MSM_MAD64_##n, "v_mad_u64_u32", "v", acc, cc, MSM_G##n);     \
+#define MSM_MAD_ASM(OP, n, ...) \
+  asm(MSM_MADL_##n(OP) : "+v"(acc), "=&s"(cc) : __VA_ARGS__)
+#define MSM_MAD_V(na)                                              \
+  if constexpr (NA == na && NM == 0) {                             \
+    if constexpr (SIGNED) MSM_MAD_ASM("v_mad_i64_i32", na, MSM_MADV_##na); \
+    else MSM_MAD_ASM("v_mad_u64_u32", na, MSM_MADV_##na);          \
   }
-  MSM_GROUP(1)
-  MSM_GROUP(2)
-  MSM_GROUP(3)
-  MSM_GROUP(4)
-  MSM_GROUP(5)
-  MSM_GROUP(6)
-  MSM_GROUP(7)
-  MSM_GROUP(8)
-#undef MSM_GROUP
-#undef MSM_CALL
-#undef MSM_G8
-#undef MSM_G7
-#undef MSM_G6
-#undef MSM_G5
-#undef MSM_G4
-#undef MSM_G3
-#undef MSM_G2
-#undef MSM_G1
+#define MSM_MAD_S(nm)                                              \
+  if constexpr (NA == 0 && NM == nm) {                             \
+    if constexpr (SIGNED) MSM_MAD_ASM("v_mad_i64_i32", nm, MSM_MADS_##nm); \
+    else MSM_MAD_ASM("v_mad_u64_u32", nm, MSM_MADS_##nm);          \
+  }
+#define MSM_MAD_VS(na, nm, n)                                      \
+  if constexpr (NA == na && NM == nm)                              \
+    MSM_MAD_ASM("v_mad_i64_i32", n, MSM_MADV_##na, MSM_MADS_##nm);
+
+// acc += sum of NA products x[t] y[t] and NM products u[t] q[t] (q in SGPRs)
+template <bool SIGNED, int NA, int NM, typename A, typename W>
+__device__ __forceinline__ void mad64_block(A& acc, const W* x, const W* y, const W* u,
+                                            const W* q) {
+  uint64_t cc;
+  MSM_MAD_V(1) MSM_MAD_V(2) MSM_MAD_V(3) MSM_MAD_V(4) MSM_MAD_V(5) MSM_MAD_V(6) MSM_MAD_V(7)
+  MSM_MAD_V(8) MSM_MAD_V(9) MSM_MAD_V(10) MSM_MAD_V(11) MSM_MAD_V(12) MSM_MAD_V(13) MSM_MAD_V(14)
+  MSM_MAD_S(1) MSM_MAD_S(2) MSM_MAD_S(3) MSM_MAD_S(4) MSM_MAD_S(5) MSM_MAD_S(6) MSM_MAD_S(7)
+  MSM_MAD_S(8) MSM_MAD_S(9) MSM_MAD_S(10) MSM_MAD_S(11) MSM_MAD_S(12) MSM_MAD_S(13) MSM_MAD_S(14)
+  MSM_MAD_VS(1, 1, 2) MSM_MAD_VS(1, 2, 3) MSM_MAD_VS(2, 1, 3) MSM_MAD_VS(2, 2, 4)
+  MSM_MAD_VS(2, 3, 5) MSM_MAD_VS(3, 2, 5) MSM_MAD_VS(3, 3, 6) MSM_MAD_VS(3, 4, 7)
+  MSM_MAD_VS(4, 3, 7) MSM_MAD_VS(4, 4, 8) MSM_MAD_VS(4, 5, 9) MSM_MAD_VS(5, 4, 9)
+  MSM_MAD_VS(5, 5, 10) MSM_MAD_VS(5, 6, 11) MSM_MAD_VS(6, 5, 11) MSM_MAD_VS(6, 6, 12)
+  MSM_MAD_VS(6, 7, 13) MSM_MAD_VS(7, 6, 13) MSM_MAD_VS(7, 7, 14) MSM_MAD_VS(7, 8, 15)
+  MSM_MAD_VS(8, 7, 15) MSM_MAD_VS(8, 8, 16) MSM_MAD_VS(8, 9, 17) MSM_MAD_VS(9, 8, 17)
+  MSM_MAD_VS(9, 9, 18) MSM_MAD_VS(9, 10, 19) MSM_MAD_VS(10, 9, 19) MSM_MAD_VS(10, 10, 20)
+  MSM_MAD_VS(10, 11, 21) MSM_MAD_VS(11, 10, 21) MSM_MAD_VS(11, 11, 22) MSM_MAD_VS(11, 12, 23)
+  MSM_MAD_VS(12, 11, 23) MSM_MAD_VS(12, 12, 24) MSM_MAD_VS(13, 12, 25)
   (void)cc;
 }
 
-// acc += sum of the L products x[t] y[t] (y in SGPRs when SGPR_Y)
-template <int L, bool SIGNED, bool SGPR_Y, typename A, typename W>
-__device__ __forceinline__ void mad64_run(A& acc, const W* x, const W* y) {
-  if constexpr (L > 0) {
-    constexpr int G = L < 8 ? L : 8;
-    mad64_group<G, SIGNED, SGPR_Y>(acc, x, y);
-    if constexpr (L > G) mad64_run<L - G, SIGNED, SGPR_Y>(acc, x + G, y + G);
-  }
-}
+#undef MSM_MAD_VS
+#undef MSM_MAD_S
+#undef MSM_MAD_V
+#undef MSM_MAD_ASM
 
 }  // namespace msm

@@ -277,8 +277,9 @@ int msm_run_noalloc(const uint32_t* xyu, const uint32_t* scalars, size_t n, int 
  * multiple of 4, at least 4);
  * tree_quad, aggregation-tree levels
  * with fewer outputs than this run on the four-lane unit (default 65536);
- * tree_wide, levels with at most this many outputs run on the wide two-wave
- * unit (default 1024).  Jobs of a batch with the same width and schedule
+ * tree_wide, the levels from the first with at most this many outputs on run
+ * in one block per window (default: from the first with at most 128 additions
+ * per window on; a level with more never does).  Jobs of a batch with the same width and schedule
  * form one class.  The schedule changes the time, never the result.  A batch
  * keeps the pointers: between runs the caller may rewrite the scalars and
  * points in place, not move them.
@@ -306,7 +307,7 @@ typedef struct msm_job {
   int c;
   int chunk;      /* accumulation entries per lane (0 = default) */
   int tree_quad;  /* quad-unit threshold of the aggregation tree (0 = 65536) */
-  int tree_wide;  /* wide-unit threshold of the aggregation tree (0 = 1024) */
+  int tree_wide;  /* outputs from which a window's levels share a block (0 = default) */
 } msm_job;
 
 typedef struct msm_batch msm_batch;

@@ -174,7 +174,7 @@ struct Plan {
   size_t long_items = 0;  // capacity of the long-span list: items and segments
   size_t long_segs = 0;
   uint64_t tree_quad = 65536;  // tree levels with fewer outputs run on quads
-  uint64_t tree_wide = 1024;   // levels with at most this many outputs on wide units
+  uint64_t tree_wide = 0;      // outputs from which a window's levels run in one block (0: k_agg.hip's rule)
   bool small_sort = false;            // the one-kernel sort
   uint32_t lo_bits = 0, hi_bits = 0;  // split of the bb bucket bits in the sort
   uint32_t tpb = 1;                   // pass-1 tiles per block (one histogram per group)

@@ -12,14 +12,16 @@
 // Every output of a level is one independent addition, the whole tree costs
 // about 2 * 2^c additions per window (as many as the running-sum method) and
 // its dependent depth is only c additions.  Large levels run one addition per
-// lane; small ones use the four-lane quad unit (quad29.hpp) to cut latency.
+// lane, the first two in one kernel; smaller ones use four-lane quads
+// (quad29.hpp) to cut latency; the last ones of a window, and its Horner pass,
+// share one block.
 //
 // Each window then forms S_w by Horner's rule on one latency unit, and group
 // aggregation Q = sum_w 2^(w c) S_w is Horner's rule over the windows of a job
 // (c doublings per window), the dependent chain the paper assigns to its
 // low-latency unit: one three-wave unit per job (wide26.hpp).  The
-// result is mapped back to Weierstrass affine form.  A "window" below is a segment: one window of one
-// job of the batch.
+// result is mapped back to Weierstrass affine form.  A "window" below is a
+// segment: one window of one job of the batch.
 #include "common.hpp"
 #include "convert.hpp"
 #include "curve29.hpp"
@@ -36,17 +38,55 @@ __device__ __forceinline__ size_t rec_index(uint32_t w, uint32_t nodes, uint32_t
   return ((size_t)w * nodes + n) * slots + s;
 }
 
-// Bucket sums and the lane and quad levels' records are signed (fe29.hpp); the
-// wide unit converts what it loads, and the last level (U = k T in the place
-// of T) stores coordinates in [0, 2p).
+// All records of the tree are signed (fe29.hpp) but the root's, which the
+// latency unit reads: U = k T in the place of T and coordinates in [0, 2p).
+
+// Levels 0 and 1 on two lanes per node of four buckets B0 .. B3: the even lane
+// adds B0 + B1, the odd one B2 + B3 = V[1]; then the even lane adds both sums, S,
+// and the odd one B1 + B3 = V[0].  One pass over the buckets where two levels
+// write and read every record again: n = 2^20 (262 K buckets) 74 -> 50 us,
+// n = 300007, signed digits (278 K) 84 -> 65.  Bound by VALU issue at two waves
+// per SIMD; 1.8 M buckets (n = 2^22) take 291 us, 221 of it issue.
+__global__ void __launch_bounds__(256) k_tree_first(const uint32_t* __restrict__ in,
+                                                    uint64_t lanes,
+                                                    uint32_t* __restrict__ out) {
+  const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= lanes) return;  // whole pairs
+  const bool odd = (g & 1u) != 0;
+  const uint32_t* B = in + (g >> 1) * 4 * XYTZ_WORDS;
+  uint32_t* O = out + (g >> 1) * 3 * XYTZ_WORDS;  // V[0], V[1], S
+  const uint32_t* mine = B + (odd ? 2 : 0) * XYTZ_WORDS;
+  const xytz29 s = padd29_full(pt29_from(ld_xytz(mine)), pt29_from(ld_xytz(mine + XYTZ_WORDS)));
+  if (odd) st_xytz(O + XYTZ_WORDS, pt29_to_words(s));
+  // the even lane's second operand is the odd lane's sum; the odd lane adds
+  // B1 and B3, read again (its registers hold the sum)
+  xytz29 l, r;
+  const xytz b1 = ld_xytz(B + XYTZ_WORDS), b3 = ld_xytz(B + 3 * XYTZ_WORDS);
+  auto other = [](const fe29& v) {
+    fe29 o;
+#pragma unroll
+    for (int i = 0; i < NL29; ++i) o.v[i] = qperm<1, 0, 3, 2>(v.v[i]);
+    return o;
+  };
+  auto pick = [&](const fe29& sum, const fe& x, const fe& y, fe29& lo, fe29& ro) {
+    const fe29 so = other(sum);
+    lo = f29_select(odd, f29_from_words(x), sum);
+    ro = f29_select(odd, f29_from_words(y), so);
+  };
+  pick(s.X, b1.X, b3.X, l.X, r.X);
+  pick(s.Y, b1.Y, b3.Y, l.Y, r.Y);
+  pick(s.T, b1.T, b3.T, l.T, r.T);
+  pick(s.Z, b1.Z, b3.Z, l.Z, r.Z);
+  st_xytz(O + (odd ? 0 : 2) * XYTZ_WORDS, pt29_to_words(padd29_full(l, r)));
+}
 
 // One level h -> h+1, one addition per lane: addition a < h forms slot a,
 // addition h the total (slot h + 1); the lane of addition 0 also copies
 // slot h (= R.S), so that no lane of a wave idles through another's addition.
 __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__ in, uint32_t h,
                                                     uint32_t nodes_in, uint32_t w_lo,
-                                                    uint32_t w_cnt, uint32_t* __restrict__ out,
-                                                    int to_u) {
+                                                    uint32_t w_cnt,
+                                                    uint32_t* __restrict__ out) {
   const uint32_t nodes_out = nodes_in >> 1, slots_in = h + 1, slots_out = h + 2;
   const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= (uint64_t)w_cnt * nodes_out * slots_in) return;
@@ -56,25 +96,52 @@ __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__
   const uint32_t* L = in + rec_index(w, nodes_in, 2 * n, slots_in, 0) * XYTZ_WORDS;
   const uint32_t* R = L + (size_t)slots_in * XYTZ_WORDS;
   uint32_t* O = out + rec_index(w, nodes_out, n, slots_out, 0) * XYTZ_WORDS;
-  // U = k T uses k in the 29-bit form's scale, so U stays consistent with
-  // the point's scale
-  if (a == 0) {
-    xytz29 c = pt29_from(ld_xytz(R + (size_t)h * XYTZ_WORDS));
-    if (to_u) c.T = f29_mul_const(c.T, kK29);
-    st_xytz(O + (size_t)h * XYTZ_WORDS, to_u ? pt29_to_unsigned(c) : pt29_to_words(c));
-  }
+  if (a == 0)
+    st_xytz(O + (size_t)h * XYTZ_WORDS, ld_xytz(R + (size_t)h * XYTZ_WORDS));
   const uint32_t s = a < h ? a : h + 1;  // output slot
-  xytz29 r = padd29_full(pt29_from(ld_xytz(L + (size_t)a * XYTZ_WORDS)),
-                         pt29_from(ld_xytz(R + (size_t)a * XYTZ_WORDS)));
-  if (to_u) r.T = f29_mul_const(r.T, kK29);
-  st_xytz(O + (size_t)s * XYTZ_WORDS, to_u ? pt29_to_unsigned(r) : pt29_to_words(r));
+  const xytz29 r = padd29_full(pt29_from(ld_xytz(L + (size_t)a * XYTZ_WORDS)),
+                               pt29_from(ld_xytz(R + (size_t)a * XYTZ_WORDS)));
+  st_xytz(O + (size_t)s * XYTZ_WORDS, pt29_to_words(r));
 }
 
-// Same level, four lanes per output record.
+// Levels h and h + 1 on quads, one per output record: slot t < h of a node is
+// the sum of its four grandchildren's slot t, slots h and h + 1 of S1 + S3 and
+// S2 + S3, the total of all four S (one addition more than the two levels
+// take).  Three additions in a row in one launch where two launches of one
+// addition each cost 6-8 us apiece once a level no longer fills the chip
+// (n = 65536, seven levels 58 -> 53 us; n = 300007 six levels 56 -> 46).
+__global__ void __launch_bounds__(256) k_tree_quad2(const uint32_t* __restrict__ in, uint32_t h,
+                                                    uint64_t outs, uint32_t* __restrict__ out) {
+  const uint64_t g = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 2;
+  if (g >= outs) return;  // whole quads
+  const uint32_t s = (uint32_t)(g % (h + 3));
+  const uint64_t node = g / (h + 3);  // over all windows
+  const uint32_t* R = in + (node * 4 * (h + 1) + (s < h ? s : h)) * XYTZ_WORDS;
+  const size_t stride = (size_t)(h + 1) * XYTZ_WORDS;
+  // which of the four are summed
+  uint32_t left = s == h ? 0xau : (s == h + 1 ? 0xcu : 0xfu);
+  auto next = [&] {
+    const uint32_t i = (uint32_t)__builtin_ctz(left);
+    left &= left - 1;
+    return ld_aos(R + i * stride, (int)quad_lane());
+  };
+  fe29 acc = f29_from_words(next());
+  fe w = next();
+  for (;;) {
+    const fe29 v = f29_from_words(w);
+    const bool more = left != 0;
+    if (more) w = next();
+    acc = quad_add(acc, v);
+    if (!more) break;
+  }
+  quad_st(out + g * XYTZ_WORDS, acc);
+}
+
+// One level on quads, one per output record.
 __global__ void __launch_bounds__(256) k_tree_level_quad(const uint32_t* __restrict__ in, uint32_t h,
                                                          uint32_t nodes_in, uint32_t w_lo,
                                                          uint32_t w_cnt,
-                                                         uint32_t* __restrict__ out, int to_u) {
+                                                         uint32_t* __restrict__ out) {
   const uint32_t nodes_out = nodes_in >> 1, slots_in = h + 1, slots_out = h + 2;
   const uint64_t g = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 2;
   // whole quads only: the task count test is uniform across a quad
@@ -87,122 +154,78 @@ __global__ void __launch_bounds__(256) k_tree_level_quad(const uint32_t* __restr
   const uint32_t src = (s < h) ? s : h;
   fe29 r = quad_ld(R + (size_t)src * XYTZ_WORDS);
   if (s != h) r = quad_add(quad_ld(L + (size_t)src * XYTZ_WORDS), r);
-  uint32_t* O = out + rec_index(w, nodes_out, n, slots_out, s) * XYTZ_WORDS;
-  if (to_u)
-    quad_st_unsigned(O, quad_to_u(r));
-  else
-    quad_st(O, r);
+  quad_st(out + rec_index(w, nodes_out, n, slots_out, s) * XYTZ_WORDS, r);
 }
 
-// Same level, one wide unit (two waves) per output record, for levels with
-// few outputs, where the latency of one addition sets the level's time.  The
-// operands carry T (not U = k T), so the complete addition takes three
-// product phases, four products per phase across the unit's four half-waves:
-//   1: A = (Y1 - X1)(Y2 - X2), B = (Y1 + X1)(Y2 + X2), D = 2 Z1 Z2, V = T1 T2
-//   2: C = k V, T3 = E H                      (E = B - A, H = B + A)
-//   3: X3 = E F, Y3 = G H, Z3 = F G, T3 or U3 = k T3   (F = D - C, G = D + C)
-// (subtractions add the pre-borrowed 3p).  The copy of R.S (output slot h)
-// runs phase 3 alone on (X2, Y2, Z2, T2) times (1, 1, 1, 1 or k).  Every
-// input below 2p gives products below 1.2p and product operands below 6p.
-__global__ void __launch_bounds__(128) k_tree_level_wide(const uint32_t* __restrict__ in,
-                                                         uint32_t h, uint32_t nodes_in,
-                                                         uint32_t w_lo, uint32_t w_cnt,
-                                                         uint32_t* __restrict__ out, int to_u) {
-  __shared__ wunit_lds<2> s;
-  const uint32_t nodes_out = nodes_in >> 1, slots_in = h + 1, slots_out = h + 2;
-  const uint64_t g = blockIdx.x;  // one output record per block
-  if (g >= (uint64_t)w_cnt * nodes_out * slots_out) return;
-  const uint32_t slot = (uint32_t)(g % slots_out);
-  const uint32_t t = (uint32_t)(g / slots_out);
-  const uint32_t n = t % nodes_out, w = w_lo + t / nodes_out;
-  const uint32_t src = slot < h ? slot : h;
-  const uint32_t* L = in + rec_index(w, nodes_in, 2 * n, slots_in, src) * XYTZ_WORDS;
-  const uint32_t* R = in + rec_index(w, nodes_in, 2 * n + 1, slots_in, src) * XYTZ_WORDS;
-  wunit_init(s);
-  // operand limbs: thread e loads limb e & 15 of coordinate (e >> 4) & 3 of
-  // L (e < 64, into acc) or R (into opd[0])
-  {
-    const uint32_t e = threadIdx.x, coord = (e >> 4) & 3u, j = e & 15u;
-    const uint32_t* rec = e < 64 ? L : R;
-    const limb_src v = wu_fetch(rec, coord, j);
-    uint32_t limb = limb_extract(v, j);
-    // 2p added to a negative coordinate, whose top limb then loses the
-    // 2^384 of its two's complement
-    if ((int32_t)rec[coord * NL + NL - 1] < 0)
-      limb += 2u * kP24[j] - (j == 15 ? 1u << 24 : 0u);
-    (e < 64 ? s.acc : s.opd[0])[16 * coord + j] = limb;
-  }
-  unit_sync();
-  const wslot q = wslot_here();
-  const uint32_t wave = threadIdx.x >> 6;
-  uint32_t* P1 = s.prod[0];  // A, B, D, V
-  uint32_t* P2 = s.prod[1];  // C, T3
-  uint32_t* O = s.opd[1];    // output X, Y, T or U, Z
-  const uint32_t c3 = s.c3p[q.j];
-  uint32_t l3, r3;           // this half's phase-3 operands
-  if (slot == h) {
-    const uint32_t* R2 = s.opd[0];
-    l3 = q.k == 3 ? (to_u ? limb_of_const(kK, q.j) : limb_of_const(kOne, q.j))
-                  : limb_of_const(kOne, q.j);
-    r3 = R2[16 * (q.k == 2 ? 3u : (q.k == 3 ? 2u : q.k)) + q.j];  // X2, Y2, Z2, T2
-  } else {
-    {
-      const uint32_t* X = s.acc;
-      const uint32_t* Y = s.opd[0];
-      const uint32_t x1 = X[q.j], y1 = X[16 + q.j], x2 = Y[q.j], y2 = Y[16 + q.j];
-      uint32_t l = q.k == 0 ? (y1 + c3) - x1 : (q.k == 1 ? y1 + x1 : X[16 * (5u - q.k) + q.j]);
-      uint32_t r = q.k == 0 ? (y2 + c3) - x2 : (q.k == 1 ? y2 + x2 : Y[16 * (5u - q.k) + q.j]);
-      uint32_t v = wmul2_hi(q.act ? l : 0u, q.act ? r : 0u, s.mul[wave]);  // A, B, Z1 Z2, T1 T2
-      if (q.k == 2) v <<= 1;                                               // D = 2 Z1 Z2
-      if (!q.act) P1[16 * q.k + q.j] = v;
-    }
-    unit_sync();
-    const uint32_t A = P1[q.j], B = P1[16 + q.j];
-    if (wave == 0) {
-      const uint32_t l = q.k == 0 ? limb_of_const(kK, q.j) : (B + c3) - A;
-      const uint32_t r = q.k == 0 ? P1[48 + q.j] : B + A;
-      const uint32_t v = wmul2_hi(q.act ? l : 0u, q.act ? r : 0u, s.mul[0]);  // C, T3
-      if (!q.act) P2[16 * q.k + q.j] = v;
-    }
-    unit_sync();
-    const uint32_t D = P1[32 + q.j], C = P2[q.j];
-    const uint32_t E = (B + c3) - A, H = B + A, F = (D + c3) - C, G = D + C;
-    l3 = q.k == 0 ? E : (q.k == 1 ? G : (q.k == 2 ? F : (to_u ? limb_of_const(kK, q.j)
-                                                             : limb_of_const(kOne, q.j))));
-    r3 = q.k == 0 ? F : (q.k == 1 ? H : (q.k == 2 ? G : P2[16 + q.j]));
-  }
-  const uint32_t v = wmul2_hi(q.act ? l3 : 0u, q.act ? r3 : 0u, s.mul[wave]);
-  // X3, Y3, Z3, T3 / U3 to coordinates 0, 1, 3, 2
-  if (!q.act) O[16 * (q.k == 2 ? 3u : (q.k == 3 ? 2u : q.k)) + q.j] = v;
-  __syncthreads();  // the record's coordinates come from both waves
-  const uint32_t lane = wlane();
-  if (wave == 0 && lane < 4)
-    st_aos(out + rec_index(w, nodes_out, n, slots_out, slot) * XYTZ_WORDS, (int)lane,
-           words_of_limbs(O + 16 * lane));
-}
-
-// Per window (block w, one latency unit of wide26.hpp): S_w = sum_t 2^t X_t
-// (+ S for signed digits) by Horner's rule over the bits t, with X_t (slot
-// t < bb of the tree's root) and S (slot bb) in XYUZ form.  Writes S_w as XYTZ
+// A window's last levels h0 .. bb - 1 and its Horner pass, one block per window
+// (block w).  The levels run on the block's quads, the records between them in
+// LDS; the root goes to LDS in the form the latency unit reads, and waves 0..2
+// form S_w = sum_t 2^t X_t (+ S for signed digits) by Horner's rule over the
+// bits t (X_t: slot t < bb of the root, S: slot bb).  Writes S_w as XYTZ
 // (record 2w) and XYUZ (record 2w + 1).  Wave 2 loads each slot a step ahead
 // and lays it out as the next addition's operand.
-__global__ void __launch_bounds__(W26_THREADS) k_window_combine(const uint32_t* __restrict__ root,
-                                                                uint32_t bb, int add_total,
-                                                                uint32_t* __restrict__ wsum) {
+// A level costs its ~3 us of one quad addition where a launch of its own took
+// 6: n = 1024, unsigned digits of 8 bits, all eight levels and the Horner pass
+// 61 -> 48 us; n = 2^20, four levels 49 -> 43.
+constexpr uint32_t TAIL_THREADS = 512;
+constexpr uint32_t TAIL_ADDS = 128;  // one addition per quad at level h0
+
+// words of LDS for the records after level h0 (the largest) and after the next
+inline size_t tail_words(uint32_t h0, uint32_t bb, size_t& second) {
+  const size_t rec = 4 * NL29, n0 = (size_t)1 << (bb - 1 - h0);
+  second = h0 + 2 < bb ? (n0 >> 1) * (h0 + 3) * rec : 0;
+  return h0 + 1 < bb ? n0 * (h0 + 2) * rec : 0;
+}
+
+__global__ void __launch_bounds__(TAIL_THREADS) k_window_tail(const uint32_t* __restrict__ in,
+                                                              uint32_t h0, uint32_t bb,
+                                                              uint32_t second_at, int add_total,
+                                                              uint32_t* __restrict__ wsum) {
+  extern __shared__ int32_t lv[];  // records [4][NL29], two buffers
   __shared__ __attribute__((aligned(16))) w26_lds s;
-  const uint32_t w = blockIdx.x;
+  __shared__ __attribute__((aligned(16))) uint32_t root[21 * XYTZ_WORDS];  // bb + 1 <= 21 slots
+  const uint32_t w = blockIdx.x, quad = threadIdx.x >> 2, c = quad_lane();
+  const uint32_t* base = in + ((size_t)w << (bb - h0)) * (h0 + 1) * XYTZ_WORDS;
+  const int32_t* from = lv;
+  int32_t* to = lv;
+  for (uint32_t h = h0; h < bb; ++h) {
+    const uint32_t nodes = 1u << (bb - 1 - h), adds = nodes * (h + 1);
+    auto load = [&](uint32_t r) {
+      if (h == h0) return quad_ld(base + (size_t)r * XYTZ_WORDS);
+      fe29 v;
+#pragma unroll
+      for (int i = 0; i < NL29; ++i) v.v[i] = from[(4 * r + c) * NL29 + i];
+      return v;
+    };
+    // the additions, then the copies of R.S
+    for (uint32_t a = quad; a < adds + nodes; a += TAIL_THREADS / 4) {
+      const bool add = a < adds;
+      const uint32_t n = add ? a / (h + 1) : a - adds, src = add ? a % (h + 1) : h;
+      fe29 r = load((2 * n + 1) * (h + 1) + src);
+      if (add) r = quad_add(load(2 * n * (h + 1) + src), r);
+      const uint32_t slot = !add ? h : (src < h ? src : h + 1);
+      if (h + 1 == bb) {
+        quad_st_unsigned(root + slot * XYTZ_WORDS, quad_to_u(r));
+      } else {
+#pragma unroll
+        for (int i = 0; i < NL29; ++i) to[(4 * (n * (h + 2) + slot) + c) * NL29 + i] = r.v[i];
+      }
+    }
+    __syncthreads();
+    from = to;
+    to = lv + (to == lv ? second_at : 0);
+  }
+  if (threadIdx.x >= W26_THREADS) return;  // the barriers below are the first three waves'
   const w26_lane q = w26_lane_here(s);
-  const uint32_t* V = root + (size_t)w * (bb + 1) * XYTZ_WORDS;
   const int steps = (int)bb + (add_total ? 1 : 0);
   // step i adds slot bb - 1 - i (i < bb) or the total (slot bb); clamped
-  auto slot = [&](int i) { return V + (size_t)(i < (int)bb ? (int)bb - 1 - i : (int)bb) * XYTZ_WORDS; };
-  w26_fetch f;
-  if (q.wave == 2) f = w26_load(slot(0));
+  auto slot = [&](int i) { return root + (i < (int)bb ? (int)bb - 1 - i : (int)bb) * XYTZ_WORDS; };
   w26_init(s);
   w26_sync();
+  w26_fetch f;
   if (q.wave == 2) {
     w26_put_identity(s);
-    w26_put_operand(s, q, f, 0);
+    w26_put_operand(s, q, w26_load(slot(0)), 0);
     f = w26_load(slot(1));
   }
   w26_sync();
@@ -333,25 +356,43 @@ int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStrea
   uint32_t* wsum = ws_at<uint32_t>(ws, pl.o_wsum);
   ProfScope prof(PT_AGG, st);
   const uint32_t* in = buckets;
-  uint32_t nodes = 1u << bb;
-  for (uint32_t h = 0; h < bb; ++h) {
-    uint32_t* out = lv[h & 1];
-    const uint64_t outs = (uint64_t)S * (nodes >> 1) * (h + 2);
-    const int to_u = (h + 1 == bb) ? 1 : 0;
-    const uint64_t adds = (uint64_t)S * (nodes >> 1) * (h + 1);
-    // the schedule's unit thresholds (defaults: below 65536 outputs a level
-    // runs on quads, up to 1024 outputs on wide units, one per output)
-    if (outs >= pl.tree_quad)
-      k_tree_level<<<(unsigned)((adds + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S, out, to_u);
-    else if (outs > pl.tree_wide)
-      k_tree_level_quad<<<(unsigned)((4 * outs + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S,
-                                                                           out, to_u);
-    else
-      k_tree_level_wide<<<(unsigned)outs, 128, 0, st>>>(in, h, nodes, 0, S, out, to_u);
+  uint32_t nodes = 1u << bb, h = 0, level = 0;
+  // outputs and additions of level h over all windows
+  auto outs = [&](uint32_t l) { return ((uint64_t)S << (bb - 1 - l)) * (l + 2); };
+  auto adds = [&](uint32_t l) { return ((uint64_t)S << (bb - 1 - l)) * (l + 1); };
+  // the fused tail: from the first level with one addition per quad of a
+  // window's block on (or a schedule's number of outputs over all windows)
+  auto tail = [&](uint32_t l) {
+    return l + 1 == bb || (adds(l) <= (uint64_t)S * TAIL_ADDS &&
+                           (pl.tree_wide == 0 || outs(l) <= pl.tree_wide));
+  };
+  while (!tail(h)) {
+    uint32_t* out = lv[level++ & 1];
+    // one lane per addition down to tree_quad outputs, then quads
+    if (h == 0 && !tail(1) && outs(1) >= pl.tree_quad) {
+      const uint64_t lanes = (uint64_t)S << (bb - 1);
+      k_tree_first<<<(unsigned)((lanes + 255) / 256), 256, 0, st>>>(in, lanes, out);
+      ++h;
+      nodes >>= 1;
+    } else if (outs(h) >= pl.tree_quad) {
+      k_tree_level<<<(unsigned)((adds(h) + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S, out);
+    } else if (!tail(h + 1)) {
+      const uint64_t o2 = outs(h + 1);
+      k_tree_quad2<<<(unsigned)((4 * o2 + 255) / 256), 256, 0, st>>>(in, h, o2, out);
+      ++h;
+      nodes >>= 1;
+    } else {
+      k_tree_level_quad<<<(unsigned)((4 * outs(h) + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S,
+                                                                              out);
+    }
     in = out;
+    ++h;
     nodes >>= 1;
   }
-  k_window_combine<<<S, W26_THREADS, 0, st>>>(in, bb, pl.encoding == MSM_DIGITS_UNSIGNED ? 0 : 1, wsum);
+  size_t second = 0;
+  const size_t first = tail_words(h, bb, second);
+  k_window_tail<<<S, TAIL_THREADS, (first + second) * 4, st>>>(
+      in, h, bb, (uint32_t)first, pl.encoding == MSM_DIGITS_UNSIGNED ? 0 : 1, wsum);
   HIPCHK(hipGetLastError());
   return MSM_OK;
 }

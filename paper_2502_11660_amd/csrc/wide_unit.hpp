@@ -1,9 +1,8 @@
 // Latency-oriented point arithmetic on wide elements: two waves per point.
 //
-// The unit of the dependent chain of msm_padd_chain, of few accumulators of
-// msm_accumulate_stream and of the smallest levels of the aggregation tree
-// (Sec. V-A's separate low-latency PADD mapping; the Horner chains run on
-// wide26.hpp).  Here one point occupies two waves: every formula below has
+// The unit of the dependent chain of msm_padd_chain and of few accumulators of
+// msm_accumulate_stream (Sec. V-A's separate low-latency PADD mapping; the
+// Horner chains run on wide26.hpp).  Here one point occupies two waves: every formula below has
 // four independent products per phase, and the four 32-lane halves of the two
 // waves each compute one of them with wmul2 (the half's index k = 2 wave +
 // half picks the product).  Coordinates live in LDS between phases as 16

@@ -246,13 +246,109 @@ __global__ void __launch_bounds__(TAIL_THREADS) k_window_tail(const uint32_t* __
   }
 }
 
-// Group aggregation of job j (block j, one latency unit): Q = sum_w 2^(w c) S_w
-// by Horner's rule over the job's W windows; wave 2 loads the next window's
-// sum during the doublings.
-__global__ void __launch_bounds__(W26_THREADS) k_horner_wide(const uint32_t* __restrict__ wsum,
-                                                             uint32_t W, uint32_t c,
-                                                             uint32_t* __restrict__ qstate) {
+// Twisted-Edwards extended (Montgomery form) -> Weierstrass affine, ordinary
+// form, canonical, on one wave: the field inversion is lane-parallel
+// (fe_inv_lanes) and the ten products around it run as wide products, two at
+// a time (one per half-wave), in five dependent steps:
+//   d = (Z - Y) X, un = (Z + Y) X;   [d^-1]   im = d^-1 R^3 (Montgomery
+//   inverse), vn = (Z + Y) Z;   u = un im, v = vn im;   u alpha, v beta;
+//   x = (u alpha - 1) / R, y = v beta / R (out of Montgomery form).
+// The steps are one loop over operands in LDS, and the reductions one
+// function: code that a lone wave runs once costs its instruction fetches
+// too (written out step by step the conversion was three times as long, and
+// the kernel 10 us slower).
+enum { AF_D, AF_UN, AF_VN, AF_X, AF_Z, AF_ZMY, AF_ZPY, AF_R3, AF_ALPHA, AF_BETA, AF_UNIT, AF_SLOTS };
+
+struct affine_lds {
+  uint32_t mul[WMUL2_WORDS];
+  uint32_t slot[AF_SLOTS][16];
+  uint32_t q[XYTZ_WORDS];  // the point
+};
+__device__ const uint32_t kAffineConsts[3][NL] = {
+    {0x8815de20u, 0x581f532fu, 0xbe329585u, 0xe50f4148u, 0x0449f513u, 0x2be8b118u,
+     0xc804a20eu, 0x6a2a9516u, 0x13590cb9u, 0x3f725407u, 0xc0e7dda5u, 0x01065ab4u},
+    {0x8894e1e4u, 0x3fabdfd0u, 0xcc1f55aau, 0xcbf921ddu, 0x460edc0cu, 0xd17deff1u,
+     0x7897028du, 0xd394e81eu, 0x0912681au, 0xc29c995du, 0xaff9d568u, 0x01515e6cu},
+    {0xa38cfd11u, 0xface0c97u, 0x0adb8383u, 0x8cc7c229u, 0xd44ae9cbu, 0x4765cd5fu,
+     0x22354029u, 0x9ae986d8u, 0x252ab9bdu, 0xc3dc7860u, 0xc8942395u, 0x00486011u}};
+
+// canonical words of 16 lazily reduced limbs
+__device__ __noinline__ fe canon_of_limbs(const uint32_t* limbs) {
+  return fe_canon(words_of_limbs(limbs));
+}
+
+// Lane 32 h gets x (h = 0) or y (h = 1) of the point s.q; false for the
+// identity (zero for both).
+__device__ __forceinline__ bool wide_to_weierstrass(affine_lds& s, fe& out) {
+  const uint32_t lane = wlane(), h = lane >> 5, j = lane & 15u;
+  const bool act = (lane & 31u) < 16u;
+  const uint32_t c2p = 2u * kP24[j] + (j < 15 ? (1u << 26) : 0u) - (j >= 1 ? 4u : 0u);
+  wmul2_init(s.mul);
+  if (lane < 16) {
+    const uint32_t X = limb_extract(limb_fetch(s.q, j), j),
+                   Y = limb_extract(limb_fetch(s.q + NL, j), j),
+                   Z = limb_extract(limb_fetch(s.q + 3 * NL, j), j);
+    s.slot[AF_X][j] = X;
+    s.slot[AF_Z][j] = Z;
+    s.slot[AF_ZMY][j] = (Z + c2p) - Y;
+    s.slot[AF_ZPY][j] = Z + Y;
+    s.slot[AF_UNIT][j] = j == 0 ? 1u : 0u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      s.slot[AF_R3 + k][j] = limb_extract(limb_fetch(kAffineConsts[k], j), j);
+  }
+  wave_lds_sync();
+  // operands and results of the steps by half, a byte each: l, r, result
+  constexpr uint32_t kStep[5][2] = {
+      {AF_ZMY | AF_X << 8 | AF_D << 16, AF_ZPY | AF_X << 8 | AF_UN << 16},
+      {AF_D | AF_R3 << 8 | AF_D << 16, AF_ZPY | AF_Z << 8 | AF_VN << 16},
+      {AF_UN | AF_D << 8 | AF_D << 16, AF_VN | AF_D << 8 | AF_VN << 16},
+      {AF_D | AF_ALPHA << 8 | AF_D << 16, AF_VN | AF_BETA << 8 | AF_VN << 16},
+      {AF_D | AF_UNIT << 8 | AF_D << 16, AF_VN | AF_UNIT << 8 | AF_VN << 16}};
+  bool finite = true;
+#pragma unroll 1
+  for (int i = 0; i < 5; ++i) {
+    uint32_t op = h ? kStep[0][1] : kStep[0][0];
+#pragma unroll
+    for (int k = 1; k < 5; ++k) op = i == k ? (h ? kStep[k][1] : kStep[k][0]) : op;
+    const uint32_t l = s.slot[op & 0xffu][j], r = s.slot[(op >> 8) & 0xffu][j];
+    uint32_t v = wmul2_hi(act ? l : 0u, act ? r : 0u, s.mul);
+    // u alpha - 1 (Montgomery)
+    if (i == 3 && h == 0) v += c2p - limb_of_const(kOne, j);
+    if (!act) s.slot[op >> 16][j] = v;
+    wave_lds_sync();
+    if (i == 0) {
+      const fe d = canon_of_limbs(s.slot[AF_D]);  // 0 for the identity alone (y = 1 or x = 0)
+      finite = !fe_is_zero_canon(d);
+      const fe inv = fe_inv_lanes(d);
+      wave_lds_sync();
+      if (lane < NL) {
+        uint32_t w = inv.v[0];
+#pragma unroll
+        for (uint32_t k = 1; k < (uint32_t)NL; ++k) w = lane == k ? inv.v[k] : w;
+        s.q[lane] = w;
+      }
+      wave_lds_sync();
+      if (lane < 16) s.slot[AF_D][j] = limb_extract(limb_fetch(s.q, j), j);
+      wave_lds_sync();
+    }
+  }
+  out = canon_of_limbs(s.slot[h ? AF_VN : AF_D]);
+  if (!finite) out = fe_zero();
+  return finite;
+}
+
+// Group aggregation and the affine result of job j (block j): Q = sum_w 2^(w c)
+// S_w by Horner's rule over the job's W windows on one latency unit, wave 2
+// loading the next window's sum during the doublings; then wave 0 maps Q
+// back and writes the result.  One kernel: the conversion alone took 33 us, a
+// launch and a round trip of Q through memory among them (n = 33: group
+// aggregation and conversion 212 -> 202 us).
+__global__ void __launch_bounds__(W26_THREADS) k_group(const uint32_t* __restrict__ wsum,
+                                                       uint32_t W, uint32_t c, JobView jv,
+                                                       const uint32_t* __restrict__ flags) {
   __shared__ __attribute__((aligned(16))) w26_lds s;
+  __shared__ __attribute__((aligned(16))) affine_lds a;
   const uint32_t job = blockIdx.x;
   const w26_lane q = w26_lane_here(s);
   const uint32_t* ws = wsum + (size_t)2 * job * W * XYTZ_WORDS;
@@ -280,73 +376,19 @@ __global__ void __launch_bounds__(W26_THREADS) k_horner_wide(const uint32_t* __r
     });
     o ^= 1;
   }
-  if (q.wave == 0) w26_store(s, qstate + (size_t)job * XYTZ_WORDS, W26_T);
-}
-
-// Twisted-Edwards extended (Montgomery form) -> Weierstrass affine, ordinary
-// form, canonical, on one wave whose lanes all hold Q: the field inversion is
-// lane-parallel (fe_inv_lanes) and the ten products around it run as wide
-// products, two per step (one per half-wave), in five dependent steps:
-//   d = (Z - Y) X, un = (Z + Y) X;   [d^-1]   im = d^-1 R^3 (Montgomery
-//   inverse), vn = (Z + Y) Z;   u = un im, v = vn im;   u alpha, v beta;
-//   x = (u alpha - 1) / R, y = v beta / R (out of Montgomery form).
-// Returns false for the identity (x = y = 0 written).
-__device__ bool wide_to_weierstrass(const xytz& Q, fe& xw, fe& yw, uint32_t* mul,
-                                    uint32_t* stage) {
-  if (fe_is_zero_canon(fe_canon(Q.X))) {
-    xw = fe_zero();
-    yw = fe_zero();
-    return false;
-  }
-  const uint32_t lane = wlane(), h = lane >> 5, j = lane & 15u;
-  const bool act = (lane & 31u) < 16u;
-  const uint32_t c2p = 2u * kP24[j] + (j < 15 ? (1u << 26) : 0u) - (j >= 1 ? 4u : 0u);
-  const uint32_t X = limb_of_const(Q.X.v, j), Y = limb_of_const(Q.Y.v, j),
-                 Z = limb_of_const(Q.Z.v, j);
-  // one step: half h multiplies its (l, r); the result limbs go to
-  // stage[16 slot_h + j]
-  auto step = [&](uint32_t l, uint32_t r, uint32_t slot0, uint32_t slot1) {
-    const uint32_t v = wmul2_hi(act ? l : 0u, act ? r : 0u, mul);
-    if (!act) stage[16 * (h ? slot1 : slot0) + j] = v;
-    wave_lds_sync();
-  };
-  wmul2_init(mul);
-  // stage slots: 0 d / im / u / u alpha / x, 1 un, 2 vn / v / v beta / y
-  step(h ? Z + Y : (Z + c2p) - Y, X, 0, 1);  // d (< 1.2p), un
-  const fe inv = fe_inv_lanes(fe_canon(words_of_limbs(stage)));
-  const uint32_t iv = limb_of_const(inv.v, j);
-  step(h ? Z + Y : iv, h ? Z : limb_of_const(kR3, j), 0, 2);  // im, vn
-  step(h ? stage[32 + j] : stage[16 + j], stage[j], 0, 2);    // u, v
-  step(stage[(h ? 32 : 0) + j], h ? limb_of_const(kBeta, j) : limb_of_const(kAlpha, j), 0, 2);
-  const uint32_t am = (stage[j] + c2p) - limb_of_const(kOne, j);  // u alpha - 1 (Montgomery)
-  step(h ? stage[32 + j] : am, j == 0 ? 1u : 0u, 0, 2);           // times 1 / R
-  xw = fe_canon(words_of_limbs(stage));
-  yw = fe_canon(words_of_limbs(stage + 32));
-  return true;
-}
-
-// The affine Weierstrass result of each job, one wave per job (lane 0
-// writes).
-__global__ void __launch_bounds__(64) k_finalize(const uint32_t* __restrict__ qstate, JobView jv,
-                                                 const uint32_t* __restrict__ flags) {
-  __shared__ uint32_t mul[WMUL2_WORDS];
-  __shared__ uint32_t stage[48];
-  const uint32_t j = blockIdx.x;
-  uint32_t* result = jv.get(j).result;
-  xytz Q = ld_xytz(qstate + (size_t)j * XYTZ_WORDS);
-  fe xw, yw;
-  bool fin = wide_to_weierstrass(Q, xw, yw, mul, stage);
-  if (threadIdx.x != 0) return;
+  if (q.wave != 0) return;
+  w26_store(s, a.q, W26_T);
+  wave_lds_sync();
+  fe out;
+  const bool finite = wide_to_weierstrass(a, out);
+  uint32_t* result = jv.get(job).result;
+  const uint32_t lane = wlane();
+  if ((lane & 31u) == 0)
 #pragma unroll
-  for (int l = 0; l < NL; ++l) {
-    result[l] = xw.v[l];
-    result[NL + l] = yw.v[l];
-  }
-  result[2 * NL] = fin ? 0u : 1u;
-  result[2 * NL + 1] = flags[j];
-  for (int l = 2 * NL + 2; l < MSM_RESULT_WORDS; ++l) result[l] = 0u;
+    for (int l = 0; l < NL; ++l) result[(lane >> 5) * NL + l] = out.v[l];
+  if (lane < MSM_RESULT_WORDS - 2 * NL)
+    result[2 * NL + lane] = lane == 0 ? (finite ? 0u : 1u) : (lane == 1 ? flags[job] : 0u);
 }
-
 
 }  // namespace
 
@@ -400,10 +442,9 @@ int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStrea
 int launch_horner(const Plan& pl, void* ws, hipStream_t st) {
   ProfScope prof(PT_HORNER, st);
   const JobView jv = job_view(pl, ws);
-  uint32_t* qstate = ws_at<uint32_t>(ws, pl.o_qstate);
-  k_horner_wide<<<(unsigned)pl.J, W26_THREADS, 0, st>>>(ws_at<uint32_t>(ws, pl.o_wsum), (uint32_t)pl.W,
-                                                 (uint32_t)pl.c, qstate);
-  k_finalize<<<(unsigned)pl.J, 64, 0, st>>>(qstate, jv, ws_at<uint32_t>(ws, pl.o_flags));
+  k_group<<<(unsigned)pl.J, W26_THREADS, 0, st>>>(ws_at<uint32_t>(ws, pl.o_wsum), (uint32_t)pl.W,
+                                                  (uint32_t)pl.c, jv,
+                                                  ws_at<uint32_t>(ws, pl.o_flags));
   HIPCHK(hipGetLastError());
   return MSM_OK;
 }

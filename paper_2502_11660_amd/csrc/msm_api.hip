@@ -241,7 +241,6 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
   pl.o_tail = pl.o_head + pl.chunks * rec;
   pl.o_lvl1 = pl.o_buckets;
   pl.o_wsum = take(2 * pl.S * rec);
-  pl.o_qstate = take((size_t)J * rec);
   pl.o_jobs = take((size_t)J * sizeof(JobDesc));
   pl.o_segoff = take(pl.S * 8);
   pl.bytes = o;

@@ -54,11 +54,11 @@ def n_bucket(n):
 def default_chunk(total_entries, cus=256):
     """The average length of the library's default accumulation chunks for a
     class with this many digit entries: one chunk per lane of one, two or
-    three waves per SIMD (below 16 and 48 entries a lane of one wave), at
+    three waves per SIMD (below 16 and 160 entries a lane of one wave), at
     least 4 entries; the library splits that into lengths K and K + 4
     (multiples of 4)."""
     e, lanes = int(total_entries), cus * 4 * 64
-    waves = 1 if e < 16 * lanes else 2 if e < 48 * lanes else 3
+    waves = 1 if e < 16 * lanes else 2 if e < 160 * lanes else 3
     return max(4, -(-e // (waves * lanes)))
 
 

@@ -135,14 +135,15 @@ struct AccumGeom {
 };
 // Quads up to 2^18 digit slots: above, lanes of four entries are as fast.
 constexpr size_t ACCUM_QUAD_MAX = (size_t)1 << 18;
-// Units for E entries.  Lanes: one wave a SIMD up to 16 entries a lane (a second
-// wave shares the SIMD's issue slots and doubles the split buckets), two up to
-// 24, three above (the most its registers allow).  n = 65536, split digits
-// (1.3 M entries): lanes of 16 took 242 us, two waves a SIMD of lanes of 10
-// take 147.
+// Units for E entries.  Lanes: a lone wave a SIMD leaves 13% of its issue slots
+// empty, and each further wave doubles or halves again the split buckets to
+// merge.  One wave up to 16 entries a lane (n = 40000, split digits, 13: 442 us,
+// with two waves 457; n = 90000, 27: 502, 485), two up to 160 (n = 262144, 80: two
+// 821, three 834; n = 700000 signed, 171: 1768, 1756; n = 2^21, 512: 4297, 4128),
+// three above, the most that its registers allow.
 __host__ __device__ inline uint32_t accum_units(const AccumGeom& g, uint32_t E) {
   const uint64_t u = g.units;
-  return g.quad || E < 16 * u ? g.units : (E < 48 * u ? 2 * g.units : 3 * g.units);
+  return g.quad || E < 16 * u ? g.units : (E < 160 * u ? 2 * g.units : 3 * g.units);
 }
 
 // The one-kernel sort takes jobs of at most SMALL_SORT_MAX point records (16 for

@@ -27,7 +27,7 @@
 namespace msm {
 namespace {
 
-constexpr uint32_t SMALL_SPAN = 8;   // chunks beyond the first that one quad sums
+constexpr uint32_t SMALL_SPAN = 63;  // chunks beyond the first of a span that k_merge sums
 constexpr uint32_t SEG_HEADS = 128;  // heads of a segment of a longer span
 
 // An entry's index word is the point index in its job with the digit's sign in
@@ -263,30 +263,50 @@ struct LongList {
   __device__ __forceinline__ uint32_t* segment(uint32_t i) const { return w + 2 + 2 * items + 2 * i; }
 };
 
-// Split buckets: one quad sums tail + heads when the span is at most
-// SMALL_SPAN chunks; longer spans (skewed inputs) are listed for k_merge_long.
-// A block looks at 256 chunks and orders its sums by span, longest first, so
-// that the quads of a wave run sums of one length and none idles for a chunk
-// without a tail.  Bound by VALU issue when every chunk boundary splits a
-// bucket, by the latency of the span's additions, ~3 us each, when there
-// are few.  Against one lane a chunk: n = 2^20 (196 K chunks, span 1)
-// 73 -> 58 us, n = 65536 (split digits, spans of 3-4) 92 -> 51 us.
+// Split buckets: tail + heads, up to SMALL_SPAN heads; longer spans (skewed
+// inputs) are listed for k_merge_long.  A block looks at MERGE_CHUNKS chunks
+// and cuts their spans into runs of at most MERGE_RUN records, one quad a
+// run, ordered by length, longest first, so that the quads of a wave do sums
+// of one length and none idles for a chunk without a tail; the runs of a span
+// of several are folded pairwise through LDS.  Bound by VALU issue when
+// every chunk boundary splits a bucket, by the latency of a span's additions,
+// ~3 us each behind ~13 us of start and index loads, when there are few.
+// With spans of up to 8 on one quad each, 256 chunks a block: n = 65536 (split
+// digits, spans of 3-4, of 24 in the top window) 51 us and 39 in k_merge_long
+// -> 49 and 5; n = 2^20 in two waves a SIMD (spans of 1-2) 46 -> 42.  Runs of 3 or
+// 64 chunks a block: n = 65536 8-14 us slower, no gain elsewhere.
+constexpr uint32_t MERGE_CHUNKS = 128;
+constexpr uint32_t MERGE_RUN = 4;
+constexpr uint32_t MERGE_RUNS = MERGE_CHUNKS + SMALL_SPAN;        // a span of n heads has <= n
+constexpr uint32_t MERGE_PARTS = (MERGE_CHUNKS + SMALL_SPAN) / 2;  // of several runs, <= n / 2
+constexpr uint32_t MERGE_PAIRS = 64;  // a span of R > 1 runs has R / 2 <= n / 4
+static_assert(MERGE_CHUNKS + SMALL_SPAN <= 4 * MERGE_PAIRS && MERGE_RUNS < 256, "");
+
 __global__ void __launch_bounds__(256) k_merge(const uint32_t* __restrict__ key,
                                                const uint32_t* __restrict__ offsets,
                                                const uint32_t* __restrict__ total, uint32_t bb,
                                                AccumGeom g, const uint32_t* __restrict__ head,
                                                const uint32_t* __restrict__ tail,
                                                uint32_t* __restrict__ buckets, LongList list) {
-  __shared__ uint32_t cnt[SMALL_SPAN + 1];  // sums of each span, then their places
-  __shared__ uint2 task[256];               // tail's chunk in the block | span << 24, bucket
-  const uint32_t tid = threadIdx.x;
-  if (tid <= SMALL_SPAN) cnt[tid] = 0;
+  __shared__ uint32_t runs[MERGE_RUN + 1];  // runs of each length
+  __shared__ uint32_t parts, pairs, most;   // places, quads and most runs of spans of several
+  // a run: its first record's chunk in the block's order | length << 8 | its
+  // place in part << 16 (0xff: the whole span), its bucket; bit 31 of the
+  // first word: that record is a tail
+  __shared__ uint2 run[MERGE_RUNS];
+  // a quad of a span's fold: first place in part | runs << 8 | its number << 16,
+  // the bucket
+  __shared__ uint2 pair[MERGE_PAIRS];
+  __shared__ int32_t part[MERGE_PARTS][4][NL29];
+  const uint32_t tid = threadIdx.x, q = quad_lane();
+  if (tid <= MERGE_RUN) runs[tid] = 0;
+  if (tid == 0) parts = pairs = most = 0;
   __syncthreads();
   const uint32_t E1 = *total;
   const Chunks c = chunks_of(g, E1);
-  const uint32_t ch0 = blockIdx.x * blockDim.x;
-  uint32_t b = 0, c1 = 0;
-  uint32_t span = tail_of(key, offsets, E1, bb, c, ch0 + tid, b, c1) ? c1 - (ch0 + tid) : 0u;
+  const uint32_t ch0 = blockIdx.x * MERGE_CHUNKS;
+  uint32_t b = 0, c1 = 0, span = 0;
+  if (tid < MERGE_CHUNKS && tail_of(key, offsets, E1, bb, c, ch0 + tid, b, c1)) span = c1 - (ch0 + tid);
   if (span > SMALL_SPAN) {
     const uint32_t item = atomicAdd(&list.w[0], 1u), segs = (span + SEG_HEADS - 1) / SEG_HEADS;
     *list.item(item) = ch0 + tid;
@@ -298,26 +318,79 @@ __global__ void __launch_bounds__(256) k_merge(const uint32_t* __restrict__ key,
     }
     span = 0;
   }
-  const uint32_t rank = span ? atomicAdd(&cnt[span], 1u) : 0u;
-  __syncthreads();
-  uint32_t tasks = 0, at = 0;
-  for (uint32_t t = SMALL_SPAN; t >= 1; --t) {
-    if (t == span) at = tasks;
-    tasks += cnt[t];
-  }
-  if (span) task[at + rank] = make_uint2(tid | (span << 24), b);
-  __syncthreads();
-  for (uint32_t i = tid >> 2; i < tasks; i += 64) {
-    const uint2 t = task[i];
-    const uint32_t ch = ch0 + (t.x & 0xffffffu), n = t.x >> 24;
-    fe29 acc = quad_ld(tail + (size_t)ch * XYTZ_WORDS);
-    fe w = ld_aos(head + (size_t)(ch + 1) * XYTZ_WORDS, (int)quad_lane());
-    for (uint32_t j = 1; j <= n; ++j) {
-      const fe29 h = f29_from_words(w);
-      w = ld_aos(head + (size_t)(ch + (j < n ? j + 1 : j)) * XYTZ_WORDS, (int)quad_lane());
-      acc = quad_add(acc, h);
+  // the span's runs: `more` of len + 1 records, the others of len
+  const uint32_t nr = span ? (span + MERGE_RUN) / MERGE_RUN : 0u;
+  const uint32_t len = nr ? (span + 1) / nr : 0u, more = nr ? (span + 1) % nr : 0u;
+  uint32_t at_more = 0, at_len = 0, place = 0xffu;
+  if (nr) {
+    if (more) at_more = atomicAdd(&runs[len + 1], more);
+    at_len = atomicAdd(&runs[len], nr - more);
+    if (nr > 1) {
+      place = atomicAdd(&parts, nr);
+      const uint32_t at = atomicAdd(&pairs, nr / 2);
+      for (uint32_t i = 0; i < nr / 2; ++i) pair[at + i] = make_uint2(place | nr << 8 | i << 16, b);
+      atomicMax(&most, nr);
     }
-    quad_st(buckets + (size_t)t.y * XYTZ_WORDS, acc);
+  }
+  __syncthreads();
+  uint32_t nruns = 0;
+  for (uint32_t t = MERGE_RUN; t >= 1; --t) {
+    if (t == len + 1) at_more += nruns;
+    if (t == len) at_len += nruns;
+    nruns += runs[t];
+  }
+  for (uint32_t i = 0, rec = 0; i < nr; ++i) {
+    const uint32_t l = i < more ? len + 1 : len;
+    run[i < more ? at_more + i : at_len + (i - more)] =
+        make_uint2((tid + rec) | l << 8 | (nr > 1 ? place + i : 0xffu) << 16 |
+                       (rec == 0 ? 1u << 31 : 0u),
+                   b);
+    rec += l;
+  }
+  __syncthreads();
+  for (uint32_t i = tid >> 2; i < nruns; i += 64) {
+    const uint2 t = run[i];
+    const size_t ch = ch0 + (t.x & 0xffu);
+    const uint32_t n = (t.x >> 8) & 0xffu, at = (t.x >> 16) & 0xffu;
+    const uint32_t* h = head + ch * XYTZ_WORDS;
+    fe29 acc = quad_ld((t.x >> 31 ? tail : head) + ch * XYTZ_WORDS);
+    fe w = ld_aos(h + XYTZ_WORDS, (int)q);
+    for (uint32_t j = 1; j < n; ++j) {
+      const fe29 r = f29_from_words(w);
+      w = ld_aos(h + (j + 1 < n ? j + 1 : j) * XYTZ_WORDS, (int)q);
+      acc = quad_add(acc, r);
+    }
+    if (at == 0xffu) {
+      quad_st(buckets + (size_t)t.y * XYTZ_WORDS, acc);
+    } else {
+#pragma unroll
+      for (int k = 0; k < NL29; ++k) part[at][q][k] = acc.v[k];
+    }
+  }
+  // fold a span's m runs into (m + 1) / 2 until one is left
+  const uint32_t quad = tid >> 2;
+  const uint2 t = quad < pairs ? pair[quad] : make_uint2(0u, 0u);
+  const uint32_t at = (t.x & 0xffu) + (t.x >> 16);
+  uint32_t m = (t.x >> 8) & 0xffu;
+  for (uint32_t left = most; left > 1; left = (left + 1) >> 1) {
+    __syncthreads();
+    const uint32_t half = (m + 1) >> 1;
+    if ((t.x >> 16) + half < m) {
+      fe29 l, r;
+#pragma unroll
+      for (int k = 0; k < NL29; ++k) {
+        l.v[k] = part[at][q][k];
+        r.v[k] = part[at + half][q][k];
+      }
+      l = quad_add(l, r);
+      if (half == 1) {
+        quad_st(buckets + (size_t)t.y * XYTZ_WORDS, l);
+      } else {
+#pragma unroll
+        for (int k = 0; k < NL29; ++k) part[at][q][k] = l.v[k];
+      }
+    }
+    m = half;
   }
 }
 
@@ -443,7 +516,7 @@ int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t s
     kernel<<<grid, 256, 0, st>>>(pl.one.xyu, segoff, bb, key, idx, total, g, buckets, head, tail);
   }
   ProfScope prof(PT_MERGE, st);
-  k_merge<<<grid_for(pl.chunks, 256), 256, 0, st>>>(key, offsets, total, bb, g, head, tail, buckets, list);
+  k_merge<<<grid_for(pl.chunks, MERGE_CHUNKS), 256, 0, st>>>(key, offsets, total, bb, g, head, tail, buckets, list);
   k_merge_long<<<(unsigned)std::min<size_t>(1024, pl.long_segs), 256, 0, st>>>(
       key, offsets, total, bb, g, head, tail, buckets, list);
   HIPCHK(hipGetLastError());

@@ -89,10 +89,18 @@ struct ProfScope {
 bool prof_kernel_events(int tag, hipStream_t st, hipEvent_t* a, hipEvent_t* b);
 void prof_kernel_record(int tag, hipEvent_t a, hipEvent_t b);
 
-// Digit sort geometry: partitions of uniformly spread digits hold about
-// SORT_PART_TARGET entries; pass 2 stages up to SORT_PART_CAP in LDS and
+// Digit sort geometry: partitions of uniformly spread digits hold at most
+// sort_part_target entries; pass 2 stages up to SORT_PART_CAP in LDS and
 // sorts larger partitions on many blocks, in items of SORT_BIG_ITEM entries.
-constexpr uint32_t SORT_PART_TARGET = 4096;
+// 8192 from jobs of more than 2^21 point records on: half the partitions, so a
+// tile's runs to each are twice as long (split digits, n = 2^22: sort 787 ->
+// 648 us; signed, 2^22: 627 -> 552).  4096 below, where the scatter is not what
+// counts and a window of fewer digit values (twice the entries a bucket) then
+// exceeds the stage (split digits, n = 2^20: 193 us, with 8192 197; n = 65536:
+// 73, 79).
+inline uint32_t sort_part_target(size_t max_n) {
+  return max_n > (size_t)1 << 21 ? 8192u : 4096u;
+}
 constexpr uint32_t SORT_PART_CAP = 10240;
 constexpr uint32_t SORT_BIG_ITEM = 4096;
 

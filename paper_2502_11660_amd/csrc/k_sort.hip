@@ -837,7 +837,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_add(uint32_t* __restrict_
 
 // Split of the bb bucket bits: enough high bits that a partition of uniformly
 // distributed digits of the largest job holds about max_n / 2^hi <=
-// SORT_PART_TARGET entries, at most 8 low bits (pass-2 histogram) and at most 12
+// sort_part_target entries, at most 8 low bits (pass-2 histogram) and at most 12
 // high bits (pass-1 histogram).  Also the tile grouping and the count-matrix
 // size.  A pass-1 block takes a group of tpb tiles with one histogram: tpb =
 // 2^hi / (32 x staged entry bytes) keeps about 256 bytes of staged entries
@@ -854,7 +854,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_add(uint32_t* __restrict_
 void sort_geometry(Plan& pl, const size_t* ns, uint32_t J, size_t mult) {
   const uint32_t bb = (uint32_t)pl.bb;
   uint32_t want = 0;
-  while (want < 12 && (pl.max_n >> want) > SORT_PART_TARGET) ++want;
+  while (want < 12 && (pl.max_n >> want) > sort_part_target(pl.max_n)) ++want;
   const uint32_t hi_min = bb > 8 ? bb - 8 : 0;
   uint32_t hi = std::max<uint32_t>(want, hi_min);
   hi = std::min<uint32_t>(hi, std::min<uint32_t>(bb, 12));

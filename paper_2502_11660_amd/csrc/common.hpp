@@ -103,6 +103,7 @@ inline uint32_t sort_part_target(size_t max_n) {
 }
 constexpr uint32_t SORT_PART_CAP = 10240;
 constexpr uint32_t SORT_BIG_ITEM = 4096;
+constexpr int SORT_COUNTERS = 3;  // cleared by each sort's first kernel
 
 // ---------------------------------------------------------------------------
 // jobs and workspace plans (msm_api.hip)
@@ -194,7 +195,7 @@ struct Plan {
   // byte offsets into the workspace
   size_t o_flags = 0, o_total = 0, o_offsets = 0, o_counts = 0, o_blocksums = 0, o_digits = 0,
          o_tmp = 0, o_key = 0, o_idx = 0, o_head = 0, o_tail = 0, o_buckets = 0, o_lvl0 = 0,
-         o_lvl1 = 0, o_wsum = 0, o_longlist = 0, o_big = 0, o_bigdesc = 0, o_bigcnt = 0, o_bigitem = 0, o_jobs = 0, o_segoff = 0, bytes = 0;
+         o_lvl1 = 0, o_wsum = 0, o_longlist = 0, o_counters = 0, o_bigdesc = 0, o_bigsum = 0, o_bigcnt = 0, o_bigitem = 0, o_jobs = 0, o_segoff = 0, bytes = 0;
 };
 
 int num_windows(int c, int encoding);
@@ -260,6 +261,5 @@ int launch_padd(const uint32_t* a, const uint32_t* b, uint32_t* out, uint32_t co
 int launch_prepare(const uint32_t* xy, const uint32_t* inf, uint32_t* xyu, uint32_t n,
                    uint32_t* status, bool endo, hipStream_t st);
 int launch_gen_points(const uint32_t* k, uint32_t* xy, uint32_t* inf, uint32_t n, hipStream_t st);
-int launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st);
 
 }  // namespace msm

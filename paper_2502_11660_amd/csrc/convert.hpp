@@ -473,15 +473,6 @@ __device__ __forceinline__ scalar256 ld_scalar_flag(const uint32_t* __restrict__
   return r;
 }
 
-// The same, reported through *flags.
-__device__ __forceinline__ scalar256 ld_scalar(const uint32_t* __restrict__ s, uint32_t i,
-                                               uint32_t* __restrict__ flags) {
-  uint32_t over = 0;
-  const scalar256 r = ld_scalar_flag(s, i, over);
-  if (over && flags) atomicOr(flags, MSM_FLAG_RANGE);
-  return r;
-}
-
 // c-bit digit starting at bit position pos (c <= 20, pos < 253)
 // Endomorphism split (optional, not in the paper): lambda = x0^2 - 1 with
 // lambda^2 + lambda + 1 = r; s = s1 lambda + s0 with 0 <= s0 < lambda and

@@ -315,12 +315,6 @@ __global__ void __launch_bounds__(256) k_gen_points(const uint32_t* __restrict__
   inf[i] = fin ? 0u : 1u;
 }
 
-__global__ void k_fill_u32(uint32_t* __restrict__ p, size_t n, uint32_t v) {
-  size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = v;
-}
-
 }  // namespace
 
 int launch_fe_mul(const uint32_t* a, const uint32_t* b, uint32_t* out, uint32_t count,
@@ -358,15 +352,6 @@ int launch_prepare(const uint32_t* xy, const uint32_t* inf, uint32_t* xyu, uint3
 
 int launch_gen_points(const uint32_t* k, uint32_t* xy, uint32_t* inf, uint32_t n, hipStream_t st) {
   k_gen_points<<<grid_for(n, 256), 256, 0, st>>>(k, xy, inf, n);
-  HIPCHK(hipGetLastError());
-  return MSM_OK;
-}
-
-int launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st) {
-  unsigned g = grid_for(n, 256);
-  if (g > 4096u) g = 4096u;
-  if (g == 0) g = 1;
-  k_fill_u32<<<g, 256, 0, st>>>(p, n, v);
   HIPCHK(hipGetLastError());
   return MSM_OK;
 }

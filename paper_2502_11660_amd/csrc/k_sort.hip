@@ -12,7 +12,11 @@
 // and writes the identity into every empty bucket.
 //
 // Small jobs take one kernel (k_small_sort).  Otherwise it is a two-pass
-// most-significant-digit counting sort with no global atomics:
+// most-significant-digit counting sort, with global atomics for large
+// partitions alone, in seven launches: each costs ~4.6 us however little it
+// does, and twelve of them (flags cleared, three scan passes, a plan and a scan
+// for large partitions on their own) took 72 us at n = 65536 with split digits
+// where these take 51, and 120 -> 88 us at n = 300007 signed:
 //   slice   digits of every window, stored segment-major (coalesced);
 //   pass 1  per tile of one segment, an LDS histogram of the bucket index's
 //           high bits; the (partition, tile) count matrix is scanned, and each
@@ -38,12 +42,35 @@ constexpr uint32_t TILE = SORT_TILE;  // entries per pass-1 tile
 constexpr uint32_t PER_THREAD = TILE / SORT_THREADS;
 constexpr uint32_t PART_CAP = SORT_PART_CAP;  // entries staged in LDS by pass 2
 constexpr unsigned BIG_GRID = 512;    // blocks of the large-partition kernels
+constexpr int SCAN_THREADS = 256;
+constexpr int SCAN_PER_THREAD = 16;
+constexpr int SCAN_ITEMS = SCAN_THREADS * SCAN_PER_THREAD;
 
 struct SortGeom {
   JobView jv;
   uint32_t W, S, bb, lo_bits, hi_bits;
   uint32_t tpb;  // pass-1 tiles per block: a block's group of tpb tiles shares one histogram
 };
+
+// The scanned count matrix: starts within each SCAN_ITEMS counts and the
+// starts of those groups, added as they are read (a pass over the matrix for
+// that was a launch of its own).
+struct Scanned {
+  const uint32_t* __restrict__ counts;
+  const uint32_t* __restrict__ sums;
+  const uint32_t* __restrict__ total;
+  size_t n;
+  __device__ __forceinline__ uint32_t operator[](size_t i) const {
+    return counts[i] + sums[i / SCAN_ITEMS];
+  }
+  // the start of element i <= n, n being the end of all
+  __device__ __forceinline__ uint32_t start(size_t i) const { return i < n ? (*this)[i] : *total; }
+};
+
+// Digit words: q | sign << 31, and in window 0's word RANGE_BIT when the
+// point's scalar is out of range; its job's status flag is set from that in
+// pass 1, after k_slice has cleared it.
+constexpr uint32_t RANGE_BIT = 1u << 30;
 
 // Staged entries between the passes (tmp): the index word (point index |
 // sign << 31) and the bucket key, 8 bytes; or, for jobs of at most 2^23
@@ -130,12 +157,21 @@ __device__ __forceinline__ uint32_t signed_digit(uint32_t v0, uint32_t& carry, i
 // images, interleaved: point 2i takes the digits of s0 of scalar i, point
 // 2i + 1 those of s1; one thread splits scalar i and writes both digit words
 // of each window (n and pt_off are even there).  N counts threads: points,
-// or point pairs with the split.
+// or point pairs with the split.  The first threads also clear the J status
+// flags and the counters of later passes.
 __global__ void __launch_bounds__(256) k_slice(JobView jv, uint32_t N, int c, int W, int encoding,
                                                uint32_t* __restrict__ digits,
-                                               uint32_t* __restrict__ flags) {
+                                               uint32_t* __restrict__ flags,
+                                               uint32_t* __restrict__ counters,
+                                               uint32_t* __restrict__ longlist) {
   const uint32_t gt = blockIdx.x * blockDim.x + threadIdx.x;
   if (gt >= N) return;
+  if (gt < jv.J) flags[gt] = 0u;  // J <= N
+  if (gt == 0) {
+    for (int i = 0; i < SORT_COUNTERS; ++i) counters[i] = 0u;
+    longlist[0] = 0u;  // of the accumulation's merges
+    longlist[1] = 0u;
+  }
   const uint32_t gi = encoding == MSM_DIGITS_GLV ? 2u * gt : gt;  // first point
   const uint32_t j = jv.tab ? find_job(jv.J, gi, [&](uint32_t k) { return jv.tab[k].pt_off; }) : 0u;
   const JobDesc d = jv.get(j);
@@ -143,7 +179,8 @@ __global__ void __launch_bounds__(256) k_slice(JobView jv, uint32_t N, int c, in
   uint32_t* out = digits + (size_t)W * d.pt_off + i;
   if (encoding == MSM_DIGITS_GLV) {
     scalar256 s0, s1;
-    glv_split(ld_scalar(d.scalars, i >> 1, flags + j), s0, s1);
+    uint32_t over = 0;
+    glv_split(ld_scalar_flag(d.scalars, i >> 1, over), s0, s1);
     uint2* out2 = reinterpret_cast<uint2*>(out);
     uint32_t carry0 = 0, carry1 = 0;
     for (int w = 0; w < W; ++w) {
@@ -151,17 +188,20 @@ __global__ void __launch_bounds__(256) k_slice(JobView jv, uint32_t N, int c, in
       uint2 q;
       q.x = signed_digit(digit_at(s0, w * c, c), carry0, c, top);
       q.y = signed_digit(digit_at(s1, w * c, c), carry1, c, top);
+      if (w == 0 && over) q.x |= RANGE_BIT;
       out2[(size_t)w * (d.n >> 1)] = q;
     }
     return;
   }
-  const scalar256 s = ld_scalar(d.scalars, i, flags + j);
-  if (encoding == MSM_DIGITS_UNSIGNED) {
-    for (int w = 0; w < W; ++w) out[(size_t)w * d.n] = digit_at(s, w * c, c);
-    return;
+  uint32_t over = 0, carry = 0;
+  const scalar256 s = ld_scalar_flag(d.scalars, i, over);
+  const bool is_signed = encoding != MSM_DIGITS_UNSIGNED;
+  for (int w = 0; w < W; ++w) {
+    const uint32_t v = digit_at(s, w * c, c);
+    uint32_t q = is_signed ? signed_digit(v, carry, c, w + 1 == W) : v;
+    if (w == 0 && over) q |= RANGE_BIT;
+    out[(size_t)w * d.n] = q;
   }
-  uint32_t carry = 0;
-  for (int w = 0; w < W; ++w) out[(size_t)w * d.n] = signed_digit(digit_at(s, w * c, c), carry, c, w + 1 == W);
 }
 
 // bucket index and the entry's index word of a digit word q != 0
@@ -173,7 +213,8 @@ __device__ __forceinline__ uint32_t bucket_of(uint32_t q, uint32_t off) {
 // after another into one LDS histogram)
 __global__ void __launch_bounds__(SORT_THREADS) k_part_count(SortGeom g, uint32_t off,
                                                              const uint32_t* __restrict__ digits,
-                                                             uint32_t* __restrict__ counts) {
+                                                             uint32_t* __restrict__ counts,
+                                                             uint32_t* __restrict__ flags) {
   __shared__ uint32_t hist[1u << 12];
   const TileRef t = tile_ref(g, blockIdx.x);
   const uint32_t H = 1u << g.hi_bits;
@@ -181,6 +222,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_part_count(SortGeom g, uint32_
   __syncthreads();
   const uint32_t g0 = t.tile * TILE * g.tpb, g1 = min(g0 + TILE * g.tpb, t.d.n);
   const uint32_t* dg = digits + (size_t)g.W * t.d.pt_off + (size_t)t.w * t.d.n;
+  uint32_t over = 0;
   for (uint32_t e0 = g0; e0 < g1; e0 += TILE) {
     const uint32_t e1 = min(e0 + TILE, g1);
     uint32_t dq[PER_THREAD];
@@ -191,10 +233,12 @@ __global__ void __launch_bounds__(SORT_THREADS) k_part_count(SortGeom g, uint32_
     }
 #pragma unroll
     for (uint32_t r = 0; r < PER_THREAD; ++r) {
-      const uint32_t q = e0 + r * SORT_THREADS + threadIdx.x < e1 ? dq[r] : 0u;
+      over |= dq[r];
+      const uint32_t q = e0 + r * SORT_THREADS + threadIdx.x < e1 ? dq[r] & ~RANGE_BIT : 0u;
       if (q) atomicAdd(&hist[bucket_of(q, off) >> g.lo_bits], 1u);
     }
   }
+  if (over & RANGE_BIT) atomicOr(flags + t.j, (uint32_t)MSM_FLAG_RANGE);
   __syncthreads();
   for (uint32_t b = threadIdx.x; b < H; b += SORT_THREADS)
     counts[count_index(g, t.d, t.w, b, t.tile)] = hist[b];
@@ -249,17 +293,8 @@ __device__ uint32_t lds_exclusive_scan(uint32_t* v, uint32_t n) {
 template <bool PK>
 __global__ void __launch_bounds__(SORT_THREADS) k_part_scatter(SortGeom g, uint32_t off,
                                                                const uint32_t* __restrict__ digits,
-                                                               const uint32_t* __restrict__ scanned,
-                                                               typename TmpEnt<PK>::T* __restrict__ tmp,
-                                                               uint32_t* __restrict__ clear0,
-                                                               uint32_t* __restrict__ clear1) {
-  // list counters of later passes start at zero (the large-partition list of
-  // pass 2 and the long-merge list of the accumulation)
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    clear0[0] = 0u;
-    clear1[0] = 0u;
-    clear1[1] = 0u;
-  }
+                                                               Scanned scanned,
+                                                               typename TmpEnt<PK>::T* __restrict__ tmp) {
   // dynamic LDS, sized by the launch for H = 2^hi_bits partitions: the tile
   // stage, then per partition its global start and its local count / start
   extern __shared__ uint2 scatter_lds[];
@@ -289,7 +324,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_part_scatter(SortGeom g, uint3
 #pragma unroll
     for (uint32_t r = 0; r < PER_THREAD; ++r) {
       const uint32_t e = e0 + r * SORT_THREADS + threadIdx.x;
-      const uint32_t q = e < e1 ? dq[r] : 0u;
+      const uint32_t q = e < e1 ? dq[r] & ~RANGE_BIT : 0u;
       part[r] = H;  // no entry
       rank[r] = 0;
       ent[r] = make_uint2(0u, 0u);
@@ -324,15 +359,13 @@ __global__ void __launch_bounds__(SORT_THREADS) k_part_scatter(SortGeom g, uint3
 
 // partition p's range [start, start + size) in tmp; partitions are contiguous
 // in the count matrix, the next one starting tps entries later
-__device__ __forceinline__ void part_range(const SortGeom& g, const uint32_t* __restrict__ scanned,
-                                           uint32_t total, size_t ncounts, uint32_t p,
+__device__ __forceinline__ void part_range(const SortGeom& g, const Scanned& scanned, uint32_t p,
                                            uint32_t& start, uint32_t& size) {
   const uint32_t s = p >> g.hi_bits, hi = p & ((1u << g.hi_bits) - 1);
   const JobDesc d = g.jv.get(s / g.W);
   const size_t ci = count_index(g, d, s % g.W, hi, 0);
   start = scanned[ci];
-  const uint32_t end = (ci + d.tps < ncounts) ? scanned[ci + d.tps] : total;
-  size = end - start;
+  size = scanned.start(ci + d.tps) - start;
 }
 
 // first bucket of partition p
@@ -400,31 +433,52 @@ __device__ __forceinline__ void part_sort_rows(const SortGeom& g, uint32_t p, ui
   }
 }
 
+// The large partitions' list.  count[0] partitions of count[1] items; an item
+// is BIG_CH consecutive entries of one partition.  desc[4b ..] = id, start,
+// size and first item of partition b; item_of[item] its partition; cnt[item *
+// 256 + lo] the item's count of bucket lo; sum[b * 512 + lo] the partition's,
+// and 256 words on, how many of them have their places.
+constexpr uint32_t BIG_CH = SORT_BIG_ITEM;
+struct BigList {
+  uint32_t *count, *desc, *item_of, *cnt, *sum;
+};
+
 // Partitions of up to SHORT_ROWS rows (evenly spread digits) take the short
 // form, larger ones up to PART_CAP entries the long one.  A partition of more
-// than PART_CAP entries (skewed digits) is only listed in big[] here; the
-// k_big_* kernels sort it with many blocks.
+// than PART_CAP entries (skewed digits) is only listed here; the k_big_*
+// kernels sort it with many blocks.
 constexpr uint32_t SHORT_ROWS = 20;
 
 template <bool PK>
 __global__ void __launch_bounds__(SORT_THREADS) k_part_sort(
-    SortGeom g, const uint32_t* __restrict__ scanned, const uint32_t* __restrict__ total_p,
-    size_t ncounts, const typename TmpEnt<PK>::T* __restrict__ tmp, uint32_t* __restrict__ key,
-    uint32_t* __restrict__ idx, uint32_t* __restrict__ offsets, uint32_t* __restrict__ buckets,
-    uint32_t* __restrict__ big) {
+    SortGeom g, Scanned scanned, const typename TmpEnt<PK>::T* __restrict__ tmp,
+    uint32_t* __restrict__ key, uint32_t* __restrict__ idx, uint32_t* __restrict__ offsets,
+    uint32_t* __restrict__ buckets, BigList big) {
   __shared__ uint32_t out_idx[PART_CAP];  // index words in bucket order
   __shared__ uint8_t out_lo[PART_CAP];    // their low bucket bits
   __shared__ uint32_t hist[256], cur[256];
   constexpr uint32_t ROWS = (PART_CAP + SORT_THREADS - 1) / SORT_THREADS;
   const uint32_t p = blockIdx.x;
-  const uint32_t total = *total_p;
   uint32_t start, size;
-  part_range(g, scanned, total, ncounts, p, start, size);
+  part_range(g, scanned, p, start, size);
   // a segment's last partition ends it
   if (((p + 1) & ((1u << g.hi_bits) - 1)) == 0 && threadIdx.x == 0)
     offsets[(size_t)((p >> g.hi_bits) + 1) * ((1u << g.bb) + 1) - 1] = start + size;
   if (size > PART_CAP) {
-    if (threadIdx.x == 0) big[1 + atomicAdd(&big[0], 1u)] = p;
+    const uint32_t items = (size + BIG_CH - 1) / BIG_CH;
+    if (threadIdx.x == 0) {
+      const uint32_t b = atomicAdd(&big.count[0], 1u), first = atomicAdd(&big.count[1], items);
+      uint32_t* d = big.desc + 4 * b;
+      d[0] = p;
+      d[1] = start;
+      d[2] = size;
+      d[3] = first;
+      cur[0] = b;
+      cur[1] = first;
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < items; k += SORT_THREADS) big.item_of[cur[1] + k] = cur[0];
+    for (uint32_t k = threadIdx.x; k < 512; k += SORT_THREADS) big.sum[512 * cur[0] + k] = 0u;
     return;
   }
   if (size <= SHORT_ROWS * SORT_THREADS)
@@ -435,65 +489,17 @@ __global__ void __launch_bounds__(SORT_THREADS) k_part_sort(
                              hist, cur);
 }
 
-// Large partitions, sorted by many blocks.  big[0] = their count n, big[1..n]
-// their ids.  desc[4b .. 4b + 3] = id, start, size and first item of large
-// partition b, desc[4n] = the item count; an item is BIG_CH consecutive
-// entries of one large partition, item_of[item] its partition.  cnt[item * 256 + lo] holds the item's count
-// of bucket lo, then its cursor (the bucket's start plus the entries of
-// earlier items).
-constexpr uint32_t BIG_CH = SORT_BIG_ITEM;
-
-
-// numbering of the items (one block); item_of[item] = its large partition
-__global__ void __launch_bounds__(SORT_THREADS) k_big_plan(
-    SortGeom g, const uint32_t* __restrict__ scanned, const uint32_t* __restrict__ total_p,
-    size_t ncounts, const uint32_t* __restrict__ big, uint32_t* __restrict__ desc,
-    uint32_t* __restrict__ item_of) {
-  __shared__ uint32_t chunks[16 * SORT_THREADS];
-  const uint32_t nbig = big[0], total = *total_p;
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base < nbig; base += 16 * SORT_THREADS) {
-    const uint32_t n = min(16u * SORT_THREADS, nbig - base);
-    for (uint32_t i = threadIdx.x; i < n; i += SORT_THREADS) {
-      const uint32_t p = big[1 + base + i];
-      uint32_t start, size;
-      part_range(g, scanned, total, ncounts, p, start, size);
-      desc[4 * (base + i) + 0] = p;
-      desc[4 * (base + i) + 1] = start;
-      desc[4 * (base + i) + 2] = size;
-      chunks[i] = (size + BIG_CH - 1) / BIG_CH;
-    }
-    __syncthreads();
-    const uint32_t tot = lds_exclusive_scan(chunks, n);
-    for (uint32_t i = threadIdx.x; i < n; i += SORT_THREADS) {
-      const uint32_t first = carry + chunks[i];
-      desc[4 * (base + i) + 3] = first;
-      const uint32_t items = (desc[4 * (base + i) + 2] + BIG_CH - 1) / BIG_CH;
-      for (uint32_t k = 0; k < items; ++k) item_of[first + k] = base + i;
-    }
-    carry += tot;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) desc[4 * nbig] = carry;
-}
-
-// per item: histogram of the low bucket bits
+// Large partitions, per item: histogram of the low bucket bits
 template <bool PK>
-__global__ void __launch_bounds__(SORT_THREADS) k_big_count(SortGeom g,
-                                                            const uint32_t* __restrict__ big,
-                                                            const uint32_t* __restrict__ desc,
-                                                            const uint32_t* __restrict__ item_of,
-                                                            const typename TmpEnt<PK>::T* __restrict__ tmp,
-                                                            uint32_t* __restrict__ cnt) {
+__global__ void __launch_bounds__(SORT_THREADS) k_big_count(
+    SortGeom g, BigList big, const typename TmpEnt<PK>::T* __restrict__ tmp) {
   __shared__ uint32_t hist[256];
-  const uint32_t nbig = big[0];
-  if (nbig == 0) return;
-  const uint32_t items = desc[4 * nbig], L = 1u << g.lo_bits;
+  const uint32_t items = big.count[1], L = 1u << g.lo_bits, lo = threadIdx.x;
   for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-    const uint32_t b = item_of[item];
-    const uint32_t start = desc[4 * b + 1], size = desc[4 * b + 2];
-    const uint32_t e0 = (item - desc[4 * b + 3]) * BIG_CH, e1 = min(e0 + BIG_CH, size);
-    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+    const uint32_t b = big.item_of[item];
+    const uint32_t start = big.desc[4 * b + 1], size = big.desc[4 * b + 2];
+    const uint32_t e0 = (item - big.desc[4 * b + 3]) * BIG_CH, e1 = min(e0 + BIG_CH, size);
+    hist[lo] = 0;
     __syncthreads();
     constexpr uint32_t PER = BIG_CH / SORT_THREADS;
     uint32_t kv[PER];
@@ -506,67 +512,29 @@ __global__ void __launch_bounds__(SORT_THREADS) k_big_count(SortGeom g,
     for (uint32_t r = 0; r < PER; ++r)
       if (e0 + r * SORT_THREADS + threadIdx.x < e1) atomicAdd(&hist[kv[r]], 1u);
     __syncthreads();
-    for (uint32_t lo = threadIdx.x; lo < L; lo += SORT_THREADS)
-      cnt[(size_t)item * 256 + lo] = hist[lo];
+    const uint32_t n = hist[lo];
+    big.cnt[(size_t)item * 256 + lo] = n;
+    if (n) atomicAdd(&big.sum[512 * b + lo], n);
     __syncthreads();
   }
 }
 
-// per large partition: counts -> cursors, bucket offsets, identities
-__global__ void __launch_bounds__(SORT_THREADS) k_big_scan(SortGeom g,
-                                                           const uint32_t* __restrict__ big,
-                                                           const uint32_t* __restrict__ desc,
-                                                           uint32_t* __restrict__ cnt,
-                                                           uint32_t* __restrict__ offsets,
-                                                           uint32_t* __restrict__ buckets) {
-  __shared__ uint32_t bstart[256];
-  const uint32_t nbig = big[0], L = 1u << g.lo_bits, lo = threadIdx.x;
-  for (uint32_t b = blockIdx.x; b < nbig; b += gridDim.x) {
-    const uint32_t p = desc[4 * b], start = desc[4 * b + 1], size = desc[4 * b + 2];
-    const uint32_t it0 = desc[4 * b + 3], nit = (size + BIG_CH - 1) / BIG_CH;
-    uint32_t run = 0;
-    if (lo < L) {
-      for (uint32_t it = 0; it < nit; ++it) {
-        uint32_t* c = cnt + (size_t)(it0 + it) * 256 + lo;
-        const uint32_t v = *c;
-        *c = run;
-        run += v;
-      }
-    }
-    if (lo < 256) bstart[lo] = run;
-    __syncthreads();
-    lds_exclusive_scan256(bstart, L);
-    const uint32_t bucket0 = part_bucket0(g, p);
-    if (lo < L) {
-      offsets[offset_index(bucket0, g.bb) + lo] = start + bstart[lo];
-      if (run == 0 && buckets)
-        st_xytz(buckets + (size_t)(bucket0 + lo) * XYTZ_WORDS, pt_identity());
-      for (uint32_t it = 0; it < nit; ++it) cnt[(size_t)(it0 + it) * 256 + lo] += bstart[lo];
-    }
-    __syncthreads();
-  }
-}
-
-// per item: place its entries at the cursors
+// Per item: reserves its entries' places in the partition's buckets and fills
+// them (the order of a bucket's entries is free); the partition's first item
+// also writes the bucket offsets and the empty buckets' identities.
 template <bool PK>
-__global__ void __launch_bounds__(SORT_THREADS) k_big_scatter(SortGeom g,
-                                                              const uint32_t* __restrict__ big,
-                                                              const uint32_t* __restrict__ desc,
-                                                              const uint32_t* __restrict__ item_of,
-                                                              const uint32_t* __restrict__ cnt,
-                                                              const typename TmpEnt<PK>::T* __restrict__ tmp,
-                                                              uint32_t* __restrict__ key,
-                                                              uint32_t* __restrict__ idx) {
+__global__ void __launch_bounds__(SORT_THREADS) k_big_scatter(
+    SortGeom g, BigList big, const typename TmpEnt<PK>::T* __restrict__ tmp,
+    uint32_t* __restrict__ key, uint32_t* __restrict__ idx, uint32_t* __restrict__ offsets,
+    uint32_t* __restrict__ buckets) {
   __shared__ uint32_t cur[256];
-  const uint32_t nbig = big[0];
-  if (nbig == 0) return;
-  const uint32_t items = desc[4 * nbig], L = 1u << g.lo_bits;
+  const uint32_t items = big.count[1], L = 1u << g.lo_bits, lo = threadIdx.x;
   for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-    const uint32_t b = item_of[item];
-    const uint32_t p = desc[4 * b], start = desc[4 * b + 1], size = desc[4 * b + 2];
-    const uint32_t e0 = (item - desc[4 * b + 3]) * BIG_CH, e1 = min(e0 + BIG_CH, size);
+    const uint32_t b = big.item_of[item];
+    const uint32_t p = big.desc[4 * b], start = big.desc[4 * b + 1], size = big.desc[4 * b + 2];
+    const uint32_t it0 = big.desc[4 * b + 3];
+    const uint32_t e0 = (item - it0) * BIG_CH, e1 = min(e0 + BIG_CH, size);
     const uint32_t bucket0 = part_bucket0(g, p);
-    for (uint32_t lo = threadIdx.x; lo < L; lo += SORT_THREADS) cur[lo] = cnt[(size_t)item * 256 + lo];
     constexpr uint32_t PER = BIG_CH / SORT_THREADS;
     typename TmpEnt<PK>::T ev[PER];
 #pragma unroll
@@ -574,13 +542,25 @@ __global__ void __launch_bounds__(SORT_THREADS) k_big_scatter(SortGeom g,
       const uint32_t k = e0 + r * SORT_THREADS + threadIdx.x;
       ev[r] = tmp[start + (k < e1 ? k : e1 - 1)];
     }
+    const uint32_t n = big.cnt[(size_t)item * 256 + lo], all = big.sum[512 * b + lo];
+    const uint32_t before = n ? atomicAdd(&big.sum[512 * b + 256 + lo], n) : 0u;
+    cur[lo] = all;
+    __syncthreads();
+    lds_exclusive_scan256(cur, 256);  // (counts from L on are 0)
+    const uint32_t first = start + cur[lo];
+    if (item == it0 && lo < L) {
+      offsets[offset_index(bucket0, g.bb) + lo] = first;
+      if (all == 0 && buckets)
+        st_xytz(buckets + (size_t)(bucket0 + lo) * XYTZ_WORDS, pt_identity());
+    }
+    cur[lo] = first + before;
     __syncthreads();
 #pragma unroll
     for (uint32_t r = 0; r < PER; ++r) {
       if (e0 + r * SORT_THREADS + threadIdx.x < e1) {
-        const uint32_t lo = TmpEnt<PK>::lo(ev[r], L);
-        const uint32_t pos = start + atomicAdd(&cur[lo], 1u);
-        key[pos] = bucket0 + lo;
+        const uint32_t m = TmpEnt<PK>::lo(ev[r], L);
+        const uint32_t pos = atomicAdd(&cur[m], 1u);
+        key[pos] = bucket0 + m;
         idx[pos] = TmpEnt<PK>::idx(ev[r]);
       }
     }
@@ -729,10 +709,7 @@ __global__ void __launch_bounds__(1024) k_small_sort(SortGeom g, int c, int enco
   }
 }
 
-// Exclusive scan in three passes, SCAN_ITEMS elements per block.
-constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_PER_THREAD = 16;
-constexpr int SCAN_ITEMS = SCAN_THREADS * SCAN_PER_THREAD;
+// Exclusive scan of the count matrix, SCAN_ITEMS elements per block.
 
 __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t& excl) {
   __shared__ uint32_t wsum[SCAN_THREADS / 64];
@@ -757,8 +734,13 @@ __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t& excl) {
   return total;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_block(uint32_t* __restrict__ data, size_t n,
-                                                             uint32_t* __restrict__ blocksums) {
+// Starts within each block's elements; the block that finishes last scans the
+// blocks' sums.
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan(uint32_t* __restrict__ data, size_t n,
+                                                       uint32_t* __restrict__ blocksums,
+                                                       uint32_t* __restrict__ total_out,
+                                                       uint32_t* __restrict__ done) {
+  __shared__ uint32_t last;
   size_t base = (size_t)blockIdx.x * SCAN_ITEMS + (size_t)threadIdx.x * SCAN_PER_THREAD;
   uint32_t v[SCAN_PER_THREAD];
   // a thread's 16 words are 64-byte aligned: 16-byte loads when all in range
@@ -798,39 +780,33 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_block(uint32_t* __restric
     for (int j = 0; j < SCAN_PER_THREAD; ++j)
       if (base + j < n) data[base + j] = v[j];
   }
-  if (threadIdx.x == 0) blocksums[blockIdx.x] = total;
-}
-
-// one block: exclusive scan of nb <= SCAN_ITEMS block sums; grand total out
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_top(uint32_t* __restrict__ blocksums,
-                                                           uint32_t nb,
-                                                           uint32_t* __restrict__ total_out) {
-  size_t base = (size_t)threadIdx.x * SCAN_PER_THREAD;
-  uint32_t v[SCAN_PER_THREAD];
-  uint32_t sum = 0;
+  if (threadIdx.x == 0) {
+    // the sum alone has to be seen by the last block: an exchange, complete
+    // when its result is there, costs less than a fence over all that the
+    // block wrote
+    uint32_t old = atomicExch(&blocksums[blockIdx.x], total);
+    asm volatile("" : "+v"(old) : : "memory");
+    last = atomicAdd(done, 1u) + 1 == gridDim.x ? 1u : 0u;
+  }
+  __syncthreads();
+  if (last == 0) return;
+  const uint32_t nb = gridDim.x;  // <= SCAN_ITEMS
+  sum = 0;
 #pragma unroll
   for (int j = 0; j < SCAN_PER_THREAD; ++j) {
-    v[j] = (base + j < nb) ? blocksums[base + j] : 0u;
+    const uint32_t i = threadIdx.x * SCAN_PER_THREAD + j;
+    v[j] = i < nb ? __hip_atomic_load(&blocksums[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                  : 0u;
     sum += v[j];
   }
-  uint32_t excl;
-  uint32_t total = block_exclusive_scan(sum, excl);
+  total = block_exclusive_scan(sum, excl);
 #pragma unroll
   for (int j = 0; j < SCAN_PER_THREAD; ++j) {
-    if (base + j < nb) blocksums[base + j] = excl;
+    const uint32_t i = threadIdx.x * SCAN_PER_THREAD + j;
+    if (i < nb) blocksums[i] = excl;
     excl += v[j];
   }
   if (threadIdx.x == 0) *total_out = total;
-}
-
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_add(uint32_t* __restrict__ data, size_t n,
-                                                           const uint32_t* __restrict__ blocksums) {
-  size_t base = (size_t)blockIdx.x * SCAN_ITEMS;
-  uint32_t add = blocksums[blockIdx.x];
-  for (int j = threadIdx.x; j < SCAN_ITEMS; j += SCAN_THREADS) {
-    size_t i = base + j;
-    if (i < n) data[i] += add;
-  }
 }
 
 }  // namespace
@@ -882,28 +858,23 @@ void sort_geometry(Plan& pl, const size_t* ns, uint32_t J, size_t mult) {
 
 namespace {
 struct SortBufs {
-  uint32_t *digits, *counts, *total, *offsets, *key, *idx, *buckets;
-  uint32_t *big, *bigdesc, *bigcnt, *bigitem, *longlist;
+  uint32_t *digits, *offsets, *key, *idx, *buckets;
 };
 
 // pass-1 scatter, pass 2 and the many-block sort, on staged entries of
 // either form
 template <bool PK>
-void sort_passes(const Plan& pl, const SortGeom& g, uint32_t off, const SortBufs& b,
-                 typename TmpEnt<PK>::T* tmp, size_t scatter_lds, hipStream_t st) {
-  k_part_scatter<PK><<<(unsigned)pl.tiles, SORT_THREADS, scatter_lds, st>>>(
-      g, off, b.digits, b.counts, tmp, b.big, b.longlist);
+void sort_passes(const Plan& pl, const SortGeom& g, uint32_t off, const Scanned& sc,
+                 const SortBufs& b, const BigList& big, typename TmpEnt<PK>::T* tmp,
+                 size_t scatter_lds, hipStream_t st) {
+  k_part_scatter<PK><<<(unsigned)pl.tiles, SORT_THREADS, scatter_lds, st>>>(g, off, b.digits, sc,
+                                                                          tmp);
   k_part_sort<PK><<<(unsigned)(pl.S << pl.hi_bits), SORT_THREADS, 0, st>>>(
-      g, b.counts, b.total, pl.ncounts, tmp, b.key, b.idx, b.offsets, b.buckets, b.big);
+      g, sc, tmp, b.key, b.idx, b.offsets, b.buckets, big);
   // large partitions (none for evenly spread digits: these return at once)
-  k_big_plan<<<1, SORT_THREADS, 0, st>>>(g, b.counts, b.total, pl.ncounts, b.big, b.bigdesc,
-                                         b.bigitem);
-  k_big_count<PK><<<BIG_GRID, SORT_THREADS, 0, st>>>(g, b.big, b.bigdesc, b.bigitem, tmp,
-                                                     b.bigcnt);
-  k_big_scan<<<BIG_GRID, SORT_THREADS, 0, st>>>(g, b.big, b.bigdesc, b.bigcnt, b.offsets,
-                                                b.buckets);
-  k_big_scatter<PK><<<BIG_GRID, SORT_THREADS, 0, st>>>(g, b.big, b.bigdesc, b.bigitem, b.bigcnt,
-                                                       tmp, b.key, b.idx);
+  k_big_count<PK><<<BIG_GRID, SORT_THREADS, 0, st>>>(g, big, tmp);
+  k_big_scatter<PK><<<BIG_GRID, SORT_THREADS, 0, st>>>(g, big, tmp, b.key, b.idx, b.offsets,
+                                                       b.buckets);
 }
 }  // namespace
 
@@ -944,24 +915,24 @@ int launch_sort(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st) {
   }
   if (pl.lo_bits > 8 || pl.hi_bits > 12 || pl.nb > (size_t)SCAN_ITEMS) return MSM_EINVAL;
 
-  int rc;
-  if ((rc = launch_fill_u32(flags, pl.J, 0u, st)) != MSM_OK) return rc;
+  // counters: finished scan blocks, then the large-partition list's two
+  uint32_t* counters = ws_at<uint32_t>(ws, pl.o_counters);
   const size_t slice_threads = pl.encoding == MSM_DIGITS_GLV ? pl.N / 2 : pl.N;
   k_slice<<<grid_for(slice_threads, 256), 256, 0, st>>>(g.jv, (uint32_t)slice_threads, pl.c, pl.W,
-                                                        pl.encoding, digits, flags);
-  k_part_count<<<(unsigned)pl.tiles, SORT_THREADS, 0, st>>>(g, off, digits, counts);
-  k_scan_block<<<(unsigned)pl.nb, SCAN_THREADS, 0, st>>>(counts, pl.ncounts, blocksums);
-  k_scan_top<<<1, SCAN_THREADS, 0, st>>>(blocksums, (uint32_t)pl.nb, total);
-  k_scan_add<<<(unsigned)pl.nb, SCAN_THREADS, 0, st>>>(counts, pl.ncounts, blocksums);
+                                                        pl.encoding, digits, flags, counters,
+                                                        ws_at<uint32_t>(ws, pl.o_longlist));
+  k_part_count<<<(unsigned)pl.tiles, SORT_THREADS, 0, st>>>(g, off, digits, counts, flags);
+  k_scan<<<(unsigned)pl.nb, SCAN_THREADS, 0, st>>>(counts, pl.ncounts, blocksums, total, counters);
   const size_t scatter_lds = TILE * sizeof(uint2) + 2 * ((size_t)4 << pl.hi_bits);
-  SortBufs sb{digits, counts, total, offsets, key, idx, buckets,
-              ws_at<uint32_t>(ws, pl.o_big), ws_at<uint32_t>(ws, pl.o_bigdesc),
-              ws_at<uint32_t>(ws, pl.o_bigcnt), ws_at<uint32_t>(ws, pl.o_bigitem),
-              ws_at<uint32_t>(ws, pl.o_longlist)};
+  const Scanned sc{counts, blocksums, total, pl.ncounts};
+  const SortBufs sb{digits, offsets, key, idx, buckets};
+  const BigList big{counters + 1, ws_at<uint32_t>(ws, pl.o_bigdesc),
+                    ws_at<uint32_t>(ws, pl.o_bigitem), ws_at<uint32_t>(ws, pl.o_bigcnt),
+                    ws_at<uint32_t>(ws, pl.o_bigsum)};
   if (pl.tmp_packed)
-    sort_passes<true>(pl, g, off, sb, ws_at<uint32_t>(ws, pl.o_tmp), scatter_lds, st);
+    sort_passes<true>(pl, g, off, sc, sb, big, ws_at<uint32_t>(ws, pl.o_tmp), scatter_lds, st);
   else
-    sort_passes<false>(pl, g, off, sb, ws_at<uint2>(ws, pl.o_tmp), scatter_lds, st);
+    sort_passes<false>(pl, g, off, sc, sb, big, ws_at<uint2>(ws, pl.o_tmp), scatter_lds, st);
   HIPCHK(hipGetLastError());
   return MSM_OK;
 }

@@ -228,8 +228,9 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
   // there are at most NW / SORT_PART_CAP of them, and NW / SORT_BIG_ITEM +
   // that many items
   const size_t nbig_max = pl.NW / SORT_PART_CAP + 1;
-  pl.o_big = take((nbig_max + 1) * 4);
-  pl.o_bigdesc = take((nbig_max + 1) * 16);
+  pl.o_counters = take(SORT_COUNTERS * 4);
+  pl.o_bigdesc = take(nbig_max * 16);
+  pl.o_bigsum = take(nbig_max * 512 * 4);
   pl.o_bigcnt = take((pl.NW / SORT_BIG_ITEM + nbig_max + 1) * 256 * 4);
   pl.o_bigitem = take((pl.NW / SORT_BIG_ITEM + nbig_max + 1) * 4);
   // buckets, then the tree levels ping-pong between lvl0 (level 0's M

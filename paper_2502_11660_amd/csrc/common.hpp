@@ -142,8 +142,11 @@ struct AccumGeom {
   uint32_t fixed;  // a schedule's chunk length (0: from the entries)
   uint32_t quad;   // a unit is a quad
 };
-// Quads up to 2^18 digit slots: above, lanes of four entries are as fast.
-constexpr size_t ACCUM_QUAD_MAX = (size_t)1 << 18;
+// Quads up to 2^19 digit slots: a quarter of the lanes' chunks, and so of the
+// split buckets, for 1.4 times the instructions (split digits, c = 8: n = 10000 325
+// us on lanes, 265 on quads, n = 16384 328, 295).  Above, lanes of more than
+// eight entries are as fast (n = 24000, c = 13: 349, 353; n = 50000 402, 424).
+constexpr size_t ACCUM_QUAD_MAX = (size_t)1 << 19;
 // Units for E entries.  Lanes: a lone wave a SIMD leaves 13% of its issue slots
 // empty, and each further wave doubles or halves again the split buckets to
 // merge.  One wave up to 16 entries a lane (n = 40000, split digits, 13: 442 us,

@@ -33,3 +33,19 @@ def test_bucket_sizes(sizes, many):
     got, flags = api.decode_result(api.to_host(res))
     assert flags == 0
     assert got == msm.closed_form(s, [inputs.words_to_int(r) for r in kw])
+
+
+@pytest.mark.parametrize("n", [16384, 16385])
+@pytest.mark.parametrize("sizes", [list(range(1, 60)), [17, 2, 18, 19, 3, 20, 21] * 8,
+                                   [505, 250, 251, 252, 253], [4 * h + 2 for h in range(59, 67)]])
+def test_bucket_sizes_on_both_sides_of_the_quad_limit(sizes, n):
+    """2^19 digit slots at 32 windows: quads, one point more: lanes."""
+    s = np.repeat(np.arange(1, len(sizes) + 1), sizes).tolist()
+    s += [0] * (n - len(s))
+    kw = inputs.nonzero_scalars_mod_r(60 + len(sizes), n, stream=1)
+    xy, inf = api.gen_points(api.to_device(kw), n)
+    xyu, _ = api.points_prepare(xy, n, inf=inf)
+    res = api.msm_run(xyu, api.to_device(inputs.ints_to_words(s, 8)), n, 8, UNSIGNED)
+    got, flags = api.decode_result(api.to_host(res))
+    assert flags == 0
+    assert got == msm.closed_form(s, [inputs.words_to_int(r) for r in kw])

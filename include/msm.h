@@ -208,10 +208,13 @@ int msm_window_bits(int c, int encoding);
 size_t msm_workspace_bytes(size_t n, int c, int encoding);
 
 /* Window width msm_run picks for n points when called with c = 0 and signed
- * or unsigned digits (a cost model: n W entries plus the aggregation of W
- * windows of buckets, widths 4..20).  With the endomorphism split, c = 0
- * picks from a model of its own (2n W entries of W = ceil(127 / c') windows):
- * c' = 16 up to n ~ 2^21 and 19 (seven windows) above. */
+ * digits (a cost model over widths 4..20: entries, buckets, and the latencies
+ * that a single MSM waits for; the same model picks for the other encodings:
+ * with the endomorphism split c' = 8 up to n ~ 2^14, 13 up to 2^17, 16 up to
+ * 2^21 and 19, seven windows, above).  msm_run with unsigned digits and c = 0
+ * also takes a workspace sized for this width, and then runs at it if its own
+ * choice needs more.  Among jobs that run together (a batch, a server with
+ * several streams) latencies count for less, and c = 0 picks accordingly. */
 int msm_default_window(size_t n);
 
 /* Bucket accumulation (Sec. II-C), digits of c' = msm_window_bits(c,
@@ -234,8 +237,7 @@ int msm_bucket_accumulate(const uint32_t* xyu, const uint32_t* scalars, size_t n
                           void* stream);
 
 /* Full MSM: result = sum_i s_i P_i (Sec. II-C), Pippenger with window width
- * c (c = 0 picks msm_default_window(n), or the split digits' own choice)
- * and the given digit encoding.
+ * c (c = 0: see msm_default_window) and the given digit encoding.
  * result: MSM_RESULT_WORDS device words: x[12], y[12] (Weierstrass affine,
  * ordinary form, canonical), inf (1 if the sum is the point at infinity, then
  * x = y = 0), flags (MSM_FLAG_RANGE).  Other arguments as for
@@ -251,7 +253,7 @@ int msm_run(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int e
  * the caller passes inputs and the result buffer as for msm_run.  It fits n
  * up to 2^16 points at the default width in every encoding
  * (msm_workspace_bytes(n, c, encoding) must not exceed
- * MSM_NOALLOC_SCRATCH_BYTES).  Every call on a GPU
+ * MSM_NOALLOC_SCRATCH_BYTES; c = 0 picks among the widths that fit).  Every call on a GPU
  * shares that GPU's array: calls whose work overlaps on one GPU (on
  * different streams, or from several threads) race and must be ordered by
  * the caller; each call initialises what it reads of the array.  No timing
@@ -270,7 +272,7 @@ int msm_run_noalloc(const uint32_t* xyu, const uint32_t* scalars, size_t n, int 
  *
  * msm_job: device pointers owned by the caller (prepared points, scalars,
  * MSM_RESULT_WORDS result words), n >= 1 points, window width c (0 = the
- * choice of msm_run with c = 0), and the schedule (0 = the default for
+ * choice for one of njobs jobs), and the schedule (0 = the default for
  * each): chunk, the digit entries one lane (or, in small classes, four
  * lanes) sums in bucket accumulation (default: enough entries that one
  * resident round of lanes covers the class; every value is rounded up to a
@@ -327,7 +329,8 @@ int msm_batch_destroy(msm_batch* batch);
  *   priority; every request uses the given digit encoding.  *out receives the
  *   handle (host memory owned by the library).
  * msm_server_submit: queues one MSM (job as for msm_batch_create; c = 0
- *   picks as msm_run does).  Its workspace (msm_workspace_bytes) is its
+ *   picks for one of `streams` jobs, and among the widths that fit the arena
+ *   if that pick does not).  Its workspace at that width is its
  *   footprint: it is admitted -- launched on the stream with the fewest
  *   requests in flight -- as soon as that much of the arena is free and no
  *   earlier request is still waiting (FIFO).  While fewer than three

@@ -204,7 +204,11 @@ struct Plan {
 int num_windows(int c, int encoding);
 int window_bits(int c, int encoding);
 int default_window(size_t n);                     // signed-digit model (msm_default_window)
-int default_window_for(size_t n, int encoding);   // the width c = 0 picks for an encoding
+// the width c = 0 picks for an MSM of an encoding that is one of `jobs` run
+// together, among those whose workspace is within `limit` bytes (0: any)
+int default_window_for(size_t n, int encoding, size_t jobs = 1, size_t limit = 0);
+// work of `jobs` MSMs of n points in all at width c, in digit entries
+double window_work(double n, double jobs, int c, int encoding);
 // schedule of a plan (0 = default for each; msm_job's chunk, tree_quad,
 // tree_wide)
 struct Schedule {

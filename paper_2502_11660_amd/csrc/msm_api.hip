@@ -109,45 +109,6 @@ int window_bits(int c, int encoding) {
   return (bits + W - 1) / W;
 }
 
-int default_window(size_t n) {
-  // additions ~ n W (accumulation) + ~1.3 * 2^c W (signed-digit aggregation
-  // of 2^(c-1) buckets per window, merges included); widths above 18 win
-  // from n ~ 2^23 on (n = 2^24: c = 20 measured 5% faster than 17)
-  int best = 8;
-  double best_cost = 1e300;
-  for (int c = 4; c <= 20; ++c) {
-    double W = num_windows(c, MSM_DIGITS_SIGNED);
-    double cost = (double)n * W + 1.3 * std::ldexp(1.0, c) * W;
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = c;
-    }
-  }
-  return best;
-}
-
-int default_window_for(size_t n, int encoding) {
-  if (encoding != MSM_DIGITS_GLV) return default_window(n);
-  // split digits: 2n W entries of W = ceil(127 / c') windows, and 2^(c'-1)
-  // buckets per window, each costing about as much as 3.9 entries (tree,
-  // merges and the sort's identity fill: fitted to the n = 2^20 width sweep).
-  // Measured picks: c' = 16 up to n ~ 2^21 (2^18: 18% faster than the
-  // signed model's 15), c' = 19 above (2^22: 3%, 2^24: 10% faster than 16).
-  int best = 16;
-  double best_cost = 1e300;
-  for (int c = 4; c <= 20; ++c) {
-    const double W = num_windows(c, MSM_DIGITS_GLV);
-    if (W == 0) continue;
-    const int cw = window_bits(c, MSM_DIGITS_GLV);
-    const double cost = 2.0 * (double)n * W + 3.9 * std::ldexp(1.0, cw - 1) * W;
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = c;
-    }
-  }
-  return best;
-}
-
 // compute units of the current device (256 on MI355X; also the answer when
 // no device is visible, e.g. for workspace queries on a host without GPU)
 static int device_cus() {
@@ -160,6 +121,74 @@ static int device_cus() {
   }
   return cus;
 }
+
+// Cost of an MSM of n points at width c, in digit entries (8.8 G a second), one
+// of `jobs` that run together.  Work: the entries, 2.6 for each bucket (tree,
+// merges, the sort's identities) and 100 for each window.  Latency, which jobs
+// running together hide from each other: 5.5 us for each bucket bit (a level
+// of the tree and a step of the window's combination), 0.8 us for each window
+// (its step in the group aggregation), 11 us for the larger sort and the lanes'
+// merges beyond the quads' range, and a crowded top window: when its few
+// digits spread their entries over more than 64 chunks, k_merge_long has work
+// (11 us, and 23 more beyond 128 chunks, two stages).  Hence the widths whose top
+// window is nearly full, c' = 8, 11 (plain), 13 and 16, hold over long ranges of n.
+// Fitted to the widths around the pick by entries and buckets alone, 39 sizes of
+// single MSMs of each encoding and 21 batches: on average 0.6% above the best
+// width, that pick 4.5%.  Split digits, n = 4099: c' = 10 246 us, 8 229; n =
+// 24000: 12 398, 13 352; 64 jobs of 8192: 10 1.97 ms, 8 2.13.  Signed, n = 8192:
+// 10 366 us, 8 312.  Plain, n = 65536: 13 586 us, 11 513.
+double window_work(double n, double jobs, int c, int encoding) {
+  const double W = num_windows(c, encoding);
+  const int bits = window_bits(c, encoding);
+  const int bb = encoding == MSM_DIGITS_UNSIGNED ? bits : bits - 1;
+  return (encoding == MSM_DIGITS_GLV ? 2.0 : 1.0) * n * W +
+         jobs * (2.6 * std::ldexp(1.0, bb) + 100.0) * W;
+}
+
+static double window_cost(size_t n, int c, int encoding, size_t jobs, int cus) {
+  const int W = num_windows(c, encoding), bits = window_bits(c, encoding);
+  const int bb = encoding == MSM_DIGITS_UNSIGNED ? bits : bits - 1;
+  const double points = encoding == MSM_DIGITS_GLV ? 2.0 * (double)n : (double)n;
+  const double entries = points * W;
+  const double all = std::min(entries * (double)jobs, 2147483648.0);
+  AccumGeom g = {0, 0, all <= (double)ACCUM_QUAD_MAX ? 1u : 0u};
+  g.units = (uint32_t)cus * 4u * (g.quad ? 16u : 64u);
+  const double chunk = std::max(4.0, all / accum_units(g, (uint32_t)all));
+  // entries of one of the top window's digits, which run to the largest scalar's
+  // (split half's), or of its carry alone
+  const double largest = encoding == MSM_DIGITS_GLV ? std::ldexp((double)0x452217cc, 96)
+                                                    : std::ldexp((double)0x12ab655e, 224);
+  const double digits = std::floor(std::ldexp(largest, -bits * (W - 1)));
+  double span = points / std::max(1.0, digits) / chunk;
+  if (digits < 1.0) {
+    const double below = std::floor(std::ldexp(largest, -bits * (W - 2)));
+    span *= std::max(0.0, 1.0 - std::ldexp(0.5, bits) / below);
+  }
+  const double latency = 48e3 * bb + 7e3 * W + (g.quad ? 0.0 : 1e5) + (span > 64 ? 1e5 : 0.0) +
+                         (span > 128 ? 2e5 : 0.0);
+  return window_work((double)n, 1.0, c, encoding) + latency / (double)jobs;
+}
+
+int default_window_for(size_t n, int encoding, size_t jobs, size_t limit) {
+  int best = encoding == MSM_DIGITS_GLV ? 16 : 8;
+  double best_cost = 1e300;
+  const int cus = device_cus();
+  for (int c = 4; c <= 20; ++c) {
+    if (num_windows(c, encoding) == 0) continue;
+    if (limit) {
+      Plan pl;
+      if (!make_plan(&n, 1, c, encoding, pl) || pl.bytes > limit) continue;
+    }
+    const double cost = window_cost(n, c, encoding, jobs, cus);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = c;
+    }
+  }
+  return best;
+}
+
+int default_window(size_t n) { return default_window_for(n, MSM_DIGITS_SIGNED); }
 
 bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
                const Schedule& sched) {
@@ -372,9 +401,14 @@ int msm_bucket_accumulate(const uint32_t* xyu, const uint32_t* scalars, size_t n
 int msm_run(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int encoding,
             uint32_t* result, void* ws, size_t ws_bytes, void* stream) {
   if (!xyu || !scalars || !result || !ws) return MSM_EINVAL;
+  const int c_req = c;
   if (c == 0) c = default_window_for(n, encoding);
   Plan pl;
   if (!make_plan(&n, 1, c, encoding, pl)) return MSM_EINVAL;
+  // a workspace sized for msm_default_window's width serves unsigned digits too
+  if (ws_bytes < pl.bytes && c_req == 0 && encoding == MSM_DIGITS_UNSIGNED &&
+      !make_plan(&n, 1, default_window(n), encoding, pl))
+    return MSM_EINVAL;
   if (ws_bytes < pl.bytes) return MSM_ENOSPC;
   pl.one.xyu = xyu;
   pl.one.scalars = scalars;
@@ -385,9 +419,13 @@ int msm_run(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int e
 int msm_run_noalloc(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int encoding,
                     uint32_t* result, void* stream) {
   if (!xyu || !scalars || !result) return MSM_EINVAL;
+  const int c_req = c;
   if (c == 0) c = default_window_for(n, encoding);
   Plan pl;
   if (!make_plan(&n, 1, c, encoding, pl)) return MSM_EINVAL;
+  if (pl.bytes > kScratchBytes && c_req == 0 &&
+      !make_plan(&n, 1, default_window_for(n, encoding, 1, kScratchBytes), encoding, pl))
+    return MSM_EINVAL;
   if (pl.bytes > kScratchBytes) return MSM_ENOSPC;  // the MSM needs more than the scratch
   void* ws = nullptr;
   const int rc = scratch_of_current_device(&ws);

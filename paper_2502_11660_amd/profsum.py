@@ -48,10 +48,14 @@ def short_name(name):
 
 
 def sources_sha256(paths=ACCUM_SOURCES):
+    """Of the files' contents; "" when one is gone (a record of older sources)."""
     h = hashlib.sha256()
     for p in paths:
-        with open(os.path.join(ROOT, p), "rb") as f:
-            h.update(f.read())
+        try:
+            with open(os.path.join(ROOT, p), "rb") as f:
+                h.update(f.read())
+        except FileNotFoundError:
+            return ""
     return h.hexdigest()
 
 

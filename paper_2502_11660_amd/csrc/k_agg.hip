@@ -11,10 +11,9 @@
 // child R gives V[t] = L.V[t] + R.V[t] (t < h), V[h] = R.S, S = L.S + R.S.
 // Every output of a level is one independent addition, the whole tree costs
 // about 2 * 2^c additions per window (as many as the running-sum method) and
-// its dependent depth is only c additions.  Large levels run one addition per
-// lane, the first two in one kernel; smaller ones use four-lane quads
-// (quad29.hpp) to cut latency; the last ones of a window, and its Horner pass,
-// share one block.
+// its dependent depth is only c additions.  Large levels run on lanes, two to
+// a kernel; smaller ones use four-lane quads (quad29.hpp) to cut latency; the
+// last ones of a window, and its Horner pass, share one block.
 //
 // Each window then forms S_w by Horner's rule on one latency unit, and group
 // aggregation Q = sum_w 2^(w c) S_w is Horner's rule over the windows of a job
@@ -102,6 +101,44 @@ __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__
   const xytz29 r = padd29_full(pt29_from(ld_xytz(L + (size_t)a * XYTZ_WORDS)),
                                pt29_from(ld_xytz(R + (size_t)a * XYTZ_WORDS)));
   st_xytz(O + (size_t)s * XYTZ_WORDS, pt29_to_words(r));
+}
+
+// Levels h and h + 1 on lanes, one per output record as k_tree_quad2's quads
+// below (nodes: of level h + 1, over all windows): first the sums of four
+// records, then those of two, so that a wave's lanes do one kind.  The next
+// record loads during an addition, where a level of its own waits for its two
+// and writes and reads every record between: two levels at n = 300007, signed
+// digits (15 bits) 49 -> 36 us, at n = 2^20 48 -> 42, four at n = 2^22 (c = 19)
+// 295 -> 279.
+__global__ void __launch_bounds__(256) k_tree_level2(const uint32_t* __restrict__ in, uint32_t h,
+                                                     uint64_t nodes, uint32_t* __restrict__ out) {
+  const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint64_t fours = nodes * (h + 1);
+  if (g >= fours + 2 * nodes) return;
+  const bool four = g < fours;
+  const uint64_t node = four ? g / (h + 1) : (g - fours) >> 1;
+  const uint32_t a = four ? (uint32_t)(g % (h + 1)) : h;  // slot of the grandchildren
+  const uint32_t odd = (uint32_t)(g - fours) & 1u;
+  const uint32_t s = !four ? h + odd : (a < h ? a : h + 2);
+  const uint32_t* R = in + (node * 4 * (h + 1) + a) * XYTZ_WORDS;
+  const size_t stride = (size_t)(h + 1) * XYTZ_WORDS;
+  uint32_t left = four ? 0xfu : (odd ? 0xcu : 0xau);
+  auto next = [&] {
+    const uint32_t i = (uint32_t)__builtin_ctz(left);
+    left &= left - 1;
+    return ld_xytz(R + i * stride);
+  };
+  xytz29 acc = pt29_from(next());
+  xytz w = next();
+#pragma unroll 1
+  for (;;) {
+    const xytz29 v = pt29_from(w);
+    const bool more = left != 0;
+    if (more) w = next();
+    acc = padd29_full(acc, v);
+    if (!more) break;
+  }
+  st_xytz(out + (node * (h + 3) + s) * XYTZ_WORDS, pt29_to_words(acc));
 }
 
 // Levels h and h + 1 on quads, one per output record: slot t < h of a node is
@@ -414,6 +451,11 @@ int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStrea
     if (h == 0 && !tail(1) && outs(1) >= pl.tree_quad) {
       const uint64_t lanes = (uint64_t)S << (bb - 1);
       k_tree_first<<<(unsigned)((lanes + 255) / 256), 256, 0, st>>>(in, lanes, out);
+      ++h;
+      nodes >>= 1;
+    } else if (outs(h + 1) >= pl.tree_quad && !tail(h + 1)) {
+      const uint64_t n1 = (uint64_t)S << (bb - 2 - h);
+      k_tree_level2<<<(unsigned)((n1 * (h + 3) + 255) / 256), 256, 0, st>>>(in, h, n1, out);
       ++h;
       nodes >>= 1;
     } else if (outs(h) >= pl.tree_quad) {

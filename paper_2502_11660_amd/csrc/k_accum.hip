@@ -76,10 +76,11 @@ __device__ __forceinline__ Chunks chunks_of(const AccumGeom& g, uint32_t E) {
 // are converted from their 12-word records as they are loaded, the running
 // sum stays in that form and is converted when it is stored (as signed
 // words, fe29.hpp: 28 shifts and ors a coordinate).  Bound by VALU issue at
-// a power-limited clock: 3090 VALU instructions an entry, 2347 of them
-// multiply-adds, issued in 89% of SIMD cycles; n = 2^20 with split digits,
-// sustained: 2.14 ms with the 28-bit core -> 1.90 ms (8.8 G entries/s).
-// (Four waves per SIMD measured no faster than three.  Reading keys and
+// a power-limited clock: 3090 VALU instructions an entry, 2350 of them
+// multiply-adds, issued in 90% of SIMD cycles at 2.0 GHz; n = 2^20 with split
+// digits, sustained: 2.14 ms with the 28-bit core, 1.90 with this one, 1.75-1.81
+// (9.4 G entries/s) with a column's multiply-adds in one block.  Waves per SIMD:
+// see accum_units; four measured no faster than three.  (Reading keys and
 // indices in groups of four cut the kernel's HBM reads by 31%.)
 __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
                                                  const int64_t* __restrict__ segoff, uint32_t bb,

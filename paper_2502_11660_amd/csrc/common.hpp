@@ -163,6 +163,16 @@ __host__ __device__ inline uint32_t accum_units(const AccumGeom& g, uint32_t E) 
 constexpr size_t SMALL_SORT_MAX = 16384;
 constexpr int SMALL_SORT_BITS = 13;
 
+// Windows of jobs of at most SEGMENT_MAX point records and SEGMENT_BITS bucket
+// bits (one addition per quad of a block at the first level) run whole in one
+// block each (k_segment), when there are compute units for all of them: n = 128
+// split digits 178 -> 174 us, n = 256 signed 266 -> 246.  With more records a block's
+// own quads take longer than the chip's (512 signed 263 -> 279; 180 split, 360
+// records, 179 -> 192), and with more windows than compute units the blocks' idle
+// lanes cost (64 jobs of 32 to 128 points, 428 -> 493 us).
+constexpr size_t SEGMENT_MAX = 256;
+constexpr int SEGMENT_BITS = 8;
+
 // key of the entries that the one-kernel sort keeps for zero digits
 constexpr uint32_t KEY_NONE = 0xffffffffu;
 // bucket b's place in the offsets array: each segment has its 2^bb buckets'
@@ -189,6 +199,7 @@ struct Plan {
   uint64_t tree_quad = 65536;  // tree levels with fewer outputs run on quads
   uint64_t tree_wide = 0;      // outputs from which a window's levels run in one block (0: k_agg.hip's rule)
   bool small_sort = false;            // the one-kernel sort
+  bool segment = false;  // windows run whole, one block each (k_segment)
   uint32_t lo_bits = 0, hi_bits = 0;  // split of the bb bucket bits in the sort
   uint32_t tpb = 1;                   // pass-1 tiles per block (one histogram per group)
   uint32_t tile_digits = SORT_TILE;   // digits per group, SORT_TILE tpb
@@ -260,6 +271,8 @@ int launch_records_unsigned(uint32_t* recs, size_t n, hipStream_t st);
 // affine results of every job
 int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStream_t st);
 int launch_horner(const Plan& pl, void* ws, hipStream_t st);
+// k_segment.hip: all of that up to the window sums for small jobs (Plan::segment)
+int launch_segments(const Plan& pl, void* ws, hipStream_t st);
 // k_elementwise.hip
 int launch_fe_mul(const uint32_t* a, const uint32_t* b, uint32_t* out, uint32_t count,
                   int canonical, hipStream_t st);

@@ -33,6 +33,7 @@
 
 #include "common.hpp"
 #include "convert.hpp"
+#include "small_sort.hpp"
 
 namespace msm {
 namespace {
@@ -202,11 +203,6 @@ __global__ void __launch_bounds__(256) k_slice(JobView jv, uint32_t N, int c, in
     if (w == 0 && over) q |= RANGE_BIT;
     out[(size_t)w * d.n] = q;
   }
-}
-
-// bucket index and the entry's index word of a digit word q != 0
-__device__ __forceinline__ uint32_t bucket_of(uint32_t q, uint32_t off) {
-  return (q & 0x7fffffffu) - off;
 }
 
 // pass 1a: per-group histogram of the high bits (the group's tiles one
@@ -577,33 +573,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_big_scatter(
 // Every segment's block reads all scalars and splits them again, which at
 // SMALL_SORT_MAX points still costs less than the launches (signed digits:
 // 451 us at 16384 points, 470 at 16385).
-//
-// Signed digits by their place alone: with B = sum_{w < W-1} 2^(w c + c - 1)
-// added to the scalar, window w < W - 1 holds d_w + 2^(c-1), and the top window
-// its digit (the recoding's carries are the addition's).
 constexpr uint32_t SMALL_ROWS = 16;  // entries per thread
-
-struct Bias {
-  uint32_t w[SCALAR_WORDS];
-};
-
-// digit word of window w (top: the last): q | sign << 31
-__device__ __forceinline__ uint32_t small_digit(scalar256 s, const Bias& bias, int w, int c,
-                                                bool top, bool is_signed) {
-  if (is_signed) {
-    uint64_t t = 0;
-#pragma unroll
-    for (int i = 0; i < SCALAR_WORDS; ++i) {
-      t += (uint64_t)s.w[i] + bias.w[i];
-      s.w[i] = (uint32_t)t;
-      t >>= 32;
-    }
-  }
-  const uint32_t v = digit_at(s, w * c, c);
-  if (!is_signed || top) return v;
-  const int32_t d = (int32_t)v - (1 << (c - 1));
-  return d < 0 ? (uint32_t)-d | 0x80000000u : (uint32_t)d;
-}
 
 __global__ void __launch_bounds__(1024) k_small_sort(SortGeom g, int c, int encoding, Bias bias,
                                                      uint32_t* __restrict__ key,
@@ -618,9 +588,7 @@ __global__ void __launch_bounds__(1024) k_small_sort(SortGeom g, int c, int enco
   const uint32_t tid = threadIdx.x, T = blockDim.x, B = 1u << g.bb, seg = blockIdx.x;
   const uint32_t j = seg / g.W, w = seg % g.W;
   const JobDesc d = g.jv.get(j);
-  const bool glv = encoding == MSM_DIGITS_GLV, is_signed = encoding != MSM_DIGITS_UNSIGNED;
-  const bool top = w + 1 == g.W;
-  const uint32_t off = is_signed ? 1u : 0u;
+  const bool glv = encoding == MSM_DIGITS_GLV, top = w + 1 == g.W;
   if (seg == 0 && tid == 0) {
     *total = NW;
     longlist[0] = 0u;
@@ -628,65 +596,11 @@ __global__ void __launch_bounds__(1024) k_small_sort(SortGeom g, int c, int enco
   }
   for (uint32_t b = tid; b < B; b += T) start[b] = 0;
   __syncthreads();
-  // entries in registers: bucket | rank << 13 | sign << 31, all ones for none
   uint32_t ent[SMALL_ROWS];
-  uint32_t range = 0;
-  const uint32_t ns = glv ? d.n >> 1 : d.n;  // scalars
-  auto place = [&](uint32_t q) {
-    if (q == 0) return 0xffffffffu;
-    const uint32_t m = bucket_of(q, off);
-    return m | (atomicAdd(&start[m], 1u) << 13) | (q & 0x80000000u);
-  };
-#pragma unroll
-  for (uint32_t r = 0; r < SMALL_ROWS; r += 2) {
-    ent[r] = ent[r + 1] = 0xffffffffu;
-    if (glv) {
-      const uint32_t i = (r >> 1) * T + tid;
-      if (i < ns) {
-        scalar256 s0, s1;
-        uint32_t out = 0;
-        glv_split(ld_scalar_flag(d.scalars, i, out), s0, s1);
-        range |= out;
-        ent[r] = place(small_digit(s0, bias, (int)w, c, top, true));
-        ent[r + 1] = place(small_digit(s1, bias, (int)w, c, top, true));
-      }
-    } else {
-#pragma unroll
-      for (uint32_t t = r; t < r + 2; ++t) {
-        const uint32_t i = t * T + tid;
-        if (i < ns) {
-          uint32_t out = 0;
-          const scalar256 s = ld_scalar_flag(d.scalars, i, out);
-          range |= out;
-          ent[t] = place(small_digit(s, bias, (int)w, c, top, is_signed));
-        }
-      }
-    }
-  }
+  const uint32_t range = small_entries<SMALL_ROWS>(ent, start, d, bias, w, c, encoding, top);
   const int any = __syncthreads_or((int)range);
   if (w == 0 && tid == 0) flags[j] = any ? MSM_FLAG_RANGE : 0u;
-  // exclusive scan of the counts, `per` buckets a thread
-  const uint32_t per = (B + T - 1) / T, b0 = min(tid * per, B), b1 = min(b0 + per, B);
-  uint32_t sum = 0;
-  for (uint32_t b = b0; b < b1; ++b) sum += start[b];
-  uint32_t x = sum;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
-#pragma unroll
-  for (int dd = 1; dd < 64; dd <<= 1) {
-    const uint32_t y = __shfl_up(x, dd, 64);
-    if (lane >= (uint32_t)dd) x += y;
-  }
-  if (lane == 63) wsum[wave] = x;
-  __syncthreads();
-  uint32_t run = x - sum;
-  for (uint32_t k = 0; k < wave; ++k) run += wsum[k];
-  for (uint32_t b = b0; b < b1; ++b) {
-    const uint32_t v = start[b];
-    start[b] = run;
-    run += v;
-  }
-  if (tid == T - 1) start[B] = run;
-  __syncthreads();
+  small_starts(start, wsum, B);
   const uint32_t count = start[B], base = g.W * d.pt_off + w * d.n;
   uint32_t* offs = offsets + (size_t)seg * (B + 1);
   for (uint32_t b = tid; b <= B; b += T) {
@@ -699,7 +613,7 @@ __global__ void __launch_bounds__(1024) k_small_sort(SortGeom g, int c, int enco
     if (ent[r] == 0xffffffffu) continue;
     const uint32_t m = ent[r] & 0x1fffu;
     const uint32_t pos = base + start[m] + ((ent[r] >> 13) & 0x3fffu);
-    const uint32_t i = glv ? 2u * ((r >> 1) * T + tid) + (r & 1u) : r * T + tid;
+    const uint32_t i = small_index(r, glv);
     key[pos] = (seg << g.bb) + m;
     idx[pos] = i | (ent[r] & 0x80000000u);
   }
@@ -899,16 +813,10 @@ int launch_sort(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st) {
   const uint32_t off = pl.encoding == MSM_DIGITS_UNSIGNED ? 0u : 1u;
 
   if (pl.small_sort) {
-    Bias bias = {};
-    if (pl.encoding != MSM_DIGITS_UNSIGNED)
-      for (int w = 0; w + 1 < pl.W; ++w) {
-        const int bit = w * pl.c + pl.c - 1;
-        bias.w[bit >> 5] |= 1u << (bit & 31);
-      }
     // a few entries a thread, at most SMALL_ROWS
     const unsigned threads = (unsigned)std::min<size_t>(1024, (pl.max_n / 4 + 256) / 256 * 256);
     k_small_sort<<<(unsigned)pl.S, threads, ((size_t)4 << pl.bb) + 4, st>>>(
-        g, pl.c, pl.encoding, bias, key, idx, offsets, buckets, flags, total, (uint32_t)pl.NW,
+        g, pl.c, pl.encoding, small_bias(pl), key, idx, offsets, buckets, flags, total, (uint32_t)pl.NW,
         ws_at<uint32_t>(ws, pl.o_longlist));
     HIPCHK(hipGetLastError());
     return MSM_OK;

@@ -220,6 +220,10 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
     return false;
   sort_geometry(pl, ns, J, mult);
   pl.small_sort = pl.max_n <= SMALL_SORT_MAX && pl.bb <= SMALL_SORT_BITS;
+  // (a schedule is for the kernels that it schedules)
+  pl.segment = pl.max_n <= SEGMENT_MAX && pl.bb <= SEGMENT_BITS &&
+               pl.S <= (size_t)device_cus() && sched.chunk == 0 && sched.tree_quad == 0 &&
+               sched.tree_wide == 0;
   if (pl.lo_bits > 8 || pl.nb > 4096 || pl.tiles >= ((size_t)1 << 31)) return false;
   if (J == 1) {
     pl.one.n = (uint32_t)(mult * ns[0]);
@@ -280,6 +284,11 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
 int enqueue_msm(const Plan& pl, void* ws, hipStream_t st, hipEvent_t accum_after) {
   uint32_t* buckets = ws_at<uint32_t>(ws, pl.o_buckets);
   int rc;
+  if (pl.segment) {
+    if (accum_after) HIPCHK(hipStreamWaitEvent(st, accum_after, 0));
+    if ((rc = launch_segments(pl, ws, st)) != MSM_OK) return rc;
+    return launch_horner(pl, ws, st);
+  }
   {
     ProfScope prof(PT_SORT, st);
     rc = launch_sort(pl, buckets, ws, st);

@@ -336,11 +336,13 @@ int launch_padd(const uint32_t* a, const uint32_t* b, uint32_t* out, uint32_t co
 
 int launch_prepare(const uint32_t* xy, const uint32_t* inf, uint32_t* xyu, uint32_t n,
                    uint32_t* status, bool endo, hipStream_t st) {
-  // points per thread: two waves per SIMD, the most the registers of the form
-  // with images allow (256 CUs x 4 SIMDs x 64 lanes x 2), the rest of the
+  // points per thread: at most two waves per SIMD, the most the registers of the
+  // form with images allow (256 CUs x 4 SIMDs x 64 lanes x 2), the rest of the
   // points batched; n = 2^20 with images at three waves and spills 504 us, at one
-  // 514, against 457
-  const uint32_t m = std::max<uint32_t>(1u, std::min<uint32_t>(64u, n / 131072u));
+  // 514, against 457.  Rounded up, so that no second round follows for a few
+  // threads: n = 1500000 with images 501 -> 397 us, without 322 -> 272, n = 700000
+  // 248 -> 199 and 168 -> 135 (n = 262145 without 78 -> 81).
+  const uint32_t m = std::max<uint32_t>(1u, std::min<uint32_t>(64u, (n + 131071u) / 131072u));
   const uint32_t T = (uint32_t)(((uint64_t)n + m - 1) / m);
   if (endo)
     k_prepare<true><<<grid_for(T, 256), 256, 0, st>>>(xy, inf, xyu, n, T, m, status);

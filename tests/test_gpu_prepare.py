@@ -53,3 +53,19 @@ def test_records(n, endo):
     if odd:
         got = H.unaos(api.to_host(rows[odd[0] * rec].contiguous()), 3, 1)[0]
         assert got == (0, (1 << 384) % P, 0)
+
+
+@pytest.mark.parametrize("endo", [False, True])
+@pytest.mark.parametrize("n", [131073, 262144, 400001])
+def test_records_do_not_depend_on_the_batching(n, endo):
+    """Points per thread change with n; a point's record does not."""
+    kw = inputs.nonzero_scalars_mod_r(70 + n, n, stream=1)
+    xy, inf = api.gen_points(api.to_device(kw), n)
+    whole, status = api.points_prepare(xy, n, inf=inf, endo=endo)
+    assert int(api.to_host(status)[0]) == 0
+    soa = xy.view(2, 12, n)
+    rec = 72 if endo else 36
+    for lo, hi in ((0, 70000), (n - 50001, n)):
+        part, _ = api.points_prepare(soa[:, :, lo:hi].contiguous().reshape(-1), hi - lo,
+                                     inf=inf[lo:hi].contiguous(), endo=endo)
+        assert bool((part == whole[rec * lo:rec * hi]).all())

@@ -6,8 +6,8 @@ first the window width c at candidates around the static heuristic
 the schedule of the job's pipeline one parameter at a time: the
 accumulation chunk (digit entries per lane: the default that fills one
 resident round of lanes, half of it, twice it) and the aggregation tree's
-unit thresholds (the output counts below which a level runs on the four-lane
-unit, and up to which on the wide two-wave unit).  A candidate replaces the
+thresholds (the output counts below which a level runs on the four-lane
+unit, and from which on a window's levels share a block).  A candidate replaces the
 current choice only when it is faster by more than 2%, so the defaults stay
 unless a change pays.
 
@@ -33,7 +33,7 @@ from . import api
 # schedule candidates (0 = the library's default)
 CHUNK_SCALES = (0.5, 2.0)                 # times the default chunk of the class
 TREE_QUAD = (16384, 262144)               # default 65536
-TREE_WIDE = (256, 4096)                   # default 1024
+TREE_WIDE = (256, 4096)                   # default: by the additions per window
 MIN_GAIN = 0.02
 
 
@@ -54,10 +54,12 @@ def n_bucket(n):
 def default_chunk(total_entries, cus=256):
     """The average length of the library's default accumulation chunks for a
     class with this many digit entries: one chunk per lane of one, two or
-    three waves per SIMD (below 16 and 160 entries a lane of one wave), at
-    least 4 entries; the library splits that into lengths K and K + 4
-    (multiples of 4)."""
+    three waves per SIMD (below 16 and 160 entries a lane of one wave), or per
+    four lanes up to 2^19 entries, at least 4 entries; the library splits that
+    into lengths K and K + 4 (multiples of 4)."""
     e, lanes = int(total_entries), cus * 4 * 64
+    if e <= 1 << 19:
+        return max(4, -(-e // (lanes // 4)))
     waves = 1 if e < 16 * lanes else 2 if e < 160 * lanes else 3
     return max(4, -(-e // (waves * lanes)))
 

@@ -299,8 +299,8 @@ int msm_run_noalloc(const uint32_t* xyu, const uint32_t* scalars, size_t n, int 
  * msm_batch_destroy: waits for the batch's work, frees the handle, its
  *   streams and its graph; NULL is accepted.
  * Errors: MSM_EINVAL (null pointers, njobs = 0, a job with n = 0 or an
- * invalid c, more than 2^26 points or 2^31 digits per class), MSM_ENOSPC,
- * MSM_EHIP. */
+ * invalid c, more than 2^31 points, digits or buckets per class; jobs with c = 0
+ * start another class before that), MSM_ENOSPC, MSM_EHIP. */
 typedef struct msm_job {
   const uint32_t* xyu;
   const uint32_t* scalars;

@@ -10,7 +10,9 @@
 // and joined back into it.  With use_graph the whole launch sequence is
 // captured once into a HIP graph and every run is a single graph launch.
 #include <algorithm>
+#include <cmath>
 #include <map>
+#include <tuple>
 #include <vector>
 
 #include "common.hpp"
@@ -35,8 +37,9 @@ namespace {
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// a class: jobs with the same window width and schedule
-typedef std::pair<int, Schedule> ClassKey;
+// a class: jobs with the same window width and schedule, and its part: a width
+// that jobs with c = 0 share starts another class before it outgrows one
+typedef std::tuple<int, Schedule, int> ClassKey;
 typedef std::map<ClassKey, std::vector<size_t>> Classes;
 
 Schedule schedule_of(const msm_job& jb) {
@@ -55,6 +58,9 @@ Schedule schedule_of(const msm_job& jb) {
 // one class a width: 1.087 times as fast on average (0.75e5 and 1.5e5: 1.081,
 // 1.084); without joining, 16 jobs of 2^12 .. 2^15 points 1138 us, with it 986.
 constexpr double CLASS_COST = 3e5;
+// Digit slots and buckets that c = 0 puts into one class: half and an eighth of
+// what a class can hold, so that every batch of jobs that plan alone plans.
+constexpr double CLASS_SLOTS = 1073741824.0, CLASS_BUCKETS = 268435456.0;
 
 struct WidthSum {
   double jobs = 0, n = 0;
@@ -105,10 +111,28 @@ bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls) {
   }
   std::map<Schedule, std::map<int, int>> joined;
   for (const auto& kv : picked) joined[kv.first] = join_widths(kv.second, encoding);
+  struct Part {
+    int index = 0;
+    double slots = 0, buckets = 0;
+  };
+  std::map<std::pair<int, Schedule>, Part> parts;
   for (size_t i = 0; i < njobs; ++i) {
     const Schedule sched = schedule_of(jobs[i]);
     const int c = jobs[i].c == 0 ? joined[sched][width[i]] : width[i];
-    cls[ClassKey(c, sched)].push_back(i);
+    const double W = num_windows(c, encoding);
+    const double slots = (encoding == MSM_DIGITS_GLV ? 2.0 : 1.0) * (double)jobs[i].n * W;
+    const double buckets = std::ldexp(W, window_bits(c, encoding));
+    Part& p = parts[std::make_pair(c, sched)];
+    if (jobs[i].c == 0 && p.slots > 0 &&
+        (p.slots + slots > CLASS_SLOTS || p.buckets + buckets > CLASS_BUCKETS)) {
+      ++p.index;
+      p.slots = p.buckets = 0;
+    }
+    if (jobs[i].c == 0 || p.index == 0) {
+      p.slots += slots;
+      p.buckets += buckets;
+    }
+    cls[ClassKey(c, sched, jobs[i].c == 0 ? p.index : 0)].push_back(i);
   }
   return true;
 }
@@ -120,7 +144,8 @@ bool plan_classes(const msm_job* jobs, const Classes& cls, int encoding, std::ve
     std::vector<size_t> ns;
     for (size_t i : kv.second) ns.push_back(jobs[i].n);
     Plan pl;
-    if (!make_plan(ns.data(), (uint32_t)ns.size(), kv.first.first, encoding, pl, kv.first.second))
+    if (!make_plan(ns.data(), (uint32_t)ns.size(), std::get<0>(kv.first), encoding, pl,
+                   std::get<1>(kv.first)))
       return false;
     plans.push_back(pl);
     off.push_back(total);

@@ -204,17 +204,20 @@ int msm_window_bits(int c, int encoding);
 
 /* Workspace (device bytes) needed by msm_bucket_accumulate / msm_run for n
  * points, window width c (c = 0: the width msm_run would pick) and a digit
- * encoding.  Returns 0 for invalid arguments. */
+ * encoding.  Returns 0 for invalid arguments.  With c = 0 it may fall where the
+ * pick changes (the width for more points can need less); a workspace of it
+ * serves every smaller n too, msm_run then picking among the widths that fit. */
 size_t msm_workspace_bytes(size_t n, int c, int encoding);
 
 /* Window width msm_run picks for n points when called with c = 0 and signed
  * digits (a cost model over widths 4..20: entries, buckets, and the latencies
  * that a single MSM waits for; the same model picks for the other encodings:
  * with the endomorphism split c' = 8 up to n ~ 2^14, 13 up to 2^17, 16 up to
- * 2^21 and 19, seven windows, above).  msm_run with unsigned digits and c = 0
- * also takes a workspace sized for this width, and then runs at it if its own
- * choice needs more.  Among jobs that run together (a batch, a server with
- * several streams) latencies count for less, and c = 0 picks accordingly. */
+ * 2^21 and 19, seven windows, above).  When the workspace is too small for the
+ * pick, msm_run with c = 0 takes the best width that fits it, as in one sized for
+ * this width and another encoding.  Among jobs that run together (a batch, a
+ * server with several streams) latencies count for less, and c = 0 picks
+ * accordingly. */
 int msm_default_window(size_t n);
 
 /* Bucket accumulation (Sec. II-C), digits of c' = msm_window_bits(c,
@@ -241,7 +244,8 @@ int msm_bucket_accumulate(const uint32_t* xyu, const uint32_t* scalars, size_t n
  * result: MSM_RESULT_WORDS device words: x[12], y[12] (Weierstrass affine,
  * ordinary form, canonical), inf (1 if the sum is the point at infinity, then
  * x = y = 0), flags (MSM_FLAG_RANGE).  Other arguments as for
- * msm_bucket_accumulate.  Errors as for msm_bucket_accumulate. */
+ * msm_bucket_accumulate.  Errors as for msm_bucket_accumulate (MSM_ENOSPC with
+ * c = 0: no width fits ws). */
 int msm_run(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int encoding,
             uint32_t* result, void* ws, size_t ws_bytes, void* stream);
 

@@ -216,7 +216,8 @@ int num_windows(int c, int encoding);
 int window_bits(int c, int encoding);
 int default_window(size_t n);                     // signed-digit model (msm_default_window)
 // the width c = 0 picks for an MSM of an encoding that is one of `jobs` run
-// together, among those whose workspace is within `limit` bytes (0: any)
+// together, among those whose workspace is within `limit` bytes (0: any); 0 when
+// none is
 int default_window_for(size_t n, int encoding, size_t jobs = 1, size_t limit = 0);
 // work of `jobs` MSMs of n points in all at width c, in digit entries
 double window_work(double n, double jobs, int c, int encoding);
@@ -235,6 +236,12 @@ struct Schedule {
 // schedule values
 bool make_plan(const size_t* ns, uint32_t J, int c, int encoding, Plan& pl,
                const Schedule& sched = Schedule());
+
+// plan of one MSM in `limit` bytes of workspace, at width c, or for c = 0 at the
+// width picked for one of `jobs`, or if that takes more at the best that fits:
+// MSM_OK, MSM_EINVAL (as make_plan) or MSM_ENOSPC
+int plan_within(size_t n, int c, int encoding, size_t jobs, size_t limit, Plan& pl,
+                const Schedule& sched = Schedule());
 
 template <typename T>
 inline T* ws_at(void* ws, size_t off) {

@@ -170,7 +170,7 @@ static double window_cost(size_t n, int c, int encoding, size_t jobs, int cus) {
 }
 
 int default_window_for(size_t n, int encoding, size_t jobs, size_t limit) {
-  int best = encoding == MSM_DIGITS_GLV ? 16 : 8;
+  int best = 0;
   double best_cost = 1e300;
   const int cus = device_cus();
   for (int c = 4; c <= 20; ++c) {
@@ -279,6 +279,19 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
   pl.o_segoff = take(pl.S * 8);
   pl.bytes = o;
   return true;
+}
+
+// The picked width's workspace does not grow with n throughout (split digits: 512
+// points 3.9 MB, 513 2.4 MB), so one sized for more points may be too small for it
+// and yet hold a plan at the larger size's width.
+int plan_within(size_t n, int c, int encoding, size_t jobs, size_t limit, Plan& pl,
+                const Schedule& sched) {
+  const int pick = c == 0 ? default_window_for(n, encoding, jobs) : c;
+  if (!make_plan(&n, 1, pick, encoding, pl, sched)) return MSM_EINVAL;
+  if (pl.bytes <= limit) return MSM_OK;
+  const int fits = c == 0 ? default_window_for(n, encoding, jobs, limit) : 0;
+  return fits && make_plan(&n, 1, fits, encoding, pl, sched) && pl.bytes <= limit ? MSM_OK
+                                                                                  : MSM_ENOSPC;
 }
 
 int enqueue_msm(const Plan& pl, void* ws, hipStream_t st, hipEvent_t accum_after) {
@@ -410,15 +423,9 @@ int msm_bucket_accumulate(const uint32_t* xyu, const uint32_t* scalars, size_t n
 int msm_run(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int encoding,
             uint32_t* result, void* ws, size_t ws_bytes, void* stream) {
   if (!xyu || !scalars || !result || !ws) return MSM_EINVAL;
-  const int c_req = c;
-  if (c == 0) c = default_window_for(n, encoding);
   Plan pl;
-  if (!make_plan(&n, 1, c, encoding, pl)) return MSM_EINVAL;
-  // a workspace sized for msm_default_window's width serves unsigned digits too
-  if (ws_bytes < pl.bytes && c_req == 0 && encoding == MSM_DIGITS_UNSIGNED &&
-      !make_plan(&n, 1, default_window(n), encoding, pl))
-    return MSM_EINVAL;
-  if (ws_bytes < pl.bytes) return MSM_ENOSPC;
+  const int rc = plan_within(n, c, encoding, 1, ws_bytes, pl);
+  if (rc != MSM_OK) return rc;
   pl.one.xyu = xyu;
   pl.one.scalars = scalars;
   pl.one.result = result;
@@ -428,17 +435,11 @@ int msm_run(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int e
 int msm_run_noalloc(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int encoding,
                     uint32_t* result, void* stream) {
   if (!xyu || !scalars || !result) return MSM_EINVAL;
-  const int c_req = c;
-  if (c == 0) c = default_window_for(n, encoding);
   Plan pl;
-  if (!make_plan(&n, 1, c, encoding, pl)) return MSM_EINVAL;
-  if (pl.bytes > kScratchBytes && c_req == 0 &&
-      !make_plan(&n, 1, default_window_for(n, encoding, 1, kScratchBytes), encoding, pl))
-    return MSM_EINVAL;
-  if (pl.bytes > kScratchBytes) return MSM_ENOSPC;  // the MSM needs more than the scratch
-  void* ws = nullptr;
-  const int rc = scratch_of_current_device(&ws);
+  int rc = plan_within(n, c, encoding, 1, kScratchBytes, pl);
   if (rc != MSM_OK) return rc;
+  void* ws = nullptr;
+  if ((rc = scratch_of_current_device(&ws)) != MSM_OK) return rc;
   pl.one.xyu = xyu;
   pl.one.scalars = scalars;
   pl.one.result = result;

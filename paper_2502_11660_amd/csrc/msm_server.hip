@@ -236,18 +236,13 @@ int msm_server_submit(msm_server* s, const msm_job* job, void* stream, uint64_t*
   if (!s || !job || !ticket || !job->xyu || !job->scalars || !job->result) return MSM_EINVAL;
   Request r;
   r.job = *job;
-  const int c = job->c == 0 ? default_window_for(job->n, s->encoding, s->streams.size()) : job->c;
-  size_t n = job->n;
   Schedule sched;
   sched.chunk = job->chunk;
   sched.tree_quad = job->tree_quad;
   sched.tree_wide = job->tree_wide;
-  if (!make_plan(&n, 1, c, s->encoding, r.plan, sched)) return MSM_EINVAL;
-  if (r.plan.bytes > s->arena.size && job->c == 0 &&
-      !make_plan(&n, 1, default_window_for(n, s->encoding, s->streams.size(), s->arena.size),
-                 s->encoding, r.plan, sched))
-    return MSM_EINVAL;
-  if (r.plan.bytes > s->arena.size) return MSM_ENOSPC;
+  const int fit = plan_within(job->n, job->c, s->encoding, s->streams.size(), s->arena.size, r.plan,
+                              sched);
+  if (fit != MSM_OK) return fit;
   r.plan.one.xyu = job->xyu;
   r.plan.one.scalars = job->scalars;
   r.plan.one.result = job->result;

@@ -1,0 +1,50 @@
+"""A workspace of msm_workspace_bytes(n, 0, encoding) serves every smaller MSM with
+c = 0, also where the picked width needs more for fewer points."""
+
+import ctypes
+
+import pytest
+import torch
+
+from oracle import msm
+from paper_2502_11660_amd import _lib, api, inputs
+
+S, U, G = _lib.MSM_DIGITS_SIGNED, _lib.MSM_DIGITS_UNSIGNED, _lib.MSM_DIGITS_GLV
+
+
+def _host_status(n, enc, ws_bytes, c=0):
+    """msm_run's status on a host without GPU: MSM_EHIP once a plan fits."""
+    p = ctypes.c_void_p(256)
+    return _lib.lib().msm_run(p, p, n, c, enc, p, p, ws_bytes, None)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="would launch on made-up pointers")
+@pytest.mark.parametrize("enc", [S, U, G])
+def test_smaller_sizes_fit(enc):
+    sizes = sorted({int(round(1.13 ** k)) for k in range(8, 105)} | {512, 513, 927, 930, 1024, 1025,
+                                                                    14423, 15000})
+    need = [_lib.lib().msm_workspace_bytes(n, 0, enc) for n in sizes]
+    fell = 0
+    for i, n in enumerate(sizes):
+        for j in range(i, len(sizes)):
+            if need[j] < need[i]:
+                fell += 1
+                assert _host_status(n, enc, need[j]) == _lib.MSM_EHIP, (n, sizes[j])
+        assert _host_status(n, enc, need[i]) == _lib.MSM_EHIP
+        assert _host_status(n, enc, 100) == _lib.MSM_ENOSPC
+    assert fell > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("enc,n,larger", [(G, 512, 513), (G, 14423, 15000), (S, 927, 930),
+                                          (U, 1024, 1025)])
+def test_run_in_a_larger_size_s_workspace(enc, n, larger):
+    ws = api.workspace(larger, 0, enc)
+    assert ws.numel() * 4 < api.workspace_bytes(n, 0, enc)
+    kw = inputs.nonzero_scalars_mod_r(90 + n, n, stream=1)
+    sw = inputs.scalars_mod_r(90 + n, n, stream=2)
+    xy, inf = api.gen_points(api.to_device(kw), n)
+    xyu, _ = api.points_prepare(xy, n, inf=inf, endo=enc == G)
+    ws.fill_(-1)
+    got, flags = api.decode_result(api.to_host(api.msm_run(xyu, api.to_device(sw), n, 0, enc, ws=ws)))
+    assert flags == 0 and got == msm.closed_form_words(sw, kw)

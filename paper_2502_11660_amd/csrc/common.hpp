@@ -212,15 +212,6 @@ struct Plan {
          o_lvl1 = 0, o_wsum = 0, o_longlist = 0, o_counters = 0, o_bigdesc = 0, o_bigsum = 0, o_bigcnt = 0, o_bigitem = 0, o_jobs = 0, o_segoff = 0, bytes = 0;
 };
 
-int num_windows(int c, int encoding);
-int window_bits(int c, int encoding);
-int default_window(size_t n);                     // signed-digit model (msm_default_window)
-// the width c = 0 picks for an MSM of an encoding that is one of `jobs` run
-// together, among those whose workspace is within `limit` bytes (0: any); 0 when
-// none is
-int default_window_for(size_t n, int encoding, size_t jobs = 1, size_t limit = 0);
-// work of `jobs` MSMs of n points in all at width c, in digit entries
-double window_work(double n, double jobs, int c, int encoding);
 // schedule of a plan (0 = default for each; msm_job's chunk, tree_quad,
 // tree_wide)
 struct Schedule {
@@ -231,6 +222,17 @@ struct Schedule {
     return tree_wide < o.tree_wide;
   }
 };
+
+int num_windows(int c, int encoding);
+int window_bits(int c, int encoding);
+int default_window(size_t n);                     // signed-digit model (msm_default_window)
+// the width c = 0 picks for an MSM of an encoding that is one of `jobs` run
+// together, among those whose workspace (on a schedule) is within `limit` bytes
+// (0: any); 0 when none is
+int default_window_for(size_t n, int encoding, size_t jobs = 1, size_t limit = 0,
+                       const Schedule& sched = Schedule());
+// work of `jobs` MSMs of n points in all at width c, in digit entries
+double window_work(double n, double jobs, int c, int encoding);
 
 // plan of a batch with job sizes ns[0..J); false for invalid sizes, c or
 // schedule values

@@ -169,7 +169,7 @@ static double window_cost(size_t n, int c, int encoding, size_t jobs, int cus) {
   return window_work((double)n, 1.0, c, encoding) + latency / (double)jobs;
 }
 
-int default_window_for(size_t n, int encoding, size_t jobs, size_t limit) {
+int default_window_for(size_t n, int encoding, size_t jobs, size_t limit, const Schedule& sched) {
   int best = 0;
   double best_cost = 1e300;
   const int cus = device_cus();
@@ -177,7 +177,7 @@ int default_window_for(size_t n, int encoding, size_t jobs, size_t limit) {
     if (num_windows(c, encoding) == 0) continue;
     if (limit) {
       Plan pl;
-      if (!make_plan(&n, 1, c, encoding, pl) || pl.bytes > limit) continue;
+      if (!make_plan(&n, 1, c, encoding, pl, sched) || pl.bytes > limit) continue;
     }
     const double cost = window_cost(n, c, encoding, jobs, cus);
     if (cost < best_cost) {
@@ -289,7 +289,7 @@ int plan_within(size_t n, int c, int encoding, size_t jobs, size_t limit, Plan& 
   const int pick = c == 0 ? default_window_for(n, encoding, jobs) : c;
   if (!make_plan(&n, 1, pick, encoding, pl, sched)) return MSM_EINVAL;
   if (pl.bytes <= limit) return MSM_OK;
-  const int fits = c == 0 ? default_window_for(n, encoding, jobs, limit) : 0;
+  const int fits = c == 0 ? default_window_for(n, encoding, jobs, limit, sched) : 0;
   return fits && make_plan(&n, 1, fits, encoding, pl, sched) && pl.bytes <= limit ? MSM_OK
                                                                                   : MSM_ENOSPC;
 }

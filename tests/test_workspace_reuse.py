@@ -48,3 +48,28 @@ def test_run_in_a_larger_size_s_workspace(enc, n, larger):
     ws.fill_(-1)
     got, flags = api.decode_result(api.to_host(api.msm_run(xyu, api.to_device(sw), n, 0, enc, ws=ws)))
     assert flags == 0 and got == msm.closed_form_words(sw, kw)
+
+
+@pytest.mark.gpu
+def test_server_fits_the_width_to_the_schedule():
+    """chunk = 4 takes more workspace at the picked width than the arena holds,
+    and less at another."""
+    n, sched = 20000, {"chunk": 4}
+
+    def need(c):
+        jobs = (_lib.MsmJob * 1)(_lib.MsmJob(16, 16, 16, n, c, 4, 0, 0))
+        return _lib.lib().msm_batch_workspace_bytes(jobs, 1, S)
+
+    budget = min(need(c) for c in range(4, 21))
+    assert need(api.default_window(n)) > budget > api.workspace_bytes(n, 0, S)
+    kw = inputs.nonzero_scalars_mod_r(91, n, stream=1)
+    sw = inputs.scalars_mod_r(91, n, stream=2)
+    xy, inf = api.gen_points(api.to_device(kw), n)
+    xyu, _ = api.points_prepare(xy, n, inf=inf)
+    res = api.words(api.MSM_RESULT_WORDS)
+    srv = api.Server(budget, streams=1)
+    srv.submit(xyu, api.to_device(sw), res, n, 0, sched)
+    srv.drain()
+    got, flags = api.decode_result(api.to_host(res))
+    srv.destroy()
+    assert flags == 0 and got == msm.closed_form_words(sw, kw)

@@ -139,6 +139,7 @@ constexpr uint32_t SORT_TILE = 8192;  // digits per pass-1 sort tile
 // unit, where `units` units give every SIMD one wave.
 struct AccumGeom {
   uint32_t units;  // lanes or quads of one wave per SIMD
+  uint32_t least;  // entries of a chunk, at least (a multiple of 4)
   uint32_t fixed;  // a schedule's chunk length (0: from the entries)
   uint32_t quad;   // a unit is a quad
 };
@@ -227,21 +228,27 @@ int num_windows(int c, int encoding);
 int window_bits(int c, int encoding);
 int default_window(size_t n);                     // signed-digit model (msm_default_window)
 // the width c = 0 picks for an MSM of an encoding that is one of `jobs` run
-// together, among those whose workspace (on a schedule) is within `limit` bytes
-// (0: any); 0 when none is
+// together, among those whose workspace (on a schedule, and compact: see
+// make_plan) is within `limit` bytes (0: any); 0 when none is
 int default_window_for(size_t n, int encoding, size_t jobs = 1, size_t limit = 0,
-                       const Schedule& sched = Schedule());
+                       const Schedule& sched = Schedule(), bool compact = false);
 // work of `jobs` MSMs of n points in all at width c, in digit entries
 double window_work(double n, double jobs, int c, int encoding);
 
+// Entries of an accumulation chunk, at least.  Four, the group in which keys are
+// read, give most units a chunk (13 us of accumulation at n = 33 against 108 with
+// sixteen).  A chunk's head and tail take 384 bytes, though, and with four entries
+// they are most of a small job's workspace: a compact plan has sixteen.
+constexpr uint32_t CHUNK_LEAST = 4, CHUNK_LEAST_COMPACT = 16;
+
 // plan of a batch with job sizes ns[0..J); false for invalid sizes, c or
-// schedule values
+// schedule values.  compact: less workspace, for callers who have no more
 bool make_plan(const size_t* ns, uint32_t J, int c, int encoding, Plan& pl,
-               const Schedule& sched = Schedule());
+               const Schedule& sched = Schedule(), bool compact = false);
 
 // plan of one MSM in `limit` bytes of workspace, at width c, or for c = 0 at the
-// width picked for one of `jobs`, or if that takes more at the best that fits:
-// MSM_OK, MSM_EINVAL (as make_plan) or MSM_ENOSPC
+// width picked for one of `jobs`, or if that takes more at the best that fits;
+// compact when nothing else fits: MSM_OK, MSM_EINVAL (as make_plan) or MSM_ENOSPC
 int plan_within(size_t n, int c, int encoding, size_t jobs, size_t limit, Plan& pl,
                 const Schedule& sched = Schedule());
 

@@ -65,7 +65,7 @@ __device__ __forceinline__ Chunks chunks_of(const AccumGeom& g, uint32_t E) {
   Chunks c = {g.fixed, 0u};
   if (g.fixed == 0) {
     const uint32_t units = accum_units(g, E);
-    c.K = max(4u, (E / units) & ~3u);
+    c.K = max(g.least, (E / units) & ~3u);
     const uint64_t even = (uint64_t)c.K * units;
     c.X = E > even ? (uint32_t)((E - even + 3) / 4) : 0u;
   }

@@ -151,9 +151,10 @@ static double window_cost(size_t n, int c, int encoding, size_t jobs, int cus) {
   const double points = encoding == MSM_DIGITS_GLV ? 2.0 * (double)n : (double)n;
   const double entries = points * W;
   const double all = std::min(entries * (double)jobs, 2147483648.0);
-  AccumGeom g = {0, 0, all <= (double)ACCUM_QUAD_MAX ? 1u : 0u};
+  AccumGeom g = {};
+  g.quad = all <= (double)ACCUM_QUAD_MAX ? 1u : 0u;
   g.units = (uint32_t)cus * 4u * (g.quad ? 16u : 64u);
-  const double chunk = std::max(4.0, all / accum_units(g, (uint32_t)all));
+  const double chunk = std::max((double)CHUNK_LEAST, all / accum_units(g, (uint32_t)all));
   // entries of one of the top window's digits, which run to the largest scalar's
   // (split half's), or of its carry alone
   const double largest = encoding == MSM_DIGITS_GLV ? std::ldexp((double)0x452217cc, 96)
@@ -169,7 +170,8 @@ static double window_cost(size_t n, int c, int encoding, size_t jobs, int cus) {
   return window_work((double)n, 1.0, c, encoding) + latency / (double)jobs;
 }
 
-int default_window_for(size_t n, int encoding, size_t jobs, size_t limit, const Schedule& sched) {
+int default_window_for(size_t n, int encoding, size_t jobs, size_t limit, const Schedule& sched,
+                       bool compact) {
   int best = 0;
   double best_cost = 1e300;
   const int cus = device_cus();
@@ -177,7 +179,7 @@ int default_window_for(size_t n, int encoding, size_t jobs, size_t limit, const 
     if (num_windows(c, encoding) == 0) continue;
     if (limit) {
       Plan pl;
-      if (!make_plan(&n, 1, c, encoding, pl, sched) || pl.bytes > limit) continue;
+      if (!make_plan(&n, 1, c, encoding, pl, sched, compact) || pl.bytes > limit) continue;
     }
     const double cost = window_cost(n, c, encoding, jobs, cus);
     if (cost < best_cost) {
@@ -191,7 +193,7 @@ int default_window_for(size_t n, int encoding, size_t jobs, size_t limit, const 
 int default_window(size_t n) { return default_window_for(n, MSM_DIGITS_SIGNED); }
 
 bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
-               const Schedule& sched) {
+               const Schedule& sched, bool compact) {
   pl = Plan();
   const int W = num_windows(c_req, encoding);
   if (W == 0 || J == 0 || !ns) return false;
@@ -230,14 +232,16 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
     pl.one.tps = (uint32_t)((mult * ns[0] + pl.tile_digits - 1) / pl.tile_digits);
   }
   // accumulation chunks (AccumGeom): at most one per unit, each of at least
-  // four entries, or all of a schedule's length
+  // `least` entries, or all of a schedule's length
   const size_t simds = (size_t)device_cus() * 4;
   if (sched.chunk) pl.accum.fixed = ((uint32_t)std::max(4, sched.chunk) + 3u) & ~3u;
+  pl.accum.least = compact ? CHUNK_LEAST_COMPACT : CHUNK_LEAST;
   pl.accum.quad = pl.NW <= ACCUM_QUAD_MAX ? 1u : 0u;
   pl.accum.units = (uint32_t)(simds * (pl.accum.quad ? 16 : 64));
   pl.chunks = pl.accum.fixed
                   ? (pl.NW + pl.accum.fixed - 1) / pl.accum.fixed
-                  : std::min<size_t>(accum_units(pl.accum, (uint32_t)pl.NW), (pl.NW + 3) / 4);
+                  : std::min<size_t>(accum_units(pl.accum, (uint32_t)pl.NW),
+                                     (pl.NW + pl.accum.least - 1) / pl.accum.least);
   pl.long_items = pl.chunks / 8 + 1;
   pl.long_segs = pl.long_items + pl.chunks / 128;
   size_t o = 0;
@@ -252,18 +256,20 @@ bool make_plan(const size_t* ns, uint32_t J, int c_req, int encoding, Plan& pl,
   pl.o_offsets = take((pl.M + pl.S) * 4);
   pl.o_counts = take(pl.ncounts * 4);
   pl.o_blocksums = take(4096 * 4);
+  // large sort partitions: each holds more than SORT_PART_CAP entries, so
+  // there are at most NW / SORT_PART_CAP of them, and NW / SORT_BIG_ITEM +
+  // that many items; their 512 counts each take the place of the digits (more),
+  // which pass 1 has read
+  const size_t nbig_max = pl.NW / SORT_PART_CAP;
+  static_assert(SORT_PART_CAP >= 512, "");
   pl.o_digits = take(pl.NW * 4);
+  pl.o_bigsum = pl.o_digits;
   pl.o_tmp = take(pl.NW * 8);
   pl.o_key = take(pl.NW * 4 + 32);  // + 16-byte groups read past the end
   pl.o_idx = take(pl.NW * 4 + 32);
   pl.o_longlist = take((2 + 2 * pl.long_items + 2 * pl.long_segs) * 4);
-  // large sort partitions: each holds more than SORT_PART_CAP entries, so
-  // there are at most NW / SORT_PART_CAP of them, and NW / SORT_BIG_ITEM +
-  // that many items
-  const size_t nbig_max = pl.NW / SORT_PART_CAP + 1;
   pl.o_counters = take(SORT_COUNTERS * 4);
   pl.o_bigdesc = take(nbig_max * 16);
-  pl.o_bigsum = take(nbig_max * 512 * 4);
   pl.o_bigcnt = take((pl.NW / SORT_BIG_ITEM + nbig_max + 1) * 256 * 4);
   pl.o_bigitem = take((pl.NW / SORT_BIG_ITEM + nbig_max + 1) * 4);
   // buckets, then the tree levels ping-pong between lvl0 (level 0's M
@@ -289,9 +295,11 @@ int plan_within(size_t n, int c, int encoding, size_t jobs, size_t limit, Plan& 
   const int pick = c == 0 ? default_window_for(n, encoding, jobs) : c;
   if (!make_plan(&n, 1, pick, encoding, pl, sched)) return MSM_EINVAL;
   if (pl.bytes <= limit) return MSM_OK;
-  const int fits = c == 0 ? default_window_for(n, encoding, jobs, limit, sched) : 0;
-  return fits && make_plan(&n, 1, fits, encoding, pl, sched) && pl.bytes <= limit ? MSM_OK
-                                                                                  : MSM_ENOSPC;
+  for (const bool compact : {false, true}) {
+    const int w = c == 0 ? default_window_for(n, encoding, jobs, limit, sched, compact) : c;
+    if (w && make_plan(&n, 1, w, encoding, pl, sched, compact) && pl.bytes <= limit) return MSM_OK;
+  }
+  return MSM_ENOSPC;
 }
 
 int enqueue_msm(const Plan& pl, void* ws, hipStream_t st, hipEvent_t accum_after) {
@@ -403,14 +411,13 @@ int msm_gen_points(const uint32_t* k, size_t n, uint32_t* xy_std, uint32_t* inf,
 int msm_bucket_accumulate(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c,
                           int encoding, uint32_t* buckets, void* ws, size_t ws_bytes,
                           void* stream) {
-  if (!xyu || !scalars || !buckets || !ws) return MSM_EINVAL;
+  if (!xyu || !scalars || !buckets || !ws || c == 0) return MSM_EINVAL;
   Plan pl;
-  if (!make_plan(&n, 1, c, encoding, pl)) return MSM_EINVAL;
-  if (ws_bytes < pl.bytes) return MSM_ENOSPC;
+  int rc = plan_within(n, c, encoding, 1, ws_bytes, pl);
+  if (rc != MSM_OK) return rc;
   pl.one.xyu = xyu;
   pl.one.scalars = scalars;
   hipStream_t st = (hipStream_t)stream;
-  int rc;
   {
     ProfScope prof(PT_SORT, st);
     rc = launch_sort(pl, buckets, ws, st);

@@ -73,3 +73,38 @@ def test_server_fits_the_width_to_the_schedule():
     got, flags = api.decode_result(api.to_host(res))
     srv.destroy()
     assert flags == 0 and got == msm.closed_form_words(sw, kw)
+
+
+# bytes that chunks of at least 16 entries need, on quads and on lanes
+COMPACT = [(G, 468, 2, 2766336), (S, 1000, 8, 3049472), (S, 20000, 8, 30170880)]
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="would launch on made-up pointers")
+@pytest.mark.parametrize("enc,n,c,nbytes", COMPACT)
+def test_longer_chunks_where_there_is_less(enc, n, c, nbytes):
+    lib, p = _lib.lib(), ctypes.c_void_p(256)
+    assert nbytes < lib.msm_workspace_bytes(n, c, enc)
+    assert _host_status(n, enc, nbytes, c) == _lib.MSM_EHIP
+    assert lib.msm_bucket_accumulate(p, p, n, c, enc, p, p, nbytes, None) == _lib.MSM_EHIP
+    assert _host_status(n, enc, nbytes // 2, c) == _lib.MSM_ENOSPC
+    assert lib.msm_bucket_accumulate(p, p, n, c, enc, p, p, nbytes // 2, None) == _lib.MSM_ENOSPC
+    assert lib.msm_bucket_accumulate(p, p, n, 0, enc, p, p, nbytes, None) == _lib.MSM_EINVAL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ones", [False, True])
+@pytest.mark.parametrize("enc,n,c,nbytes", COMPACT)
+def test_run_in_longer_chunks(enc, n, c, nbytes, ones):
+    """ones: half the scalars are 1, a bucket over many chunks."""
+    ws = api.words(nbytes // 4 + 64)
+    ws.fill_(-1)
+    kw = inputs.nonzero_scalars_mod_r(92 + n, n, stream=1)
+    sw = inputs.scalars_mod_r(92 + n, n, stream=2)
+    if ones:
+        sw[: n // 2] = inputs.ints_to_words([1], 8)
+    xy, inf = api.gen_points(api.to_device(kw), n)
+    xyu, _ = api.points_prepare(xy, n, inf=inf, endo=enc == G)
+    got, flags = api.decode_result(api.to_host(
+        api.msm_run(xyu, api.to_device(sw), n, c, enc, ws=ws[:nbytes // 4])))
+    assert flags == 0 and got == msm.closed_form_words(sw, kw)
+    assert bool((ws[nbytes // 4:] == -1).all())  # nothing beyond the workspace

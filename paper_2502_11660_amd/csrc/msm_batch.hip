@@ -93,7 +93,7 @@ std::map<int, int> join_widths(std::map<int, WidthSum> sums, int encoding) {
   }
 }
 
-// classes of a job list: (window width, schedule) -> job indices (in job order)
+// classes of a job list -> job indices (given widths first, then c = 0)
 bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls) {
   if (!jobs || njobs == 0 || njobs >= ((size_t)1 << 20)) return false;
   std::map<Schedule, std::map<int, WidthSum>> picked;
@@ -116,24 +116,26 @@ bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls) {
     double slots = 0, buckets = 0;
   };
   std::map<std::pair<int, Schedule>, Part> parts;
-  for (size_t i = 0; i < njobs; ++i) {
-    const Schedule sched = schedule_of(jobs[i]);
-    const int c = jobs[i].c == 0 ? joined[sched][width[i]] : width[i];
-    const double W = num_windows(c, encoding);
-    const double slots = (encoding == MSM_DIGITS_GLV ? 2.0 : 1.0) * (double)jobs[i].n * W;
-    const double buckets = std::ldexp(W, window_bits(c, encoding));
-    Part& p = parts[std::make_pair(c, sched)];
-    if (jobs[i].c == 0 && p.slots > 0 &&
-        (p.slots + slots > CLASS_SLOTS || p.buckets + buckets > CLASS_BUCKETS)) {
-      ++p.index;
-      p.slots = p.buckets = 0;
-    }
-    if (jobs[i].c == 0 || p.index == 0) {
+  // the jobs of given widths first, all in part 0 of theirs; then those with
+  // c = 0, which see how full it is
+  for (const bool given : {true, false})
+    for (size_t i = 0; i < njobs; ++i) {
+      if ((jobs[i].c != 0) != given) continue;
+      const Schedule sched = schedule_of(jobs[i]);
+      const int c = given ? width[i] : joined[sched][width[i]];
+      const double W = num_windows(c, encoding);
+      const double slots = (encoding == MSM_DIGITS_GLV ? 2.0 : 1.0) * (double)jobs[i].n * W;
+      const double buckets = std::ldexp(W, window_bits(c, encoding));
+      Part& p = parts[std::make_pair(c, sched)];
+      if (!given && p.slots > 0 &&
+          (p.slots + slots > CLASS_SLOTS || p.buckets + buckets > CLASS_BUCKETS)) {
+        ++p.index;
+        p.slots = p.buckets = 0;
+      }
       p.slots += slots;
       p.buckets += buckets;
+      cls[ClassKey(c, sched, p.index)].push_back(i);
     }
-    cls[ClassKey(c, sched, jobs[i].c == 0 ? p.index : 0)].push_back(i);
-  }
   return true;
 }
 

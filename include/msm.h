@@ -294,7 +294,8 @@ int msm_run_noalloc(const uint32_t* xyu, const uint32_t* scalars, size_t n, int 
  * points in place, not move them.
  *
  * msm_batch_workspace_bytes: device bytes a batch of these jobs needs
- *   (0 for invalid jobs).
+ *   (0 for invalid jobs).  msm_batch_create also takes less where longer chunks
+ *   (as msm_run) or one width for all jobs with c = 0 fit.
  * msm_batch_create: validates and plans the jobs, copies their tables into
  *   ws (a synchronous host-to-device copy; ws must stay allocated and
  *   untouched until msm_batch_destroy) and creates the internal streams.

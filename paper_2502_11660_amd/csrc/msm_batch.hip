@@ -93,8 +93,9 @@ std::map<int, int> join_widths(std::map<int, WidthSum> sums, int encoding) {
   }
 }
 
-// classes of a job list -> job indices (given widths first, then c = 0)
-bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls) {
+// classes of a job list -> job indices (given widths first, then c = 0; those at
+// width `all` when it is not 0)
+bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls, int all = 0) {
   if (!jobs || njobs == 0 || njobs >= ((size_t)1 << 20)) return false;
   std::map<Schedule, std::map<int, WidthSum>> picked;
   std::vector<int> width(njobs);
@@ -102,7 +103,7 @@ bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls) {
     const msm_job& jb = jobs[i];
     if (!jb.xyu || !jb.scalars || !jb.result || jb.n == 0) return false;
     if (jb.chunk < 0 || jb.tree_quad < 0 || jb.tree_wide < 0) return false;
-    width[i] = jb.c == 0 ? default_window_for(jb.n, encoding, njobs) : jb.c;
+    width[i] = jb.c ? jb.c : (all ? all : default_window_for(jb.n, encoding, njobs));
     if (num_windows(width[i], encoding) == 0) return false;
     if (jb.c != 0) continue;
     WidthSum& w = picked[schedule_of(jb)][width[i]];
@@ -140,20 +141,44 @@ bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls) {
 }
 
 bool plan_classes(const msm_job* jobs, const Classes& cls, int encoding, std::vector<Plan>& plans,
-                  std::vector<size_t>& off, size_t& total) {
+                  std::vector<size_t>& off, size_t& total, bool compact = false) {
+  plans.clear();
+  off.clear();
   total = 0;
   for (const auto& kv : cls) {
     std::vector<size_t> ns;
     for (size_t i : kv.second) ns.push_back(jobs[i].n);
     Plan pl;
     if (!make_plan(ns.data(), (uint32_t)ns.size(), std::get<0>(kv.first), encoding, pl,
-                   std::get<1>(kv.first)))
+                   std::get<1>(kv.first), compact))
       return false;
     plans.push_back(pl);
     off.push_back(total);
     total += align256(pl.bytes);
   }
   return true;
+}
+
+// Classes and plans of a batch in `limit` bytes.  A workspace of
+// msm_batch_workspace_bytes holds those picked for speed.  One sized for other jobs
+// (more of them or more points, whose picks may need less) perhaps only compact
+// plans, or those of all jobs with c = 0 at one width: the widest that fits.
+int plan_within(const msm_job* jobs, size_t njobs, int encoding, size_t limit, Classes& cls,
+                std::vector<Plan>& plans, std::vector<size_t>& off) {
+  auto fits = [&](int all, bool compact, bool& valid) {
+    size_t total = 0;
+    cls.clear();
+    valid = classify(jobs, njobs, encoding, cls, all) &&
+            plan_classes(jobs, cls, encoding, plans, off, total, compact);
+    return valid && total <= limit;
+  };
+  bool valid = false;
+  if (fits(0, false, valid)) return MSM_OK;
+  if (!valid) return MSM_EINVAL;
+  if (fits(0, true, valid)) return MSM_OK;
+  for (int c = 20; c >= 4; --c)
+    if (fits(c, true, valid)) return MSM_OK;
+  return MSM_ENOSPC;
 }
 
 int enqueue_batch(msm_batch* b, hipStream_t st) {
@@ -186,10 +211,9 @@ void release(msm_batch* b) {
 int create(const msm_job* jobs, size_t njobs, int encoding, void* ws, size_t ws_bytes,
            int use_graph, msm_batch* b) {
   Classes cls;
-  if (!ws || !classify(jobs, njobs, encoding, cls)) return MSM_EINVAL;
-  size_t total = 0;
-  if (!plan_classes(jobs, cls, encoding, b->plans, b->ws_off, total)) return MSM_EINVAL;
-  if (ws_bytes < total) return MSM_ENOSPC;
+  if (!ws) return MSM_EINVAL;
+  const int rc = plan_within(jobs, njobs, encoding, ws_bytes, cls, b->plans, b->ws_off);
+  if (rc != MSM_OK) return rc;
   HIPCHK(hipGetDevice(&b->device));
   b->ws = static_cast<char*>(ws);
   b->use_graph = use_graph != 0;

@@ -382,7 +382,9 @@ int msm_server_destroy(msm_server* server);
  *     bucket accumulation kernel), "merge" (split-bucket merge), "agg"
  *     (bucket aggregation), "horner" (group aggregation and the affine
  *     result).  Each event record stalls the stream briefly between kernels,
- *     so this mode adds several microseconds per phase boundary.
+ *     so this mode adds several microseconds per phase boundary.  Jobs small
+ *     enough for one kernel up to their window sums have that as "accum", and
+ *     no "sort", "merge" or "agg".
  *   MSM_PROFILE_ACCUM_KERNEL (2): only "accum", from start and stop events
  *     attached to the accumulation kernel's own dispatch: no event records
  *     between kernels, so the stream runs as it does unprofiled.

@@ -9,6 +9,8 @@
 // quads that hold them, and window_tail does the levels.  Bound by the latency
 // of those additions, one wave a SIMD of a compute unit: n = 33, signed digits,
 // five launches of 51 us -> one of 37 (251.7 -> 238.4 us in all).
+#include <hip/hip_ext.h>
+
 #include <algorithm>
 
 #include "common.hpp"
@@ -151,16 +153,28 @@ __global__ void __launch_bounds__(TAIL_THREADS) k_segment(
 }  // namespace
 
 int launch_segments(const Plan& pl, void* ws, hipStream_t st) {
-  ProfScope prof(PT_ACCUM, st);
   const uint32_t bb = (uint32_t)pl.bb;
   size_t second = 0;
   const size_t first = tail_words(0, bb, second);
   const size_t words = std::max(seg_words(bb, (uint32_t)pl.max_n), first + second);
-  k_segment<<<(unsigned)pl.S, TAIL_THREADS, words * 4, st>>>(
-      job_view(pl, ws), pl.one.xyu, pl.J == 1 ? nullptr : ws_at<const int64_t>(ws, pl.o_segoff),
-      (uint32_t)pl.W, bb, pl.c, pl.encoding, small_bias(pl), (uint32_t)first,
-      ws_at<uint32_t>(ws, pl.o_buckets), ws_at<uint32_t>(ws, pl.o_flags),
-      ws_at<uint32_t>(ws, pl.o_wsum));
+  const JobView jv = job_view(pl, ws);
+  const int64_t* segoff = pl.J == 1 ? nullptr : ws_at<const int64_t>(ws, pl.o_segoff);
+  const Bias bias = small_bias(pl);
+  uint32_t* buckets = ws_at<uint32_t>(ws, pl.o_buckets);
+  uint32_t* flags = ws_at<uint32_t>(ws, pl.o_flags);
+  uint32_t* wsum = ws_at<uint32_t>(ws, pl.o_wsum);
+  const uint32_t W = (uint32_t)pl.W, S = (uint32_t)pl.S, lds = (uint32_t)(words * 4);
+  hipEvent_t ea = nullptr, eb = nullptr;
+  if (prof_kernel_events(PT_ACCUM, st, &ea, &eb)) {
+    hipExtLaunchKernelGGL(k_segment, dim3(S), dim3(TAIL_THREADS), lds, st, ea, eb, 0, jv,
+                          pl.one.xyu, segoff, W, bb, pl.c, pl.encoding, bias, (uint32_t)first,
+                          buckets, flags, wsum);
+    prof_kernel_record(PT_ACCUM, ea, eb);
+  } else {
+    ProfScope prof(PT_ACCUM, st);
+    k_segment<<<S, TAIL_THREADS, lds, st>>>(jv, pl.one.xyu, segoff, W, bb, pl.c, pl.encoding, bias,
+                                            (uint32_t)first, buckets, flags, wsum);
+  }
   HIPCHK(hipGetLastError());
   return MSM_OK;
 }

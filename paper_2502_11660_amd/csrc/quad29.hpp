@@ -23,8 +23,8 @@
 namespace msm {
 
 // 2^385 mod p in words: the factor whose product with Z1 is the D = 2 Z1
-// 2^384 2^-406 of a prepared point
-__device__ const uint32_t kTwoR[NL] = {
+// 2^384 2^-406 of a prepared point; read like a record's coordinate, in 16-byte loads
+__device__ const uint32_t __align__(16) kTwoR[NL] = {
     0xfffffed0u, 0x059bffffu, 0xffffff62u, 0xa2813f06u, 0x14fa7fe4u, 0x3efb6753u,
     0xdcf8c60bu, 0xf69d2f6eu, 0x007909d0u, 0x99e92b7fu, 0xc5fbe934u, 0x011accc3u};
 

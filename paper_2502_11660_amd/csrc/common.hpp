@@ -279,10 +279,10 @@ inline JobView job_view(const Plan& pl, void* ws) {
 // ncounts, nb for jobs of mult * ns[j] points
 void sort_geometry(Plan& pl, const size_t* ns, uint32_t J, size_t mult);
 int launch_sort(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st);
-// k_accum.hip: bucket accumulation and split-bucket merge (signed records,
-// fe29.hpp), and their conversion to coordinates in [0, 2p) in place
-int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st);
-int launch_records_unsigned(uint32_t* recs, size_t n, hipStream_t st);
+// k_accum.hip: bucket accumulation and split-bucket merge, buckets as signed
+// records (fe29.hpp) or with coordinates in [0, 2p)
+int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st,
+                      bool unsigned_buckets = false);
 // k_agg.hip: bucket aggregation (window sums), group aggregation and the
 // affine results of every job
 int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStream_t st);

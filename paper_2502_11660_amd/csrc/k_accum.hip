@@ -14,6 +14,12 @@
 // tail[c0] + head[c0+1] + ... + head[c1]: one quad sums it when the span
 // c1 - c0 is small; longer spans are cut into segments that many blocks fold.
 //
+// Buckets are stored as signed records (fe29.hpp) for the aggregation tree, or, UNS,
+// with coordinates in [0, 2p), what the caller of msm_bucket_accumulate gets: at the
+// store, because a pass over all buckets afterwards reads and writes the empty ones
+// too (plain digits, c = 20, 13.6 M buckets: one point 1.72 ms with it, 0.77 without;
+// 2^20 points 3.69, 2.78).  Pieces are of the same form as their buckets; merges read both.
+//
 // A chunk is summed by one lane, or, when there are too few entries to give
 // every SIMD a wave of lanes a few entries each, by one quad (quad29.hpp).
 #include <hip/hip_ext.h>
@@ -82,14 +88,18 @@ __device__ __forceinline__ Chunks chunks_of(const AccumGeom& g, uint32_t E) {
 // (9.4 G entries/s) with a column's multiply-adds in one block.  Waves per SIMD:
 // see accum_units; four measured no faster than three.  (Reading keys and
 // indices in groups of four cut the kernel's HBM reads by 31%.)
-__global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
-                                                 const int64_t* __restrict__ segoff, uint32_t bb,
-                                                 const uint32_t* __restrict__ key,
-                                                 const uint32_t* __restrict__ idx,
-                                                 const uint32_t* __restrict__ total, AccumGeom g,
-                                                 uint32_t* __restrict__ buckets,
-                                                 uint32_t* __restrict__ head,
-                                                 uint32_t* __restrict__ tail) {
+template <bool UNS>
+__device__ __forceinline__ void accum_chunk(const uint32_t* __restrict__ pts,
+                                            const int64_t* __restrict__ segoff, uint32_t bb,
+                                            const uint32_t* __restrict__ key,
+                                            const uint32_t* __restrict__ idx,
+                                            const uint32_t* __restrict__ total, const AccumGeom& g,
+                                            uint32_t* __restrict__ buckets,
+                                            uint32_t* __restrict__ head,
+                                            uint32_t* __restrict__ tail) {
+  auto store = [](uint32_t* dst, const xytz29& v) {
+    st_xytz(dst, UNS ? pt29_to_unsigned(v) : pt29_to_words(v));
+  };
   const uint32_t E1 = *total;
   const Chunks c = chunks_of(g, E1);
   const uint32_t ch = blockIdx.x * blockDim.x + threadIdx.x;
@@ -136,7 +146,7 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
     if (k != cur) {
       uint32_t* dst = (first_seg && open_left) ? head + (size_t)ch * XYTZ_WORDS
                                                : buckets + (size_t)cur * XYTZ_WORDS;
-      if (cur != KEY_NONE) st_xytz(dst, pt29_to_words(acc));
+      if (cur != KEY_NONE) store(dst, acc);
       acc = pt29_identity();
       cur = k;
       first_seg = false;
@@ -155,8 +165,20 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
     dst = tail + (size_t)ch * XYTZ_WORDS;
   else
     dst = buckets + (size_t)cur * XYTZ_WORDS;
-  st_xytz(dst, pt29_to_words(acc));
+  store(dst, acc);
 }
+
+#define ACCUM_KERNEL(name, UNS)                                                          \
+  __global__ void __launch_bounds__(256) name(                                           \
+      const uint32_t* __restrict__ pts, const int64_t* __restrict__ segoff, uint32_t bb, \
+      const uint32_t* __restrict__ key, const uint32_t* __restrict__ idx,                \
+      const uint32_t* __restrict__ total, AccumGeom g, uint32_t* __restrict__ buckets,   \
+      uint32_t* __restrict__ head, uint32_t* __restrict__ tail) {                        \
+    accum_chunk<UNS>(pts, segoff, bb, key, idx, total, g, buckets, head, tail);          \
+  }
+ACCUM_KERNEL(k_accum, false)
+ACCUM_KERNEL(k_accum_unsigned, true)
+#undef ACCUM_KERNEL
 
 // The same with one quad per chunk, for up to ACCUM_QUAD_MAX digit slots: the
 // time is then that of one wave's dependent additions (~2.1 us each here,
@@ -165,6 +187,7 @@ __global__ void __launch_bounds__(256) k_accum(const uint32_t* __restrict__ pts,
 // digits: 108 us on lanes of 16 entries -> 13 us; n = 4099, split digits
 // (123 K slots): 112 -> 27 us.  At 2^18 slots both take ~30 us (16 entries a
 // quad, 4 a lane), and above the quads' 1.4 times as many instructions cost.
+template <bool UNS>
 __global__ void __launch_bounds__(256) k_accum_quad(const uint32_t* __restrict__ pts,
                                                       const int64_t* __restrict__ segoff,
                                                       uint32_t bb,
@@ -212,7 +235,7 @@ __global__ void __launch_bounds__(256) k_accum_quad(const uint32_t* __restrict__
     if (k != cur) {
       uint32_t* dst = (first_seg && open_left) ? head + (size_t)ch * XYTZ_WORDS
                                                : buckets + (size_t)cur * XYTZ_WORDS;
-      if (cur != KEY_NONE) quad_st(dst, acc);
+      if (cur != KEY_NONE) quad_st_as<UNS>(dst, acc);
       acc = quad_identity();
       cur = k;
       first_seg = false;
@@ -231,7 +254,7 @@ __global__ void __launch_bounds__(256) k_accum_quad(const uint32_t* __restrict__
     dst = tail + (size_t)ch * XYTZ_WORDS;
   else
     dst = buckets + (size_t)cur * XYTZ_WORDS;
-  quad_st(dst, acc);
+  quad_st_as<UNS>(dst, acc);
 }
 
 // chunk ch holds a tail partial: returns true, the bucket and its last chunk
@@ -283,6 +306,7 @@ constexpr uint32_t MERGE_PARTS = (MERGE_CHUNKS + SMALL_SPAN) / 2;  // of several
 constexpr uint32_t MERGE_PAIRS = 64;  // a span of R > 1 runs has R / 2 <= n / 4
 static_assert(MERGE_CHUNKS + SMALL_SPAN <= 4 * MERGE_PAIRS && MERGE_RUNS < 256, "");
 
+template <bool UNS>
 __global__ void __launch_bounds__(256) k_merge(const uint32_t* __restrict__ key,
                                                const uint32_t* __restrict__ offsets,
                                                const uint32_t* __restrict__ total, uint32_t bb,
@@ -362,7 +386,7 @@ __global__ void __launch_bounds__(256) k_merge(const uint32_t* __restrict__ key,
       acc = quad_add(acc, r);
     }
     if (at == 0xffu) {
-      quad_st(buckets + (size_t)t.y * XYTZ_WORDS, acc);
+      quad_st_as<UNS>(buckets + (size_t)t.y * XYTZ_WORDS, acc);
     } else {
 #pragma unroll
       for (int k = 0; k < NL29; ++k) part[at][q][k] = acc.v[k];
@@ -385,7 +409,7 @@ __global__ void __launch_bounds__(256) k_merge(const uint32_t* __restrict__ key,
       }
       l = quad_add(l, r);
       if (half == 1) {
-        quad_st(buckets + (size_t)t.y * XYTZ_WORDS, l);
+        quad_st_as<UNS>(buckets + (size_t)t.y * XYTZ_WORDS, l);
       } else {
 #pragma unroll
         for (int k = 0; k < NL29; ++k) part[at][q][k] = l.v[k];
@@ -432,6 +456,7 @@ __device__ __forceinline__ fe29 block_sum(const uint32_t* __restrict__ rec, uint
 // took 267 us for n = 300 K with half the scalars 0 or 1, this 56).  The block that finishes
 // an item's last segment sums the segments' results, left in the place of
 // their first heads, and adds the tail.
+template <bool UNS>
 __global__ void __launch_bounds__(256) k_merge_long(const uint32_t* __restrict__ key,
                                                     const uint32_t* __restrict__ offsets,
                                                     const uint32_t* __restrict__ total,
@@ -469,30 +494,14 @@ __global__ void __launch_bounds__(256) k_merge_long(const uint32_t* __restrict__
       sum = block_sum(first, segs, SEG_HEADS, part);
     }
     if (threadIdx.x < 4)
-      quad_st(buckets + (size_t)b * XYTZ_WORDS,
-              quad_add(quad_ld(tail + (size_t)ch * XYTZ_WORDS), sum));
+      quad_st_as<UNS>(buckets + (size_t)b * XYTZ_WORDS,
+                      quad_add(quad_ld(tail + (size_t)ch * XYTZ_WORDS), sum));
     __syncthreads();
   }
 }
 
-// One coordinate per lane: signed records (fe29.hpp) -> coordinates in
-// [0, 2p), the form the caller of msm_bucket_accumulate gets.
-__global__ void __launch_bounds__(256) k_records_unsigned(uint32_t* __restrict__ recs, size_t n) {
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i >= 4 * n) return;
-  uint32_t* rec = recs + i * NL;
-  st_aos(rec, 0, fe_unsigned(ld_aos(rec, 0)));
-}
-
-}  // namespace
-
-int launch_records_unsigned(uint32_t* recs, size_t n, hipStream_t st) {
-  k_records_unsigned<<<(unsigned)((4 * n + 255) / 256), 256, 0, st>>>(recs, n);
-  HIPCHK(hipGetLastError());
-  return MSM_OK;
-}
-
-int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st) {
+template <bool UNS>
+int accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st) {
   const uint32_t* offsets = ws_at<uint32_t>(ws, pl.o_offsets);
   const uint32_t* total = ws_at<uint32_t>(ws, pl.o_total);
   const uint32_t* key = ws_at<uint32_t>(ws, pl.o_key);
@@ -505,7 +514,7 @@ int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t s
   const uint32_t bb = (uint32_t)pl.bb;
   const AccumGeom g = pl.accum;
   const unsigned grid = grid_for((g.quad ? 4 : 1) * pl.chunks, 256);
-  const auto kernel = g.quad ? k_accum_quad : k_accum;
+  const auto kernel = g.quad ? k_accum_quad<UNS> : (UNS ? k_accum_unsigned : k_accum);
   hipEvent_t ea = nullptr, eb = nullptr;
   if (prof_kernel_events(PT_ACCUM, st, &ea, &eb)) {
     // timed by events attached to the dispatch itself
@@ -517,11 +526,20 @@ int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t s
     kernel<<<grid, 256, 0, st>>>(pl.one.xyu, segoff, bb, key, idx, total, g, buckets, head, tail);
   }
   ProfScope prof(PT_MERGE, st);
-  k_merge<<<grid_for(pl.chunks, MERGE_CHUNKS), 256, 0, st>>>(key, offsets, total, bb, g, head, tail, buckets, list);
-  k_merge_long<<<(unsigned)std::min<size_t>(1024, pl.long_segs), 256, 0, st>>>(
+  k_merge<UNS><<<grid_for(pl.chunks, MERGE_CHUNKS), 256, 0, st>>>(key, offsets, total, bb, g, head,
+                                                                  tail, buckets, list);
+  k_merge_long<UNS><<<(unsigned)std::min<size_t>(1024, pl.long_segs), 256, 0, st>>>(
       key, offsets, total, bb, g, head, tail, buckets, list);
   HIPCHK(hipGetLastError());
   return MSM_OK;
+}
+
+}  // namespace
+
+int launch_accumulate(const Plan& pl, uint32_t* buckets, void* ws, hipStream_t st,
+                      bool unsigned_buckets) {
+  return unsigned_buckets ? accumulate<true>(pl, buckets, ws, st)
+                          : accumulate<false>(pl, buckets, ws, st);
 }
 
 }  // namespace msm

@@ -423,8 +423,7 @@ int msm_bucket_accumulate(const uint32_t* xyu, const uint32_t* scalars, size_t n
     rc = launch_sort(pl, buckets, ws, st);
   }
   if (rc != MSM_OK) return rc;
-  if ((rc = launch_accumulate(pl, buckets, ws, st)) != MSM_OK) return rc;
-  return launch_records_unsigned(buckets, pl.M, st);
+  return launch_accumulate(pl, buckets, ws, st, true);
 }
 
 int msm_run(const uint32_t* xyu, const uint32_t* scalars, size_t n, int c, int encoding,

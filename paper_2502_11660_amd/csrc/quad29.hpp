@@ -139,5 +139,12 @@ __device__ __forceinline__ void quad_st(uint32_t* __restrict__ rec, const fe29& 
 __device__ __forceinline__ void quad_st_unsigned(uint32_t* __restrict__ rec, const fe29& v) {
   st_aos(rec, (int)quad_lane(), fe_unsigned(f29_to_words(v)));
 }
+template <bool UNS>
+__device__ __forceinline__ void quad_st_as(uint32_t* __restrict__ rec, const fe29& v) {
+  if (UNS)
+    quad_st_unsigned(rec, v);
+  else
+    quad_st(rec, v);
+}
 
 }  // namespace msm

@@ -90,27 +90,36 @@ namespace msm {
   if constexpr (NA == na && NM == nm)                              \
     MSM_MAD_ASM("v_mad_i64_i32", n, MSM_MADV_##na, MSM_MADS_##nm);
 
+// the numbers of products that there are blocks for (V: x y, S: u q, VS: both)
+#define MSM_MAD_LIST(V, S, VS)                                                              \
+  V(1) V(2) V(3) V(4) V(5) V(6) V(7) V(8) V(9) V(10) V(11) V(12) V(13) V(14)                \
+  S(1) S(2) S(3) S(4) S(5) S(6) S(7) S(8) S(9) S(10) S(11) S(12) S(13) S(14)                \
+  VS(1, 1, 2) VS(1, 2, 3) VS(2, 1, 3) VS(2, 2, 4) VS(2, 3, 5) VS(3, 2, 5) VS(3, 3, 6)       \
+  VS(3, 4, 7) VS(4, 3, 7) VS(4, 4, 8) VS(4, 5, 9) VS(5, 4, 9) VS(5, 5, 10) VS(5, 6, 11)     \
+  VS(6, 5, 11) VS(6, 6, 12) VS(6, 7, 13) VS(7, 6, 13) VS(7, 7, 14) VS(7, 8, 15)             \
+  VS(8, 7, 15) VS(8, 8, 16) VS(8, 9, 17) VS(9, 8, 17) VS(9, 9, 18) VS(9, 10, 19)            \
+  VS(10, 9, 19) VS(10, 10, 20) VS(10, 11, 21) VS(11, 10, 21) VS(11, 11, 22) VS(11, 12, 23)  \
+  VS(12, 11, 23) VS(12, 12, 24) VS(13, 12, 25)
+#define MSM_MAD_IS_V(na) +(NA == na && NM == 0)
+#define MSM_MAD_IS_S(nm) +(NA == 0 && NM == nm)
+#define MSM_MAD_IS_VS(na, nm, n) +(NA == na && NM == nm)
+
 // acc += sum of NA products x[t] y[t] and NM products u[t] q[t] (q in SGPRs)
 template <bool SIGNED, int NA, int NM, typename A, typename W>
 __device__ __forceinline__ void mad64_block(A& acc, const W* x, const W* y, const W* u,
                                             const W* q) {
+  static_assert(0 MSM_MAD_LIST(MSM_MAD_IS_V, MSM_MAD_IS_S, MSM_MAD_IS_VS) == 1,
+                "no block for these numbers of products");
+  static_assert(SIGNED || NA == 0 || NM == 0, "blocks of both kinds are signed");
   uint64_t cc;
-  MSM_MAD_V(1) MSM_MAD_V(2) MSM_MAD_V(3) MSM_MAD_V(4) MSM_MAD_V(5) MSM_MAD_V(6) MSM_MAD_V(7)
-  MSM_MAD_V(8) MSM_MAD_V(9) MSM_MAD_V(10) MSM_MAD_V(11) MSM_MAD_V(12) MSM_MAD_V(13) MSM_MAD_V(14)
-  MSM_MAD_S(1) MSM_MAD_S(2) MSM_MAD_S(3) MSM_MAD_S(4) MSM_MAD_S(5) MSM_MAD_S(6) MSM_MAD_S(7)
-  MSM_MAD_S(8) MSM_MAD_S(9) MSM_MAD_S(10) MSM_MAD_S(11) MSM_MAD_S(12) MSM_MAD_S(13) MSM_MAD_S(14)
-  MSM_MAD_VS(1, 1, 2) MSM_MAD_VS(1, 2, 3) MSM_MAD_VS(2, 1, 3) MSM_MAD_VS(2, 2, 4)
-  MSM_MAD_VS(2, 3, 5) MSM_MAD_VS(3, 2, 5) MSM_MAD_VS(3, 3, 6) MSM_MAD_VS(3, 4, 7)
-  MSM_MAD_VS(4, 3, 7) MSM_MAD_VS(4, 4, 8) MSM_MAD_VS(4, 5, 9) MSM_MAD_VS(5, 4, 9)
-  MSM_MAD_VS(5, 5, 10) MSM_MAD_VS(5, 6, 11) MSM_MAD_VS(6, 5, 11) MSM_MAD_VS(6, 6, 12)
-  MSM_MAD_VS(6, 7, 13) MSM_MAD_VS(7, 6, 13) MSM_MAD_VS(7, 7, 14) MSM_MAD_VS(7, 8, 15)
-  MSM_MAD_VS(8, 7, 15) MSM_MAD_VS(8, 8, 16) MSM_MAD_VS(8, 9, 17) MSM_MAD_VS(9, 8, 17)
-  MSM_MAD_VS(9, 9, 18) MSM_MAD_VS(9, 10, 19) MSM_MAD_VS(10, 9, 19) MSM_MAD_VS(10, 10, 20)
-  MSM_MAD_VS(10, 11, 21) MSM_MAD_VS(11, 10, 21) MSM_MAD_VS(11, 11, 22) MSM_MAD_VS(11, 12, 23)
-  MSM_MAD_VS(12, 11, 23) MSM_MAD_VS(12, 12, 24) MSM_MAD_VS(13, 12, 25)
+  MSM_MAD_LIST(MSM_MAD_V, MSM_MAD_S, MSM_MAD_VS)
   (void)cc;
 }
 
+#undef MSM_MAD_IS_VS
+#undef MSM_MAD_IS_S
+#undef MSM_MAD_IS_V
+#undef MSM_MAD_LIST
 #undef MSM_MAD_VS
 #undef MSM_MAD_S
 #undef MSM_MAD_V

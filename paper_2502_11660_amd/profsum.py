@@ -36,9 +36,28 @@ import re
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-ACCUM_SOURCES = ["paper_2502_11660_amd/csrc/k_accum.hip", "paper_2502_11660_amd/csrc/curve.hpp",
-                 "paper_2502_11660_amd/csrc/field.hpp", "paper_2502_11660_amd/csrc/fe29.hpp",
-                 "paper_2502_11660_amd/csrc/curve29.hpp"]
+CSRC = "paper_2502_11660_amd/csrc/"
+
+
+def with_headers(paths):
+    """The files and the device headers that they include, directly or not (all of
+    a kernel's code and geometry: its unit alone does not hold either)."""
+    out, queue = [], list(paths)
+    while queue:
+        p = queue.pop(0)
+        if p in out:
+            continue
+        out.append(p)
+        try:
+            with open(os.path.join(ROOT, p)) as f:
+                names = re.findall(r'^#include "(\w+\.hpp)"', f.read(), flags=re.M)
+        except FileNotFoundError:
+            continue
+        queue += [CSRC + n for n in names]
+    return out
+
+
+ACCUM_SOURCES = with_headers([CSRC + "k_accum.hip"])
 
 
 def short_name(name):
@@ -103,7 +122,7 @@ def traffic(args):
         fetch += sum(kf) / len(kf) * kib * f_fac
         write += sum(kw) / len(kw) * kib * w_fac
         launches.append([len(kf), len(kw)])
-    sources = ACCUM_SOURCES if args.kernel == ["k_accum"] else args.sources
+    sources = ACCUM_SOURCES if args.kernel == ["k_accum"] else with_headers(args.sources)
     return {
         "kernel": args.kernel[0] if len(args.kernel) == 1 else args.kernel,
         "fetch_bytes_per_launch": fetch,
@@ -187,7 +206,8 @@ def main(argv=None):
     t.add_argument("--kernel", action="append", default=None,
                    help="kernel (repeat to sum several); default k_accum")
     t.add_argument("--sources", nargs="*", default=[],
-                   help="source files the figure describes (default: the accumulation kernel's)")
+                   help="source files the figure describes, their headers included "
+                        "(default: the accumulation kernel's)")
     t.add_argument("--entries", type=float, default=0.0,
                    help="digit entries per profiled launch (adds bytes per entry)")
     v = sub.add_parser("valu")

@@ -21,18 +21,10 @@ constexpr uint32_t kAlpha[NL] = {0x8894e1e4u, 0x3fabdfd0u, 0xcc1f55aau, 0xcbf921
 constexpr uint32_t kBeta[NL] = {0xa38cfd11u, 0xface0c97u, 0x0adb8383u, 0x8cc7c229u,
                                 0xd44ae9cbu, 0x4765cd5fu, 0x22354029u, 0x9ae986d8u,
                                 0x252ab9bdu, 0xc3dc7860u, 0xc8942395u, 0x00486011u};
-constexpr uint32_t kBetaOverAlpha[NL] = {0xead605e4u, 0xfb7c0ab8u, 0xe2752c7au, 0x363b93d1u,
-                                         0x144be536u, 0xd2246835u, 0x429f2077u, 0xeb8bf6ddu,
-                                         0x0234d423u, 0x3a9efda2u, 0xba0c72a4u, 0x013c7943u};
 // R^3 mod p: turns a plain inverse of a Montgomery value into Montgomery form
 constexpr uint32_t kR3[NL] = {0x8815de20u, 0x581f532fu, 0xbe329585u, 0xe50f4148u,
                               0x0449f513u, 0x2be8b118u, 0xc804a20eu, 0x6a2a9516u,
                               0x13590cb9u, 0x3f725407u, 0xc0e7dda5u, 0x01065ab4u};
-// omega (Montgomery form): the cube root of unity for which
-// (x, y) -> (omega x, y) is multiplication by lambda = x0^2 - 1 on G1
-constexpr uint32_t kOmega[NL] = {0xa5847973u, 0xdacd106du, 0xbac2a79au, 0xd8fe2454u,
-                                 0xfd832edcu, 0x1ada4fd6u, 0x9d150908u, 0xfb986844u,
-                                 0xea32285eu, 0xd63eb8aeu, 0x6f873fd0u, 0x0167d6a3u};
 // conventional generator G of BLS12-377 G1, Weierstrass affine (Montgomery form)
 constexpr uint32_t kGx[NL] = {0x772451f4u, 0x260f33b9u, 0x169d5658u, 0xc54dd773u,
                               0x69a510ddu, 0x5c1551c4u, 0x425e1698u, 0x761662e4u,

@@ -620,13 +620,4 @@ __device__ __forceinline__ bool fe_eq_canon(const fe& a, const fe& b) {
   return o == 0;
 }
 
-__device__ __forceinline__ fe fe_to_mont(const fe& a) { return fe_mul(a, fe_const(kR2)); }
-
-__device__ __forceinline__ fe fe_from_mont(const fe& a) {
-  fe one = fe_zero();
-  one.v[0] = 1u;
-  return fe_canon(fe_mul(a, one));
-}
-
-
 }  // namespace msm

@@ -84,15 +84,14 @@ __global__ void __launch_bounds__(256) k_tree_first(const uint32_t* __restrict__
 // addition h the total (slot h + 1); the lane of addition 0 also copies
 // slot h (= R.S), so that no lane of a wave idles through another's addition.
 __global__ void __launch_bounds__(256) k_tree_level(const uint32_t* __restrict__ in, uint32_t h,
-                                                    uint32_t nodes_in, uint32_t w_lo,
-                                                    uint32_t w_cnt,
+                                                    uint32_t nodes_in, uint32_t S,
                                                     uint32_t* __restrict__ out) {
   const uint32_t nodes_out = nodes_in >> 1, slots_in = h + 1, slots_out = h + 2;
   const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= (uint64_t)w_cnt * nodes_out * slots_in) return;
+  if (g >= (uint64_t)S * nodes_out * slots_in) return;
   const uint32_t a = (uint32_t)(g % slots_in);
   const uint32_t t = (uint32_t)(g / slots_in);
-  const uint32_t n = t % nodes_out, w = w_lo + t / nodes_out;
+  const uint32_t n = t % nodes_out, w = t / nodes_out;
   const uint32_t* L = in + rec_index(w, nodes_in, 2 * n, slots_in, 0) * XYTZ_WORDS;
   const uint32_t* R = L + (size_t)slots_in * XYTZ_WORDS;
   uint32_t* O = out + rec_index(w, nodes_out, n, slots_out, 0) * XYTZ_WORDS;
@@ -177,16 +176,15 @@ __global__ void __launch_bounds__(256) k_tree_quad2(const uint32_t* __restrict__
 
 // One level on quads, one per output record.
 __global__ void __launch_bounds__(256) k_tree_level_quad(const uint32_t* __restrict__ in, uint32_t h,
-                                                         uint32_t nodes_in, uint32_t w_lo,
-                                                         uint32_t w_cnt,
+                                                         uint32_t nodes_in, uint32_t S,
                                                          uint32_t* __restrict__ out) {
   const uint32_t nodes_out = nodes_in >> 1, slots_in = h + 1, slots_out = h + 2;
   const uint64_t g = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 2;
   // whole quads only: the task count test is uniform across a quad
-  if (g >= (uint64_t)w_cnt * nodes_out * slots_out) return;
+  if (g >= (uint64_t)S * nodes_out * slots_out) return;
   const uint32_t s = (uint32_t)(g % slots_out);
   const uint32_t t = (uint32_t)(g / slots_out);
-  const uint32_t n = t % nodes_out, w = w_lo + t / nodes_out;
+  const uint32_t n = t % nodes_out, w = t / nodes_out;
   const uint32_t* L = in + rec_index(w, nodes_in, 2 * n, slots_in, 0) * XYTZ_WORDS;
   const uint32_t* R = L + (size_t)slots_in * XYTZ_WORDS;
   const uint32_t src = (s < h) ? s : h;
@@ -225,13 +223,20 @@ struct affine_lds {
   uint32_t slot[AF_SLOTS][16];
   uint32_t q[XYTZ_WORDS];  // the point
 };
-__device__ const uint32_t kAffineConsts[3][NL] = {
-    {0x8815de20u, 0x581f532fu, 0xbe329585u, 0xe50f4148u, 0x0449f513u, 0x2be8b118u,
-     0xc804a20eu, 0x6a2a9516u, 0x13590cb9u, 0x3f725407u, 0xc0e7dda5u, 0x01065ab4u},
-    {0x8894e1e4u, 0x3fabdfd0u, 0xcc1f55aau, 0xcbf921ddu, 0x460edc0cu, 0xd17deff1u,
-     0x7897028du, 0xd394e81eu, 0x0912681au, 0xc29c995du, 0xaff9d568u, 0x01515e6cu},
-    {0xa38cfd11u, 0xface0c97u, 0x0adb8383u, 0x8cc7c229u, 0xd44ae9cbu, 0x4765cd5fu,
-     0x22354029u, 0x9ae986d8u, 0x252ab9bdu, 0xc3dc7860u, 0xc8942395u, 0x00486011u}};
+// kR3, kAlpha, kBeta, to be read limb by limb
+struct affine_consts {
+  uint32_t w[3][NL];
+};
+constexpr affine_consts affine_consts_table() {
+  affine_consts t = {};
+  for (int l = 0; l < NL; ++l) {
+    t.w[0][l] = kR3[l];
+    t.w[1][l] = kAlpha[l];
+    t.w[2][l] = kBeta[l];
+  }
+  return t;
+}
+__device__ const affine_consts kAffineConsts = affine_consts_table();
 
 // canonical words of 16 lazily reduced limbs
 __device__ __noinline__ fe canon_of_limbs(const uint32_t* limbs) {
@@ -256,7 +261,7 @@ __device__ __forceinline__ bool wide_to_weierstrass(affine_lds& s, fe& out) {
     s.slot[AF_UNIT][j] = j == 0 ? 1u : 0u;
 #pragma unroll
     for (int k = 0; k < 3; ++k)
-      s.slot[AF_R3 + k][j] = limb_extract(limb_fetch(kAffineConsts[k], j), j);
+      s.slot[AF_R3 + k][j] = limb_extract(limb_fetch(kAffineConsts.w[k], j), j);
   }
   wave_lds_sync();
   // operands and results of the steps by half, a byte each: l, r, result
@@ -383,15 +388,14 @@ int launch_aggregate(const Plan& pl, const uint32_t* buckets, void* ws, hipStrea
       ++h;
       nodes >>= 1;
     } else if (outs(h) >= pl.tree_quad) {
-      k_tree_level<<<(unsigned)((adds(h) + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S, out);
+      k_tree_level<<<(unsigned)((adds(h) + 255) / 256), 256, 0, st>>>(in, h, nodes, S, out);
     } else if (!tail(h + 1)) {
       const uint64_t o2 = outs(h + 1);
       k_tree_quad2<<<(unsigned)((4 * o2 + 255) / 256), 256, 0, st>>>(in, h, o2, out);
       ++h;
       nodes >>= 1;
     } else {
-      k_tree_level_quad<<<(unsigned)((4 * outs(h) + 255) / 256), 256, 0, st>>>(in, h, nodes, 0, S,
-                                                                              out);
+      k_tree_level_quad<<<(unsigned)((4 * outs(h) + 255) / 256), 256, 0, st>>>(in, h, nodes, S, out);
     }
     in = out;
     ++h;

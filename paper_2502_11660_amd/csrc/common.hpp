@@ -227,6 +227,40 @@ int default_window_for(size_t n, int encoding, size_t jobs = 1, size_t limit = 0
 // work of `jobs` MSMs of n points in all at width c, in digit entries
 double window_work(double n, double jobs, int c, int encoding);
 
+// Picks for many sizes: what a width costs whatever the size is worked out once (a
+// batch of 20000 jobs with c = 0 planned in 14 ms before, 2.8 with this).
+class WidthPicker {
+ public:
+  WidthPicker(int encoding, size_t jobs);
+  int pick(size_t n) const;
+  // among the widths c that may(c) allows; 0 when none is
+  template <typename F>
+  int pick(size_t n, F may) const {
+    int best = 0;
+    double best_cost = 1e300;
+    for (int i = 0; i < count_; ++i) {
+      const double x = cost(widths_[i], mult_ * (double)n);
+      if (x < best_cost && may(widths_[i].c)) {
+        best_cost = x;
+        best = widths_[i].c;
+      }
+    }
+    return best;
+  }
+
+ private:
+  struct Width {
+    int c;
+    double W, work, latency;
+    double digits, crowd;  // the top window's: how many, and the share of entries that has one
+  };
+  double cost(const Width& w, double points) const;
+  double mult_, jobs_;
+  uint32_t simds_;
+  int count_ = 0;
+  Width widths_[17];  // 4 .. 20
+};
+
 // Entries of an accumulation chunk, at least.  Four, the group in which keys are
 // read, give most units a chunk (13 us of accumulation at n = 33 against 108 with
 // sixteen).  A chunk's head and tail take 384 bytes, though, and with four entries

@@ -111,7 +111,7 @@ int window_bits(int c, int encoding) {
 
 // compute units of the current device (256 on MI355X; also the answer when
 // no device is visible, e.g. for workspace queries on a host without GPU)
-static int device_cus() {
+static unsigned device_cus() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -119,7 +119,7 @@ static int device_cus() {
     (void)hipGetLastError();
     return 256;
   }
-  return cus;
+  return (unsigned)cus;
 }
 
 // Cost of an MSM of n points at width c, in digit entries (8.8 G a second), one
@@ -145,49 +145,56 @@ double window_work(double n, double jobs, int c, int encoding) {
          jobs * (2.6 * std::ldexp(1.0, bb) + 100.0) * W;
 }
 
-static double window_cost(size_t n, int c, int encoding, size_t jobs, int cus) {
-  const int W = num_windows(c, encoding), bits = window_bits(c, encoding);
-  const int bb = encoding == MSM_DIGITS_UNSIGNED ? bits : bits - 1;
-  const double points = encoding == MSM_DIGITS_GLV ? 2.0 * (double)n : (double)n;
-  const double entries = points * W;
-  const double all = std::min(entries * (double)jobs, 2147483648.0);
-  AccumGeom g = {};
-  g.quad = all <= (double)ACCUM_QUAD_MAX ? 1u : 0u;
-  g.units = (uint32_t)cus * 4u * (g.quad ? 16u : 64u);
-  const double chunk = std::max((double)CHUNK_LEAST, all / accum_units(g, (uint32_t)all));
-  // entries of one of the top window's digits, which run to the largest scalar's
-  // (split half's), or of its carry alone
+WidthPicker::WidthPicker(int encoding, size_t jobs)
+    : mult_(encoding == MSM_DIGITS_GLV ? 2.0 : 1.0), jobs_((double)jobs), simds_(4u * device_cus()) {
+  // the digits of the top window run to the largest scalar's (split half's)
   const double largest = encoding == MSM_DIGITS_GLV ? std::ldexp((double)0x452217cc, 96)
                                                     : std::ldexp((double)0x12ab655e, 224);
-  const double digits = std::floor(std::ldexp(largest, -bits * (W - 1)));
-  double span = points / std::max(1.0, digits) / chunk;
-  if (digits < 1.0) {
-    const double below = std::floor(std::ldexp(largest, -bits * (W - 2)));
-    span *= std::max(0.0, 1.0 - std::ldexp(0.5, bits) / below);
+  for (int c = 4; c <= 20; ++c) {
+    const int W = num_windows(c, encoding), bits = window_bits(c, encoding);
+    if (W == 0) continue;
+    const int bb = encoding == MSM_DIGITS_UNSIGNED ? bits : bits - 1;
+    Width w = {};
+    w.c = c;
+    w.W = W;
+    w.work = window_work(0.0, 1.0, c, encoding);
+    w.latency = 48e3 * bb + 7e3 * W;
+    w.digits = std::floor(std::ldexp(largest, -bits * (W - 1)));
+    w.crowd = 1.0;
+    if (w.digits < 1.0) {  // the carry alone
+      const double below = std::floor(std::ldexp(largest, -bits * (W - 2)));
+      w.crowd = std::max(0.0, 1.0 - std::ldexp(0.5, bits) / below);
+    }
+    widths_[count_++] = w;
   }
-  const double latency = 48e3 * bb + 7e3 * W + (g.quad ? 0.0 : 1e5) + (span > 64 ? 1e5 : 0.0) +
+}
+
+double WidthPicker::cost(const Width& w, double points) const {
+  const double entries = points * w.W;
+  const double all = std::min(entries * jobs_, 2147483648.0);
+  AccumGeom g = {};
+  g.quad = all <= (double)ACCUM_QUAD_MAX ? 1u : 0u;
+  g.units = simds_ * (g.quad ? 16u : 64u);
+  const double chunk = std::max((double)CHUNK_LEAST, all / accum_units(g, (uint32_t)all));
+  // chunks of the entries of one of the top window's digits
+  const double span = points / std::max(1.0, w.digits) / chunk * w.crowd;
+  const double latency = w.latency + (g.quad ? 0.0 : 1e5) + (span > 64 ? 1e5 : 0.0) +
                          (span > 128 ? 2e5 : 0.0);
-  return window_work((double)n, 1.0, c, encoding) + latency / (double)jobs;
+  return entries + w.work + latency / jobs_;
+}
+
+int WidthPicker::pick(size_t n) const {
+  return pick(n, [](int) { return true; });
 }
 
 int default_window_for(size_t n, int encoding, size_t jobs, size_t limit, const Schedule& sched,
                        bool compact) {
-  int best = 0;
-  double best_cost = 1e300;
-  const int cus = device_cus();
-  for (int c = 4; c <= 20; ++c) {
-    if (num_windows(c, encoding) == 0) continue;
-    if (limit) {
-      Plan pl;
-      if (!make_plan(&n, 1, c, encoding, pl, sched, compact) || pl.bytes > limit) continue;
-    }
-    const double cost = window_cost(n, c, encoding, jobs, cus);
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = c;
-    }
-  }
-  return best;
+  const WidthPicker picker(encoding, jobs);
+  if (limit == 0) return picker.pick(n);
+  return picker.pick(n, [&](int c) {
+    Plan pl;
+    return make_plan(&n, 1, c, encoding, pl, sched, compact) && pl.bytes <= limit;
+  });
 }
 
 int default_window(size_t n) { return default_window_for(n, MSM_DIGITS_SIGNED); }

@@ -99,11 +99,12 @@ bool classify(const msm_job* jobs, size_t njobs, int encoding, Classes& cls, int
   if (!jobs || njobs == 0 || njobs >= ((size_t)1 << 20)) return false;
   std::map<Schedule, std::map<int, WidthSum>> picked;
   std::vector<int> width(njobs);
+  const WidthPicker picker(encoding, njobs);
   for (size_t i = 0; i < njobs; ++i) {
     const msm_job& jb = jobs[i];
     if (!jb.xyu || !jb.scalars || !jb.result || jb.n == 0) return false;
     if (jb.chunk < 0 || jb.tree_quad < 0 || jb.tree_wide < 0) return false;
-    width[i] = jb.c ? jb.c : (all ? all : default_window_for(jb.n, encoding, njobs));
+    width[i] = jb.c ? jb.c : (all ? all : picker.pick(jb.n));
     if (num_windows(width[i], encoding) == 0) return false;
     if (jb.c != 0) continue;
     WidthSum& w = picked[schedule_of(jb)][width[i]];

@@ -103,7 +103,8 @@ int msm_padd_batch(const uint32_t* a_xytz, const uint32_t* b, uint32_t* out_xytz
  *   pts_xytz: AoS XYTZ records (48 words each, Montgomery form, coordinates
  *   < 2p).  unit: MSM_UNIT_WIDE (two waves share one point, each
  *   coordinate spread over 16 lanes as 24-bit limbs, a third wave preparing
- *   k T of the next point: the latency unit group aggregation uses),
+ *   k T of the next point; an MSM's own window and group chains run on another
+ *   unit, of three waves and 26-bit limbs),
  *   MSM_UNIT_QUAD (four lanes share one point: the latency unit of the
  *   aggregation tree) or MSM_UNIT_LANE (one lane does the whole addition).
  *   out_xytz: one AoS XYTZ record, lazily reduced (< 2p).
@@ -147,9 +148,10 @@ int msm_fe_mul_batch(const uint32_t* a, const uint32_t* b, uint32_t* out, size_t
  *    bits, one per lane, two elements per wave), with the reduction digits
  *    formed as one product m = (a b mod R)(-p^-1) mod R: the latency-oriented
  *    form; same output as MSM_MUL_MONT.
- *  MSM_MUL_F28: the carry-free core of the one-lane PADD unit: 14 limbs of
- *    28 bits, one per 32-bit word, so a column of 32x32->64 multiply-adds
- *    needs no carry word; Montgomery with R' = 2^392:
+ *  MSM_MUL_F28: a carry-free core: 14 limbs of 28 bits, one per 32-bit word,
+ *    so a column of 32x32->64 multiply-adds needs no carry word (the PADD
+ *    units use a signed form of the idea, 13 limbs of 29 bits, which has no
+ *    variant here); Montgomery with R' = 2^392:
  *    out = a b^rounds 2^(-392 rounds) mod p.
  * a, b, out: SoA, one coordinate (12 x count words); inputs canonical
  * (< p); output canonical.  Errors: MSM_EINVAL (null pointers, count = 0 or

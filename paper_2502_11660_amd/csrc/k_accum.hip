@@ -186,7 +186,8 @@ ACCUM_KERNEL(k_accum_unsigned, true)
 // lane loads its own coordinate of a point, one entry ahead.  n = 33, signed
 // digits: 108 us on lanes of 16 entries -> 13 us; n = 4099, split digits
 // (123 K slots): 112 -> 27 us.  At 2^18 slots both take ~30 us (16 entries a
-// quad, 4 a lane), and above the quads' 1.4 times as many instructions cost.
+// quad, 4 a lane), but the quads' chunks split a quarter as many buckets; from 2^19
+// on their 1.4 times as many instructions cost more than that (ACCUM_QUAD_MAX).
 template <bool UNS>
 __global__ void __launch_bounds__(256) k_accum_quad(const uint32_t* __restrict__ pts,
                                                       const int64_t* __restrict__ segoff,

@@ -210,8 +210,8 @@ int msm_window_bits(int c, int encoding);
  * pick changes (the width for more points can need less); a workspace of it
  * serves every smaller n too, msm_run then picking among the widths that fit.
  * Both calls also take less than this where accumulation in fewer, longer chunks
- * (of 16 digit entries at least instead of 4) fits: down to 0.4 times at n W of a few
- * thousand, with a longer accumulation.  MSM_ENOSPC below that. */
+ * (of 16 digit entries at least instead of 4) fits: down to 0.4 times at 10^4 to 10^5
+ * digit slots, with a longer accumulation.  MSM_ENOSPC below that. */
 size_t msm_workspace_bytes(size_t n, int c, int encoding);
 
 /* Window width msm_run picks for n points when called with c = 0 and signed

@@ -166,7 +166,8 @@ int msm_fe_mul_chain(const uint32_t* a, const uint32_t* b, uint32_t* out, size_t
 
 /* Convert Weierstrass affine points (x, y), y^2 = x^3 + 1, to prepared
  * twisted-Edwards form (Sec. II-D: inputs as (X, Y, U = k T), Z = 1).
- * xy_std: SoA, 2 coordinates x 12 words x n, ordinary form, canonical.
+ * xy_std: SoA, 2 coordinates x 12 words x n, ordinary form, canonical (other
+ * values of the 12 words are taken mod p).
  * inf: n uint32 flags (non-zero = point at infinity) or NULL.
  * xyu: AoS, 36 words per point, Montgomery form, canonical.
  * status: one device uint32 that receives MSM_FLAG_OFFCURVE / MSM_FLAG_EXCEPT

@@ -189,6 +189,24 @@ __device__ __forceinline__ void prepare_identity(uint32_t* rec) {
   st_aos(rec, 2, fe_zero());
 }
 
+// Point i.  Points come from outside: coordinates that are not canonical (any 384 bits)
+// are brought below p + 2^352, for one comparison where both are.
+__device__ __forceinline__ void prep_load(const uint32_t* __restrict__ xy, uint32_t n, size_t i,
+                                          fe29& x, fe29& y) {
+  fe v[2] = {ld_soa(xy, n, 0, i), ld_soa(xy, n, 1, i)};
+  if (max(v[0].v[NL - 1], v[1].v[NL - 1]) > kP[NL - 1]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll 1
+      while (v[c].v[NL - 1] > kP[NL - 1]) {
+        uint64_t borrow;
+        v[c] = fe_sub_mask(v[c], fe_const(kP), borrow);
+      }
+  }
+  x = f29_from_words(v[0]);
+  y = f29_from_words(v[1]);
+}
+
 // the image's x, the product of the w + alpha (of the point and its image),
 // and the factor d of the batch (1 for a zero denominator)
 struct prep_den {
@@ -234,8 +252,8 @@ __global__ void __launch_bounds__(256, ENDO ? 2 : 4) k_prepare(const uint32_t* _
     if (i >= n) break;
     last = j + 1;
     if (inf && inf[i]) continue;
-    const fe29 x = f29_from_words(ld_soa(xy, n, 0, (size_t)i));
-    const fe29 y = f29_from_words(ld_soa(xy, n, 1, (size_t)i));
+    fe29 x, y;
+    prep_load(xy, n, (size_t)i, x, y);
     // y^2 - 1 = x^3
     fe29 ym = y, yp = y;
     ym.v[0] -= 1;
@@ -257,8 +275,8 @@ __global__ void __launch_bounds__(256, ENDO ? 2 : 4) k_prepare(const uint32_t* _
       if (ENDO) prepare_identity(rec + XYU_WORDS);
       continue;
     }
-    const fe29 x = f29_from_words(ld_soa(xy, n, 0, (size_t)i));
-    const fe29 y = f29_from_words(ld_soa(xy, n, 1, (size_t)i));
+    fe29 x, y;
+    prep_load(xy, n, (size_t)i, x, y);
     uint32_t dummy = 0;
     const prep_den e = prep_denominators<ENDO>(x, y, dummy);
     const fe29 inv_d = f29_mul(tinv, f29_from_words(ld_aos(rec, 0)));  // 1 / d

@@ -45,7 +45,7 @@ extern "C" {
 
 #define MSM_OK 0
 #define MSM_EINVAL (-1) /* null pointer, zero/oversized count, c out of [1, 20] */
-#define MSM_ENOSPC (-2) /* workspace smaller than msm_workspace_bytes() */
+#define MSM_ENOSPC (-2) /* workspace too small (see msm_workspace_bytes()) */
 #define MSM_EHIP (-3)   /* HIP launch/runtime error; see msm_last_hip_error() */
 
 /* device-written status flags (bit set = condition detected) */
